@@ -84,7 +84,6 @@ void free_buffers(bh_ctx *c)
     dfree(c->lam);
     dfree(c->gflag);
     dfree(c->blk);
-    dfree(c->scan_tmp);
     dfree(c->c_first);
     dfree(c->c_count);
     dfree(c->c_end);
@@ -140,7 +139,7 @@ int64_t cell_bound(int64_t n, int64_t K, int nleaf)
 }
 
 struct Sizes {
-    int64_t n, K, chunks, cells, blk, scan, spill_waves;
+    int64_t n, K, chunks, cells, blk, spill_waves;
 };
 
 Sizes sizes_for(bh_ctx *c, int64_t n, int64_t K, int nleaf_min)
@@ -152,7 +151,6 @@ Sizes sizes_for(bh_ctx *c, int64_t n, int64_t K, int nleaf_min)
     z.cells = cell_bound(n, K, nleaf_min);
     z.blk = std::max(sort_blk_words(n),
                      (int64_t)(kLevels + 1) * ((n + kTreeTile - 1) / kTreeTile) + kLevels + 1);
-    z.scan = scan_tmp_words(n);
     z.spill_waves = walk_grid_waves(c);
     return z;
 }
@@ -178,7 +176,6 @@ hipError_t each_buffer(bh_ctx *c, const Sizes &z, F f)
     B(c->lam, z.n);
     B(c->gflag, z.n);
     B(c->blk, z.blk);
-    B(c->scan_tmp, z.scan);
     B(c->c_first, z.cells);
     B(c->c_count, z.cells);
     B(c->c_end, z.cells);

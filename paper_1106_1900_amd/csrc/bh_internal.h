@@ -33,6 +33,12 @@ constexpr int kTreeTile = 256;
 // kMaxGroup particles: a lane carries up to two (or three) of them.
 constexpr int kWalkWaves = 4;
 constexpr int kMaxGroup = 128;
+// Size classes 1..6 of the groups: a walk takes the large ones first.
+constexpr int kGroupClasses = 6;
+__host__ __device__ constexpr uint8_t group_class(uint32_t size)
+{
+    return (uint8_t)(1 + (size >= 9) + (size >= 17) + (size >= 33) + (size >= 49) + (size >= 65));
+}
 constexpr int kStackCap = 1408;        // >= 21 levels x 64 ranges (see walk.hip)
 
 // Per-cell record read by the walk: everything the opening test and a
@@ -98,6 +104,9 @@ struct DevMisc {
     uint32_t ngroups;
     uint32_t depth;
     uint32_t walk_next;                // group work counter of the walk
+    uint32_t team_next;                // the same for the groups walked by whole workgroups
+    uint32_t upto[kGroupClasses];      // groups of class c + 1 or more (the tree's)
+    uint32_t upto_active[kGroupClasses];   // the same of the active list
     uint32_t levels_done;              // levels scanned in the current build (self-clearing)
     uint32_t nactive;                  // groups in the active list of a partial walk
     uint32_t walk_overflow;            // set if a per-wave list would overflow
@@ -175,8 +184,6 @@ struct bh_ctx {
     uint8_t *gflag = nullptr;                // group start flags
     uint32_t *blk = nullptr;                 // per-block counters (levels, sort digits, scans)
     int64_t blk_len = 0;
-    uint32_t *scan_tmp = nullptr;
-    int64_t scan_len = 0;
 
     // ---- cells (level-major, key order within a level) ----
     uint32_t *c_first = nullptr, *c_count = nullptr, *c_child = nullptr, *c_nchild = nullptr;
@@ -260,14 +267,17 @@ hipError_t rebuild_sort_pairs(bh_ctx *c);
 int rebuild_buckets(const bh_ctx *c);      // buckets of that sort (0: radix sort instead)
 int rebuild_candidates(const bh_ctx *c);   // candidate keys the keys kernel writes for it
                                            // to splt + kRadix (0: none)
+// Positions of the non-zero flags (group classes) to idx, their number to *count;
+// the same items (positions, or with rank places in idx) by descending class to
+// order, and to upto[c] how many are of class c + 1 or more.
 hipError_t compact_flags(bh_ctx *c, const uint8_t *flags, int64_t n, uint32_t *idx,
-                         uint32_t *count);
+                         uint32_t *count, uint32_t *order, uint32_t *upto, bool rank);
 int64_t sort_blk_words(int64_t n);
-int64_t scan_tmp_words(int64_t n);
 
 // walk.hip
 hipError_t launch_walk(bh_ctx *c, bool timed, bool active_only = false);
 hipError_t launch_active_groups(bh_ctx *c, const uint8_t *active);   // list for active_only
+uint32_t *walk_order(bh_ctx *c, bool active);  // the groups in the order a walk takes them
 void walk_timer_harvest(bh_ctx *c, bool block);
 hipEvent_t *walk_timer_slot(bh_ctx *c);
 hipError_t launch_scatter(bh_ctx *c, float *acc, float *pot);
@@ -377,6 +387,7 @@ __device__ __forceinline__ void reset_build_counts(DevMisc *m)
     m->nleaves = 0;
     m->ngroups = 0;
     m->walk_next = 0;
+    m->team_next = 0;
     m->ncells = 0;
     m->levels_done = 0;
 }

@@ -553,7 +553,8 @@ emit_cells_kernel(const uint8_t *__restrict__ split, const uint8_t *__restrict__
 // child (0 for a leaf), and the group starts (Sect. 2.2): a cell of at most
 // ncrit particles whose parent holds more (or the root) starts a group at its
 // first particle; a leaf still larger than ncrit is cut into runs of ncrit
-// particles.  Reads the ends of a cell's parent, never its converted fields.
+// particles.  A start's flag is the group's size class.  Reads the ends of a
+// cell's parent, never its converted fields.
 __global__ void __launch_bounds__(kBlock)
 cell_finish_kernel(DevMisc *__restrict__ m, const uint32_t *__restrict__ pcl,
                    const DevCluster *__restrict__ clus, const uint32_t *__restrict__ c_first,
@@ -584,9 +585,10 @@ cell_finish_kernel(DevMisc *__restrict__ m, const uint32_t *__restrict__ pcl,
             const uint32_t p = c_parent[c];
             top = p < ncells && c_end[p] - c_first[p] > ncrit;
         }
-        if (cnt <= ncrit && top) gflag[f] = 1;
+        if (cnt <= ncrit && top) gflag[f] = group_class(cnt);
         if (leaf && cnt > ncrit)
-            for (uint32_t o = 0; o < cnt; o += ncrit) gflag[f + o] = 1;
+            for (uint32_t o = 0; o < cnt; o += ncrit)
+                gflag[f + o] = group_class(min(ncrit, cnt - o));
     }
 }
 
@@ -1180,7 +1182,8 @@ hipError_t launch_tree(bh_ctx *c)
 
 hipError_t launch_groups(bh_ctx *c)
 {
-    return compact_flags(c, c->gflag, c->n, c->g_first, &c->misc->ngroups);
+    return compact_flags(c, c->gflag, c->n, c->g_first, &c->misc->ngroups, walk_order(c, false),
+                         c->misc->upto, true);
 }
 
 hipError_t launch_group_boxes(bh_ctx *c)

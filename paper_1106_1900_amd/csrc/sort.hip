@@ -250,48 +250,106 @@ copy_pairs_kernel(const uint64_t *__restrict__ kin, const uint32_t *__restrict__
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kScanThreads * kScanItems;
+static_assert(kScanTile < 1 << 16, "two counts of a block in one word");
 
-template <typename T>
+// Counts of the classes 1..kGroupClasses in a block, two 16-bit fields a word
+constexpr int kClassWords = (kGroupClasses + 1) / 2;
+struct ClassCounts {
+    uint32_t w[kClassWords];
+};
+
+__device__ __forceinline__ void add_flag(ClassCounts &c, uint8_t f)
+{
+#pragma unroll
+    for (int q = 0; q < kClassWords; ++q)
+        c.w[q] += f == 2 * q + 1 ? 1u : (f == 2 * q + 2 ? 1u << 16 : 0u);
+}
+
+__device__ __forceinline__ uint32_t class_count(const ClassCounts &c, int k)
+{
+    return (k & 1) ? c.w[k / 2] >> 16 : c.w[k / 2] & 0xffffu;
+}
+
+// part[b]: the flags of each class in block b
 __global__ void __launch_bounds__(kScanThreads)
-scan_reduce_kernel(const T *__restrict__ in, int64_t n, uint32_t *__restrict__ part)
+scan_reduce_kernel(const uint8_t *__restrict__ in, int64_t n, ClassCounts *__restrict__ part)
 {
     __shared__ uint32_t s_tmp[4];
     const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-    uint32_t s = 0;
+    ClassCounts c{};
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k)
-        if (base + k < n) s += (uint32_t)in[base + k];
-    uint32_t sum;
-    block_excl_scan_256(s, s_tmp, &sum);
+        if (base + k < n) add_flag(c, in[base + k]);
+    ClassCounts sum;
+#pragma unroll
+    for (int q = 0; q < kClassWords; ++q) block_excl_scan_256(c.w[q], s_tmp, &sum.w[q]);
     if (threadIdx.x == 0) part[blockIdx.x] = sum;
 }
 
-// Writes the positions of set flags, in order, to idx[0..count).  Each block
-// adds up the counts of the blocks before it (part: per-block counts from
-// scan_reduce_kernel); the last block also writes the total to *count.
+// Writes the positions of set flags, in order, to idx[0..count), and the same items
+// (their positions, or with rank their places in idx) to order: the highest class
+// first, each class in order.  Each block adds up the class counts of the blocks
+// before it and of all blocks (part, from scan_reduce_kernel); the last block also
+// writes count and upto[c] = the items of class c + 1 or more.
 __global__ void __launch_bounds__(kScanThreads)
-compact_down_kernel(const uint8_t *__restrict__ flags, int64_t n, const uint32_t *__restrict__ part,
-                    uint32_t *__restrict__ idx, uint32_t *__restrict__ count)
+compact_down_kernel(const uint8_t *__restrict__ flags, int64_t n,
+                    const ClassCounts *__restrict__ part, uint32_t *__restrict__ idx,
+                    uint32_t *__restrict__ count, uint32_t *__restrict__ order,
+                    uint32_t *__restrict__ upto, bool rank)
 {
     __shared__ uint32_t s_tmp[4];
-    uint32_t before = 0;
-    for (uint32_t b = threadIdx.x; b < blockIdx.x; b += kScanThreads) before += part[b];
-    uint32_t sum;
-    block_excl_scan_256(before, s_tmp, &sum);
-    before = sum;
-    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-    uint32_t v[kScanItems];
-    uint32_t s = 0;
+    __shared__ uint32_t s_sum[2][kGroupClasses];    // before this block, in all blocks
+    if (threadIdx.x < 2 * kGroupClasses) (&s_sum[0][0])[threadIdx.x] = 0;
+    uint32_t before[kGroupClasses] = {}, all[kGroupClasses] = {};
+    for (uint32_t b = threadIdx.x; b < gridDim.x; b += kScanThreads) {
+        const ClassCounts c = part[b];
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        v[k] = base + k < n ? (uint32_t)(flags[base + k] != 0) : 0u;
-        s += v[k];
+        for (int k = 0; k < kGroupClasses; ++k) {
+            const uint32_t v = class_count(c, k);
+            all[k] += v;
+            if (b < blockIdx.x) before[k] += v;
+        }
     }
-    uint32_t run = before + block_excl_scan_256(s, s_tmp, &sum);
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *count = before + sum;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kGroupClasses; ++k) {
+        const uint32_t v = wave_sum_u32(before[k]), t = wave_sum_u32(all[k]);
+        if (threadIdx.x % kWave == 0 && t) {
+            atomicAdd(&s_sum[0][k], v);
+            atomicAdd(&s_sum[1][k], t);
+        }
+    }
+    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
+    uint8_t f[kScanItems];
+    ClassCounts c{}, x;
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
-        if (v[k]) idx[run++] = (uint32_t)(base + k);
+        f[k] = base + k < n ? flags[base + k] : (uint8_t)0;
+        add_flag(c, f[k]);
+    }
+    uint32_t sum;
+#pragma unroll
+    for (int q = 0; q < kClassWords; ++q) x.w[q] = block_excl_scan_256(c.w[q], s_tmp, &sum);
+    __syncthreads();
+    uint32_t run = 0, next[kGroupClasses], first = 0;
+    const bool last = blockIdx.x == gridDim.x - 1 && threadIdx.x == 0;
+#pragma unroll
+    for (int k = kGroupClasses - 1; k >= 0; --k) {
+        const uint32_t mine = s_sum[0][k] + class_count(x, k);
+        next[k] = first + mine;
+        run += mine;
+        first += s_sum[1][k];
+        if (last) upto[k] = first;
+    }
+    if (last) *count = first;
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) {
+        if (!f[k]) continue;
+        const uint32_t item = rank ? run : (uint32_t)(base + k);
+        idx[run++] = (uint32_t)(base + k);
+#pragma unroll
+        for (int q = 0; q < kGroupClasses; ++q)
+            if (f[k] == q + 1) order[next[q]++] = item;
     }
 }
 
@@ -703,16 +761,17 @@ int rebuild_candidates(const bh_ctx *c)
 }
 
 hipError_t compact_flags(bh_ctx *c, const uint8_t *flags, int64_t n, uint32_t *idx,
-                         uint32_t *count)
+                         uint32_t *count, uint32_t *order, uint32_t *upto, bool rank)
 {
-    // one block at least, so that the count is written for n = 0 too
+    // one block at least, so that the counts are written for n = 0 too
     const int nblk = std::max(1, (int)((n + kScanTile - 1) / kScanTile));
-    uint32_t *part = c->scan_tmp;
-    hipLaunchKernelGGL(scan_reduce_kernel<uint8_t>, dim3(nblk), dim3(kScanThreads), 0, c->stream,
-                       flags, n, part);
+    // the level and digit counts' buffer: free between the level ranks and the next sort
+    ClassCounts *part = reinterpret_cast<ClassCounts *>(c->blk);
+    hipLaunchKernelGGL(scan_reduce_kernel, dim3(nblk), dim3(kScanThreads), 0, c->stream, flags, n,
+                       part);
     BH_LAUNCH_CHECK();
     hipLaunchKernelGGL(compact_down_kernel, dim3(nblk), dim3(kScanThreads), 0, c->stream, flags, n,
-                       part, idx, count);
+                       part, idx, count, order, upto, rank);
     BH_LAUNCH_CHECK();
     return hipSuccess;
 }
@@ -721,11 +780,6 @@ int64_t sort_blk_words(int64_t n)
 {
     const int64_t nblk = (n + kSortTile - 1) / kSortTile;
     return (int64_t)kRadix * nblk + kRadix;
-}
-
-int64_t scan_tmp_words(int64_t n)
-{
-    return (n + kScanTile - 1) / kScanTile + 1;
 }
 
 }  // namespace bh

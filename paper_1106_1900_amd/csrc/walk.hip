@@ -41,8 +41,8 @@
 // added to the particle's totals with an error-free two-sum (compensated
 // accumulation).
 //
-// Groups are handed out in Morton order (a wavefront's first group is its own
-// index, the rest come from one device-wide counter), so at any
+// Groups are handed out by size class and in Morton order within a class (see
+// team_groups), from one device-wide counter after each wavefront's first, so at any
 // moment all 256 CUs work on neighbouring groups whose interaction lists overlap:
 // the active part of the tree stays small and shared in the Infinity Cache.
 // (Splitting the groups into per-XCD ranges, so that each XCD's L2 sees one
@@ -54,7 +54,6 @@
 namespace bh {
 namespace {
 
-constexpr int kWalkBlock = kWalkWaves * kWave;
 constexpr int kPpCap = 128;
 constexpr int kLdsStack = 128;
 constexpr int kSpillPerWave = kStackCap - kLdsStack;
@@ -110,7 +109,10 @@ struct WalkArgs {
     uint32_t *spill;          // kSpillPerWave entries per wavefront of the grid
     unsigned long long *part; // out: per-workgroup interaction totals (p-p, p-c)
     DevMisc *misc;            // group and cell counts, work counter, interaction totals
-    const uint32_t *glist;    // groups to walk (misc->nactive of them), or null: all
+    const uint32_t *count;    // groups to walk
+    const uint32_t *list;     // these groups in Morton order, or null: 0, 1, ...
+    const uint32_t *order;    // the same by descending size class
+    const uint32_t *upto;     // upto[c]: the groups of class c + 1 or more at its front
 };
 
 struct WaveLds {
@@ -343,13 +345,83 @@ __device__ __forceinline__ void acc_flush(Acc<M> &acc)
     acc.trips = 0;
 }
 
-// after a tile of T trips: flush when the next tile (at most tmax trips) could
-// take a partial past kPlainTerms terms
+// A team: a group walked by the W wavefronts of its workgroup together.  The sum of a
+// particle is built from segments (the tiles between two compensated additions);
+// with W > 1 every wavefront runs the same traversal, and so sees the same tiles
+// and segments, but evaluates only the segments s = w mod W.  After each round of
+// W segments wavefront 0 adds the W partials to the totals in segment order with
+// the same two-sums as a wavefront alone, so the result does not depend on W bit
+// for bit.
+struct Team {
+    WaveLds *all;   // the workgroup's wavefronts
+    int w;          // this wavefront
+    int seg;        // current segment
+};
+
+// where wavefront w > 0 leaves the partials of its particle m for wavefront 0:
+// behind the entries its cell list can hold between evaluations
 template <int M>
-__device__ __forceinline__ void acc_tile_done(Acc<M> &acc, int T, int tmax)
+__device__ __forceinline__ float4 *team_slot(WaveLds &L, int m)
+{
+    static_assert(M <= 3 && kPcCap - kWave >= kTileReach, "a wavefront's partials fit behind its cell list");
+    return (m == 0 ? L.ca : (m == 1 ? L.cb : L.cc)) + (kPcCap - kWave);
+}
+
+// this wavefront's part in a round: its partials (zero if the group has no such
+// segment, which changes no sum) to wavefront 0, which adds them in segment order
+template <int M, int W>
+__device__ __forceinline__ void team_round(Team &t, Acc<M> &acc)
+{
+    const int lane = lane_id();
+    if (t.w != 0) {
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            team_slot<M>(t.all[t.w], m)[lane] = make_float4(acc.px[m], acc.py[m], acc.pz[m], acc.pp[m]);
+            acc.px[m] = acc.py[m] = acc.pz[m] = acc.pp[m] = 0.f;
+        }
+    }
+    __syncthreads();
+    if (t.w == 0) {
+        acc_flush<M>(acc);
+#pragma unroll 1
+        for (int q = 1; q < W; ++q)
+#pragma unroll
+            for (int m = 0; m < M; ++m) {
+                const float4 v = team_slot<M>(t.all[q], m)[lane];
+                comp_add(acc.ax[m], acc.cx[m], v.x);
+                comp_add(acc.ay[m], acc.cy[m], v.y);
+                comp_add(acc.az[m], acc.cz[m], v.z);
+                comp_add(acc.ph[m], acc.cp[m], v.w);
+            }
+    }
+    __syncthreads();
+}
+
+template <int M, int W>
+__device__ __forceinline__ bool team_mine(const Team &t)
+{
+    return W == 1 || (t.seg & (W - 1)) == t.w;
+}
+
+template <int M, int W>
+__device__ __forceinline__ void segment_end(Team &t, Acc<M> &acc)
+{
+    if (W == 1) {
+        acc_flush<M>(acc);
+        return;
+    }
+    if (team_mine<M, W>(t)) team_round<M, W>(t, acc);
+    t.seg += 1;
+    acc.trips = 0;
+}
+
+// after a tile of T trips: the segment ends when the next tile (at most tmax
+// trips) could take a partial past kPlainTerms terms
+template <int M, int W>
+__device__ __forceinline__ void acc_tile_done(Team &team, Acc<M> &acc, int T, int tmax)
 {
     acc.trips += T;
-    if (BH_WALK_COMP_EVERY_TILE || acc.trips + tmax > kPlainTerms) acc_flush<M>(acc);
+    if (BH_WALK_COMP_EVERY_TILE || acc.trips + tmax > kPlainTerms) segment_end<M, W>(team, acc);
 }
 
 template <bool kEps0, int M>
@@ -419,46 +491,50 @@ __device__ __forceinline__ void run_pp(const WaveLds &L, int cnt, const Target<M
 
 // evaluate cnt <= 64 cells of the staged cell list from entry base: the entries
 // a lane may read past them are set to padding (far away, zero mass) first
-template <bool kEps0, int M>
+template <bool kEps0, int M, int W>
 __device__ __forceinline__ void eval_pc(WaveLds &L, int base, int cnt, const Target<M> &t,
-                                        float eps2, Acc<M> &acc)
+                                        float eps2, Team &team, Acc<M> &acc)
 {
     const int lane = lane_id();
     // the lanes read entries up to k ceil(cnt / k) past base
     const int reach = t.k * uniform((cnt + t.k - 1) / t.k);
-    for (int i = base + cnt + lane; i < base + reach; i += kWave) {
-        L.ca[i] = make_float4(kFar, kFar, kFar, 0.0f);
-        L.cb[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        L.cc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (team_mine<M, W>(team)) {
+        for (int i = base + cnt + lane; i < base + reach; i += kWave) {
+            L.ca[i] = make_float4(kFar, kFar, kFar, 0.0f);
+            L.cb[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            L.cc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        wave_sync();
+        if (t.sub < t.k) run_pc<kEps0, M>(L, base, cnt, t, eps2, acc);
     }
-    wave_sync();
-    if (t.sub < t.k) run_pc<kEps0, M>(L, base, cnt, t, eps2, acc);
-    acc_tile_done<M>(acc, reach / t.k, t.tmax);
+    acc_tile_done<M, W>(team, acc, reach / t.k, t.tmax);
     wave_sync();
 }
 
 // stage up to 64 particles (lane j holds particle index idx) and evaluate them
-template <bool kEps0, int M>
+template <bool kEps0, int M, int W>
 __device__ __forceinline__ void eval_pp(const WalkArgs &a, WaveLds &L, uint32_t idx, int cnt,
                                         const double4 gc, const Target<M> &t, float eps2,
-                                        Acc<M> &acc)
+                                        Team &team, Acc<M> &acc)
 {
     const int lane = lane_id();
-    if (lane < cnt) {
-        const double4 p = a.p4[idx];
-        L.ta[lane] = make_float4((float)(p.x - gc.x), (float)(p.y - gc.y), (float)(p.z - gc.z), (float)p.w);
-    } else {
-        L.ta[lane] = make_float4(kFar, kFar, kFar, 0.0f);
+    if (team_mine<M, W>(team)) {
+        if (lane < cnt) {
+            const double4 p = a.p4[idx];
+            L.ta[lane] = make_float4((float)(p.x - gc.x), (float)(p.y - gc.y), (float)(p.z - gc.z), (float)p.w);
+        } else {
+            L.ta[lane] = make_float4(kFar, kFar, kFar, 0.0f);
+        }
+        wave_sync();
+        if (t.sub < t.k) run_pp<kEps0, M>(L, cnt, t, eps2, acc);
     }
-    wave_sync();
-    if (t.sub < t.k) run_pp<kEps0, M>(L, cnt, t, eps2, acc);
-    acc_tile_done<M>(acc, uniform((cnt + t.k - 1) / t.k), t.tmax);
+    acc_tile_done<M, W>(team, acc, uniform((cnt + t.k - 1) / t.k), t.tmax);
     wave_sync();
 }
 
-// the next group after the current one: from the device-wide counter, offset by
-// the W wavefronts of the grid (wavefront w starts with group w, so the launch
-// does not begin with W fetches at one address)
+// the next slot after the current one: from the device-wide counter, offset by
+// the slots that are taken without it (a wavefront's first is its own index, so the
+// launch does not begin with that many fetches at one address)
 __device__ __forceinline__ uint32_t next_slot(const WalkArgs &a, uint32_t waves)
 {
     uint32_t v = 0;
@@ -497,13 +573,15 @@ __device__ __forceinline__ bool mac_accept(const WalkArgs &a, const WalkCell &w,
 }
 
 // One group: walk its cluster's tree from the root, evaluate its lists, and
-// write its particles' accelerations and potentials.  M: particles per lane.
-template <bool kEps0, int M>
-__device__ __forceinline__ void walk_group(const WalkArgs &a, WaveLds &L, CellStack &stack,
-                                           LeafList &leaves, uint32_t ncells, uint32_t gs, int gn,
-                                           const double4 gc, const float4 gh, uint32_t cid,
-                                           float eps2, bool mindist, uint32_t &npp_out,
-                                           uint32_t &npc_out, bool &overflow_out)
+// write its particles' accelerations and potentials.  M: particles per lane;
+// W: wavefronts that walk the group together (1, or the whole workgroup).
+template <bool kEps0, int M, int W>
+__device__ __forceinline__ void walk_group(const WalkArgs &a, WaveLds &L, Team &team,
+                                           CellStack &stack, LeafList &leaves, uint32_t ncells,
+                                           uint32_t gs, int gn, const double4 gc, const float4 gh,
+                                           uint32_t cid, float eps2, bool mindist,
+                                           uint32_t &npp_out, uint32_t &npc_out,
+                                           bool &overflow_out)
 {
     const int lane = lane_id();
     const int P = (gn + M - 1) / M;
@@ -624,7 +702,7 @@ __device__ __forceinline__ void walk_group(const WalkArgs &a, WaveLds &L, CellSt
         }
         if (pc_n >= tsz) {       // pc_n < tsz + 64: one tile of the last tsz entries
             __builtin_amdgcn_s_setprio(0);
-            eval_pc<kEps0, M>(L, pc_n - tsz, tsz, t, eps2, acc);
+            eval_pc<kEps0, M, W>(L, pc_n - tsz, tsz, t, eps2, team, acc);
             pc_n -= tsz;
         }
         while (pend >= (uint32_t)psz) {
@@ -636,13 +714,13 @@ __device__ __forceinline__ void walk_group(const WalkArgs &a, WaveLds &L, CellSt
                 break;
             }
             __builtin_amdgcn_s_setprio(0);
-            eval_pp<kEps0, M>(a, L, idx, n, gc, t, eps2, acc);
+            eval_pp<kEps0, M, W>(a, L, idx, n, gc, t, eps2, team, acc);
             pend -= (uint32_t)n;
         }
         if (overflow) break;
     }
     __builtin_amdgcn_s_setprio(0);
-    if (pc_n > 0) eval_pc<kEps0, M>(L, 0, pc_n, t, eps2, acc);
+    if (pc_n > 0) eval_pc<kEps0, M, W>(L, 0, pc_n, t, eps2, team, acc);
     while (pend > 0) {
         uint32_t idx;
         const int n = pp_n > 0 ? pop64(leaves, pp_n, L.mark, idx, psz) : 0;
@@ -650,11 +728,20 @@ __device__ __forceinline__ void walk_group(const WalkArgs &a, WaveLds &L, CellSt
             overflow = true;
             break;
         }
-        eval_pp<kEps0, M>(a, L, idx, n, gc, t, eps2, acc);
+        eval_pp<kEps0, M, W>(a, L, idx, n, gc, t, eps2, team, acc);
         pend -= (uint32_t)n < pend ? (uint32_t)n : pend;
     }
 
-    if (acc.trips > 0) acc_flush<M>(acc);
+    if (acc.trips > 0) segment_end<M, W>(team, acc);
+    if (W > 1) {
+        // the last round may end before this wavefront's segment
+        const int rest = team.seg & (W - 1);
+        if (rest != 0 && team.w >= rest) team_round<M, W>(team, acc);
+        npp_out = npp;
+        npc_out = npc;
+        overflow_out = overflow;
+        if (team.w != 0) return;
+    }
     // add the k partial sums of each particle: halving steps over the sub-lane
     // index, in a fixed order
     float ax[M], ay[M], az[M], ph[M];
@@ -730,19 +817,81 @@ __device__ __forceinline__ int lanes_mode(int g)
     return best;
 }
 
+// one group by W wavefronts together, in the lane mode of its size
+template <bool kEps0, int W>
+__device__ __forceinline__ void walk_one(const WalkArgs &a, uint32_t g, int gn, WaveLds *all, int w,
+                                         CellStack &stack, LeafList &leaves, uint32_t ncells,
+                                         uint32_t &npp, uint32_t &npc, bool &overflow)
+{
+    const uint32_t gs = a.g_first[g];
+    const double4 gc = a.g_centre[g];
+    const float4 gh = a.g_half[g];
+    // the group's cluster: its root is the cluster's level-0 cell
+    const uint32_t cid = readfirst((uint32_t)gc.w);
+    const float eps2 = a.clus[cid].eps2;
+    const bool mindist = uniform((int)a.clus[cid].mac) != 0;
+    Team team{all, uniform(w), 0};
+    switch (uniform(lanes_mode(gn))) {
+    case 1:
+        walk_group<kEps0, 1, W>(a, all[w], team, stack, leaves, ncells, gs, gn, gc, gh, cid, eps2,
+                                mindist, npp, npc, overflow);
+        break;
+    case 2:
+        walk_group<kEps0, 2, W>(a, all[w], team, stack, leaves, ncells, gs, gn, gc, gh, cid, eps2,
+                                mindist, npp, npc, overflow);
+        break;
+    default:
+        if (kMaxPerLane >= 3)
+            walk_group<kEps0, (kMaxPerLane >= 3 ? 3 : 1), W>(a, all[w], team, stack, leaves, ncells,
+                                                             gs, gn, gc, gh, cid, eps2, mindist,
+                                                             npp, npc, overflow);
+        break;
+    }
+}
+
+// The hand-out.  A group's time grows with its size, up to several times the mean, so
+// a launch ends with wavefronts idle behind the last large groups: all of a small
+// launch, a tenth of one of 55,000 groups.  With V wavefronts in the grid (4096: all
+// that are resident at once), by the number of groups:
+//   up to 24 V    the groups are taken by descending size class (group_class), each
+//                 class in Morton order.  2^20 particles (55,388 groups): 1.69 ->
+//                 1.56 ms; 240,002: 0.38 -> 0.29 ms.  Above, Morton order alone: the
+//                 groups at work then span less of the tree, and 470,942 groups of a
+//                 batch took 7.97 ms so, 8.6 ms by size (the rest of a launch is
+//                 long enough to hide its end);
+//   up to 4 V     the groups of 65 and more (two or three particles per lane) are
+//                 walked first, each by a whole workgroup (a team, see Team): 7210
+//                 groups of up to 128: 0.40 -> 0.23 ms;
+//   up to 1.5 V   so are those of 49 and more: 5376 groups 0.60 -> 0.54 ms (with 33
+//                 and more 0.57: each of a team's wavefronts walks the whole tree);
+//   up to 0.625 V so are those of 33 and more: 1891 groups 0.164 -> 0.106 ms;
+//   up to 0.25 V  all groups are: 926 groups 0.145 -> 0.10 ms.
+// The results do not depend on it bit for bit.
+__device__ __forceinline__ uint32_t team_groups(const WalkArgs &a, uint32_t ngroups, uint32_t waves)
+{
+    if (4 * (uint64_t)ngroups <= waves) return ngroups;
+    if (8 * (uint64_t)ngroups <= 5 * (uint64_t)waves) return a.upto[group_class(33) - 1];
+    if (2 * (uint64_t)ngroups <= 3 * (uint64_t)waves) return a.upto[group_class(49) - 1];
+    if (ngroups <= 4 * (uint64_t)waves) return a.upto[group_class(65) - 1];
+    return 0;
+}
+
 // kEps0: some cluster of the launch has zero softening, so pairs at zero
 // distance (a particle with itself) must be skipped explicitly.
-template <bool kEps0>
-__global__ void __launch_bounds__(kWalkBlock)
+// W: wavefronts per workgroup.  The index of the wavefront is left in a vector register:
+// as a scalar it costs 24 more spilled scalar registers and 0.5% of the walk of
+// 4,194,304 particles.
+template <bool kEps0, int W>
+__global__ void __launch_bounds__(W * kWave)
 __attribute__((amdgpu_waves_per_eu(BH_WALK_WAVES_PER_EU))) walk_kernel(WalkArgs a)
 {
-    const uint32_t ngroups = readfirst(a.glist ? a.misc->nactive : a.misc->ngroups);
+    const uint32_t ngroups = readfirst(*a.count);
     const uint32_t ncells = readfirst(a.misc->ncells);
-    __shared__ WaveLds s_lds[kWalkWaves];
+    __shared__ WaveLds s_lds[W];
     const int w = threadIdx.x / kWave;
     const int lane = lane_id();
     WaveLds &L = s_lds[w];
-    const int64_t wave_global = (int64_t)blockIdx.x * kWalkWaves + w;
+    const int64_t wave_global = (int64_t)blockIdx.x * W + w;
     CellStack stack{L.stack, a.spill + wave_global * kSpillPerWave};
     LeafList leaves{L.pp};
 
@@ -752,36 +901,47 @@ __attribute__((amdgpu_waves_per_eu(BH_WALK_WAVES_PER_EU))) walk_kernel(WalkArgs 
 
     unsigned long long wave_pp = 0, wave_pc = 0;   // interaction totals of this wavefront
     bool wave_overflow = false;
-    const uint32_t waves = gridDim.x * kWalkWaves;
-    for (uint32_t slot = readfirst((uint32_t)wave_global); slot < ngroups;
-         slot = next_slot(a, waves)) {
-        const uint32_t g = a.glist ? readfirst(a.glist[slot]) : slot;
-        const uint32_t gs = a.g_first[g];
+    const uint32_t grid_waves = gridDim.x * W;
+    const bool sorted = ngroups <= 24 * (uint64_t)grid_waves;
+    // groups at the front of the order that whole workgroups take
+    const uint32_t teams = readfirst(team_groups(a, ngroups, grid_waves));
+    __shared__ uint32_t s_next[2];
+    int turn = 0;
+    for (uint32_t slot = blockIdx.x; slot < teams;) {
+        // the next slot is fetched now and read after this group's barriers
+        if (threadIdx.x == 0) s_next[turn] = gridDim.x + atomicAdd(&a.misc->team_next, 1u);
+        const uint32_t g = readfirst(a.order[slot]);
         const int gn = uniform((int)a.g_count[g]);
-        const double4 gc = a.g_centre[g];
-        const float4 gh = a.g_half[g];
-        // the group's cluster: its root is the cluster's level-0 cell
-        const uint32_t cid = readfirst((uint32_t)gc.w);
-        const float eps2 = a.clus[cid].eps2;
-        const bool mindist = uniform((int)a.clus[cid].mac) != 0;
         uint32_t npp = 0, npc = 0;
         bool overflow = false;
-        switch (uniform(lanes_mode(gn))) {
-        case 1:
-            walk_group<kEps0, 1>(a, L, stack, leaves, ncells, gs, gn, gc, gh, cid, eps2, mindist,
-                                 npp, npc, overflow);
-            break;
-        case 2:
-            walk_group<kEps0, 2>(a, L, stack, leaves, ncells, gs, gn, gc, gh, cid, eps2, mindist,
-                                 npp, npc, overflow);
-            break;
-        default:
-            if (kMaxPerLane >= 3)
-                walk_group<kEps0, (kMaxPerLane >= 3 ? 3 : 1)>(a, L, stack, leaves, ncells, gs, gn,
-                                                              gc, gh, cid, eps2, mindist, npp,
-                                                              npc, overflow);
-            break;
+        walk_one<kEps0, W>(a, g, gn, s_lds, w, stack, leaves, ncells, npp, npc, overflow);
+        if (uniform(w) == 0) {
+            if (lane == 0) {
+                a.g_npp[g] = npp;
+                a.g_npc[g] = npc;
+            }
+            wave_pp += (unsigned long long)npp * (unsigned long long)gn;
+            wave_pc += (unsigned long long)npc * (unsigned long long)gn;
         }
+        wave_overflow |= overflow;
+        __syncthreads();
+        slot = readfirst(s_next[turn]);
+        turn ^= 1;
+    }
+    // the workgroups without a team group start with the next slots
+    const uint32_t busy = teams < gridDim.x ? teams : gridDim.x;
+    const uint32_t waves = teams + (gridDim.x - busy) * W;
+    for (uint32_t slot = blockIdx.x < busy
+                             ? next_slot(a, waves)
+                             : teams + (blockIdx.x - busy) * W + readfirst((uint32_t)w);
+         slot < ngroups; slot = next_slot(a, waves)) {
+        uint32_t g = slot;
+        if (sorted) g = readfirst(a.order[slot]);
+        else if (a.list) g = readfirst(a.list[slot]);
+        const int gn = uniform((int)a.g_count[g]);
+        uint32_t npp = 0, npc = 0;
+        bool overflow = false;
+        walk_one<kEps0, 1>(a, g, gn, s_lds, w, stack, leaves, ncells, npp, npc, overflow);
         if (lane == 0) {
             a.g_npp[g] = npp;
             a.g_npc[g] = npc;
@@ -793,8 +953,8 @@ __attribute__((amdgpu_waves_per_eu(BH_WALK_WAVES_PER_EU))) walk_kernel(WalkArgs 
     }
     // the block's totals go to its own slot (summed by walk_sum_kernel): thousands
     // of workgroups adding to one address at the end of the kernel serialise
-    __shared__ unsigned long long s_tot[kWalkWaves][2];
-    __shared__ uint32_t s_over[kWalkWaves];
+    __shared__ unsigned long long s_tot[W][2];
+    __shared__ uint32_t s_over[W];
     if (lane == 0) {
         s_tot[w][0] = wave_pp;
         s_tot[w][1] = wave_pc;
@@ -804,7 +964,7 @@ __attribute__((amdgpu_waves_per_eu(BH_WALK_WAVES_PER_EU))) walk_kernel(WalkArgs 
     if (threadIdx.x == 0) {
         unsigned long long pp = 0, pc = 0;
         uint32_t over = 0;
-        for (int i = 0; i < kWalkWaves; ++i) {
+        for (int i = 0; i < W; ++i) {
             pp += s_tot[i][0];
             pc += s_tot[i][1];
             over |= s_over[i];
@@ -841,6 +1001,7 @@ walk_sum_kernel(const unsigned long long *__restrict__ part, int blocks, DevMisc
         m->tot_npp += s[0][0];
         m->tot_npc += s[1][0];
         m->walk_next = 0;       // the next walk hands out its groups from 0 again
+        m->team_next = 0;
     }
 }
 
@@ -920,8 +1081,9 @@ int64_t walk_grid_waves(bh_ctx *c)
 // The work counter starts at zero (set when the context's device scalars are
 // cleared and at the start of every build) and walk_sum_kernel clears it after
 // each walk; the interaction sums are written by walk_sum_kernel.
-// Flags the groups that hold at least one active particle (flags[g], zero for
-// g >= ngroups up to n so that the flags can be compacted over n entries).
+// Flags the groups that hold at least one active particle with their size class
+// (flags[g]; zero for the others and for g >= ngroups up to n, so that the flags
+// can be compacted over n entries).
 __global__ void __launch_bounds__(256)
 mark_active_groups_kernel(const DevMisc *__restrict__ m, const uint32_t *__restrict__ g_first,
                           const uint32_t *__restrict__ g_count, const uint32_t *__restrict__ pid,
@@ -934,9 +1096,18 @@ mark_active_groups_kernel(const DevMisc *__restrict__ m, const uint32_t *__restr
         if (g < (int64_t)ngroups) {
             const uint32_t s = g_first[g], e = s + g_count[g];
             for (uint32_t i = s; i < e && !f; ++i) f = active[pid[i]] != 0;
+            if (f) f = group_class(e - s);
         }
         flags[g] = f;
     }
+}
+
+// the order in which a walk takes the tree's groups, or those of the last active
+// list: the spare key buffer, which only sorts use
+uint32_t *walk_order(bh_ctx *c, bool active)
+{
+    uint32_t *p = reinterpret_cast<uint32_t *>(c->key[1]);
+    return active ? p + c->n : p;
 }
 
 hipError_t launch_active_groups(bh_ctx *c, const uint8_t *active)
@@ -947,13 +1118,34 @@ hipError_t launch_active_groups(bh_ctx *c, const uint8_t *active)
                        c->g_first, c->g_count, c->pid[c->cur], active, c->n, c->gflag);
     BH_LAUNCH_CHECK();
     // the active group list goes to the sort's spare value buffer
-    return compact_flags(c, c->gflag, c->n, c->val[1], &c->misc->nactive);
+    return compact_flags(c, c->gflag, c->n, c->val[1], &c->misc->nactive, walk_order(c, true),
+                         c->misc->upto_active, false);
+}
+
+// Wavefronts of a workgroup: four, or eight for systems whose few hundred groups
+// leave most of the CUs with one workgroup at most (4096 particles, theta = 0.5:
+// 82 us with either eight or sixteen, 171 us with a wavefront per group; 8192
+// particles: 79 us with eight, 115 us with sixteen).
+constexpr int kWideWaves = 8;
+constexpr int64_t kWideN = 8192;
+
+template <int W>
+void walk_launch(bh_ctx *c, const WalkArgs &a, int64_t blocks)
+{
+    if (c->any_eps0)
+        hipLaunchKernelGGL((walk_kernel<true, W>), dim3((unsigned)blocks), dim3(W * kWave), 0,
+                           c->stream, a);
+    else
+        hipLaunchKernelGGL((walk_kernel<false, W>), dim3((unsigned)blocks), dim3(W * kWave), 0,
+                           c->stream, a);
 }
 
 hipError_t launch_walk(bh_ctx *c, bool timed, bool active_only)
 {
-    int64_t blocks = walk_grid_waves(c) / kWalkWaves;
-    if (blocks * kWalkWaves > c->walk_spill_waves) blocks = c->walk_spill_waves / kWalkWaves;
+    const bool wide = c->n <= kWideN;
+    const int W = wide ? kWideWaves : kWalkWaves;
+    int64_t blocks = walk_grid_waves(c) / W;
+    if (blocks * W > c->walk_spill_waves) blocks = c->walk_spill_waves / W;
     if (blocks < 1) return hipErrorInvalidValue;
     WalkArgs a;
     a.clus = c->clus;
@@ -970,13 +1162,14 @@ hipError_t launch_walk(bh_ctx *c, bool timed, bool active_only)
     a.spill = c->walk_spill;
     a.part = c->walk_part;
     a.misc = c->misc;
-    a.glist = active_only ? c->val[1] : nullptr;
+    a.count = active_only ? &c->misc->nactive : &c->misc->ngroups;
+    a.order = walk_order(c, active_only);
+    a.upto = active_only ? c->misc->upto_active : c->misc->upto;
+    a.list = active_only ? c->val[1] : nullptr;
     hipEvent_t *ev = timed ? walk_timer_slot(c) : nullptr;
     if (ev) BH_HIP_TRY(hipEventRecord(ev[0], c->stream));
-    if (c->any_eps0)
-        hipLaunchKernelGGL(walk_kernel<true>, dim3((unsigned)blocks), dim3(kWalkBlock), 0, c->stream, a);
-    else
-        hipLaunchKernelGGL(walk_kernel<false>, dim3((unsigned)blocks), dim3(kWalkBlock), 0, c->stream, a);
+    if (wide) walk_launch<kWideWaves>(c, a, blocks);
+    else walk_launch<kWalkWaves>(c, a, blocks);
     BH_LAUNCH_CHECK();
     if (ev) BH_HIP_TRY(hipEventRecord(ev[1], c->stream));
     hipLaunchKernelGGL(walk_sum_kernel, dim3(1), dim3(256), 0, c->stream, c->walk_part,
