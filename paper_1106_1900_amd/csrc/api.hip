@@ -77,7 +77,6 @@ void free_buffers(bh_ctx *c)
         dfree(c->key[i]);
         dfree(c->val[i]);
     }
-    dfree(c->splt);
     dfree(c->acc4);
     dfree(c->pcl);
     dfree(c->split);
@@ -169,7 +168,6 @@ hipError_t each_buffer(bh_ctx *c, const Sizes &z, F f)
         B(c->key[i], z.n);
         B(c->val[i], z.n);
     }
-    B(c->splt, (int64_t)kRadix * 5);
     B(c->acc4, z.n);
     B(c->pcl, z.n);
     B(c->split, z.n);
@@ -371,7 +369,7 @@ int load_table(bh_ctx *c, const std::vector<bh_cluster> &cl, int64_t n)
 {
     TRY_ST(staging_ready(c));
     const int64_t K = (int64_t)cl.size();
-    int64_t first = 0, nch = 0;
+    int64_t first = 0, nch = 0, nmax = 0;
     int lmax = 1;
     for (int64_t k = 0; k < K; ++k) {
         const bh_cluster &q = cl[k];
@@ -394,11 +392,25 @@ int load_table(bh_ctx *c, const std::vector<bh_cluster> &cl, int64_t n)
         d.nchunk = (uint32_t)(nch - d.chunk0);
         c->clus_h[k] = d;
         lmax = std::max(lmax, (int)q.nleaf);
+        nmax = std::max(nmax, q.n);
         first += q.n;
     }
     c->n = n;
     c->K = K;
     c->nchunks = nch;
+    c->max_cluster = nmax;
+    // the sort's buckets and counts (none if it does not use them)
+    c->nbuckets = c->nhist = 0;
+    const int64_t sub = sort_sub(c);
+    for (int64_t k = 0; k < K && sub > 0; ++k) {
+        DevCluster &d = c->clus_h[k];
+        d.bucket0 = (uint32_t)c->nbuckets;
+        d.hist0 = (uint32_t)c->nhist;
+        if (d.nchunk > 1) {
+            c->nbuckets += sub * d.nchunk;
+            c->nhist += sub * d.nchunk * d.nchunk;
+        }
+    }
     c->max_nleaf = lmax;
     c->host_clusters = cl;
     c->rec_fresh = false;
@@ -464,7 +476,7 @@ hipError_t enqueue_load(bh_ctx *c, const double *pos, const double *mass, const 
     BH_HIP_TRY(launch_domain(c, pos));
     BH_HIP_TRY(launch_keys(c, pos));
     BH_HIP_TRY(rec(c, 1));
-    BH_HIP_TRY(radix_sort_pairs(c));
+    BH_HIP_TRY(sort_pairs(c, false));
     BH_HIP_TRY(rec(c, 2));
     BH_HIP_TRY(launch_reorder_from_caller(c, pos, mass, vel, c->val[0]));
     return enqueue_finish_build(c);
@@ -478,7 +490,7 @@ hipError_t enqueue_rebuild(bh_ctx *c)
     BH_HIP_TRY(launch_domain(c, nullptr));
     BH_HIP_TRY(launch_keys(c, nullptr));
     BH_HIP_TRY(rec(c, 1));
-    BH_HIP_TRY(rebuild_sort_pairs(c));
+    BH_HIP_TRY(sort_pairs(c, true));
     BH_HIP_TRY(rec(c, 2));
     BH_HIP_TRY(launch_reorder(c, c->val[0]));
     return enqueue_finish_build(c);

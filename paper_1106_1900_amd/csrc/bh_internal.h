@@ -68,9 +68,11 @@ struct DevCluster {
     uint32_t chunk0;     // first chunk of the cluster in the chunk table
     uint32_t nchunk;     // chunks of the cluster
     uint32_t mac;        // opening test: 0 Eq. (1), 1 minimum distance
+    uint32_t bucket0;    // sort: buckets of the clusters with several chunks before this one
+    uint32_t hist0;      // sort: first of its counts per bucket and chunk
     uint32_t pad;
 };
-static_assert(sizeof(DevCluster) == 48, "cluster record layout");
+static_assert(sizeof(DevCluster) == 56, "cluster record layout");
 
 // The cubic domain of one cluster (App. B), computed on the device at each build.
 struct DevDomain {
@@ -132,6 +134,9 @@ struct bh_ctx {
     int64_t n = 0;          // particles in the current system (all clusters)
     int64_t K = 0;          // clusters
     int64_t nchunks = 0;
+    int64_t max_cluster = 0;    // particles in the largest cluster
+    int64_t nbuckets = 0;       // sort buckets of the clusters with several chunks
+    int64_t nhist = 0;          // their counts per bucket and chunk
     int max_nleaf = 16;     // largest leaf size over the clusters (LDS halo of the tree build)
     int64_t cap_n = 0;      // particle capacity of the buffers
     int64_t cap_c = 0;      // cell capacity
@@ -178,7 +183,6 @@ struct bh_ctx {
     float4 *acc4 = nullptr;                  // ax, ay, az, pot (sorted order)
     uint64_t *key[2] = {nullptr, nullptr};   // sort ping-pong
     uint32_t *val[2] = {nullptr, nullptr};
-    uint64_t *splt = nullptr;                // a rebuild's sort: splitters, then candidates
     uint8_t *split = nullptr;                // level at which particle i leaves i-1's cell
     uint8_t *lam = nullptr;                  // level of the leaf holding particle i
     uint8_t *gflag = nullptr;                // group start flags
@@ -259,14 +263,13 @@ hipError_t launch_rcrit(bh_ctx *c);                 // per-cluster theta; also f
 hipError_t launch_cluster_ids(bh_ctx *c);           // pcl from the chunk table
 
 // sort.hip
-hipError_t radix_sort_pairs(bh_ctx *c);             // sorts key[0]/val[0] of n particles
-                                                    // within clusters; result in key[0]/val[0]
-// The same result for one cluster whose particles are held in the previous
-// build's order (a rebuild); falls back to radix_sort_pairs where it does not apply.
-hipError_t rebuild_sort_pairs(bh_ctx *c);
-int rebuild_buckets(const bh_ctx *c);      // buckets of that sort (0: radix sort instead)
-int rebuild_candidates(const bh_ctx *c);   // candidate keys the keys kernel writes for it
-                                           // to splt + kRadix (0: none)
+// Sorts key[0]/val[0] of the n particles within their clusters by key, equal keys in
+// caller order; result in key[0]/val[0].  held: the pairs come in the held order
+// (sort_sub > 0 only), else in caller order.
+hipError_t sort_pairs(bh_ctx *c, bool held);
+int sort_sub(const bh_ctx *c);             // buckets per chunk (0: radix sort)
+uint64_t *sort_candidates(bh_ctx *c);      // where the keys kernel puts the candidates
+constexpr int kSortOver = 16;              // candidates per bucket
 // Positions of the non-zero flags (group classes) to idx, their number to *count;
 // the same items (positions, or with rank places in idx) by descending class to
 // order, and to upto[c] how many are of class c + 1 or more.

@@ -192,19 +192,30 @@ domain_kernel(const double *__restrict__ part, const DevCluster *__restrict__ cl
 // are the caller order, a first load) with value i.  The stable sort that
 // follows then orders equal keys by caller index, on a first load and on every
 // rebuild alike (App. A: the split primitive keeps the input order).  With
-// held != 0 the pair goes to slot i instead (a rebuild's bucket sort, which
-// orders equal keys by pid itself).  With ncand > 0 the keys at positions
-// (c + 1) cstride, c < ncand, are also written to cand[c] (the candidate
-// splitters of that sort).
+// held != 0 the pair goes to slot i instead (the bucket sort, which orders equal keys
+// by pid itself).  With sub > 0 (buckets per chunk) the clusters of several chunks
+// also get their candidate splitters: kSortOver keys per bucket, one from each of
+// as many equal stretches of the cluster, its place drawn from a hash of its number.
 template <typename Src>
 __global__ void __launch_bounds__(kBlock)
 keys_kernel(Src src, const Chunk *__restrict__ chunks, const DevDomain *__restrict__ dom,
             const uint32_t *__restrict__ pid, uint32_t n, uint64_t *__restrict__ key,
-            uint32_t *__restrict__ val, uint32_t held, uint64_t *__restrict__ cand,
-            uint32_t ncand, uint32_t cstride, DevMisc *m)
+            uint32_t *__restrict__ val, uint32_t held, const DevCluster *__restrict__ clus,
+            uint32_t sub, uint64_t *__restrict__ cand, DevMisc *m)
 {
     const Chunk ch = chunks[blockIdx.x];
     const DevDomain &cl = dom[ch.cluster];
+    uint32_t ncand = 0, stretch = 1, first = 0;
+    if (sub) {
+        const DevCluster &dc = clus[ch.cluster];
+        if (dc.nchunk > 1) {
+            ncand = dc.nchunk * sub * kSortOver;
+            stretch = dc.n / ncand;         // 32 or more: a chunk gives 64 candidates at most
+            first = dc.first;
+            cand += (uint64_t)dc.bucket0 * kSortOver;
+        }
+    }
+    const double inv = 1.0 / (double)stretch;
     const double lx = cl.lo[0], ly = cl.lo[1], lz = cl.lo[2], scale = cl.scale;
     // kKeyBatch elements per thread at a time: all their loads are issued before
     // the scattered stores, which the compiler may not move loads across
@@ -236,8 +247,10 @@ keys_kernel(Src src, const Chunk *__restrict__ chunks, const DevDomain *__restri
             key[dst] = k;
             val[dst] = i;
             if (ncand) {
-                const uint32_t q = (uint32_t)(((double)i + 0.5) / (double)cstride);
-                if (q >= 1u && q <= ncand && q * cstride == i) cand[q - 1] = k;
+                const uint32_t j = i - first;
+                const uint32_t q = (uint32_t)(((double)j + 0.5) * inv);
+                const uint32_t at = (((q * 2654435761u) >> 16) * stretch) >> 16;
+                if (q < ncand && j - q * stretch == at) cand[q] = k;
             }
         }
     }
@@ -1112,21 +1125,19 @@ hipError_t launch_domain(bh_ctx *c, const double *pos_aos)
 
 hipError_t launch_keys(bh_ctx *c, const double *pos_aos)
 {
+    const uint32_t sub = c->nbuckets > 0 ? (uint32_t)sort_sub(c) : 0u;
+    const uint32_t held = sort_sub(c) > 0 ? 1u : 0u;
     if (pos_aos)
         hipLaunchKernelGGL(keys_kernel<AosSrc>, dim3((unsigned)c->nchunks), dim3(kBlock), 0,
                            c->stream, AosSrc{pos_aos}, c->chunks, c->dom, nullptr, (uint32_t)c->n,
-                           c->key[0], c->val[0], 0u, nullptr, 0u, 0u, c->misc);
-    else {
-        // a rebuild: held-order pairs and the candidate splitters for its bucket
-        // sort, at a fixed stride (or caller-order pairs for the radix sort)
-        const uint32_t held = rebuild_buckets(c) > 0 ? 1u : 0u;
-        const uint32_t ncand = (uint32_t)rebuild_candidates(c);
-        const uint32_t cstride = ncand ? (uint32_t)(c->n / (ncand + 1)) : 0u;
+                           c->key[0], c->val[0], 0u, c->clus, sub, sort_candidates(c), c->misc);
+    else
+        // a rebuild: held-order pairs for the bucket sort, caller-order pairs for
+        // the radix sort
         hipLaunchKernelGGL(keys_kernel<P4Src>, dim3((unsigned)c->nchunks), dim3(kBlock), 0,
                            c->stream, P4Src{c->p4[c->cur]}, c->chunks, c->dom, c->pid[c->cur],
-                           (uint32_t)c->n, c->key[0], c->val[0], held, c->splt + kRadix, ncand,
-                           cstride, c->misc);
-    }
+                           (uint32_t)c->n, c->key[0], c->val[0], held, c->clus, sub,
+                           sort_candidates(c), c->misc);
     BH_LAUNCH_CHECK();
     return hipSuccess;
 }

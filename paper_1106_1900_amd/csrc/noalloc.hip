@@ -72,6 +72,8 @@ static_table_kernel(uint32_t n, float theta, float eps, DevCluster *__restrict__
         d.chunk0 = 0;
         d.nchunk = nch;
         d.mac = 0;
+        d.bucket0 = 0;
+        d.hist0 = 0;
         d.pad = 0;
         clus[0] = d;
     }
@@ -171,6 +173,9 @@ int bh_forces_static(const double *pos, const double *mass, int64_t n, float the
     c.n = n;
     c.K = 1;
     c.nchunks = nch;
+    c.max_cluster = n;
+    c.nbuckets = nch > 1 ? nch * sort_sub(&c) : 0;
+    c.nhist = c.nbuckets * nch;
     c.max_nleaf = kStaticNleaf;
     c.any_eps0 = !(eps > 0.0f) || !(eps * eps > 0.0f);
     c.layout += 1;

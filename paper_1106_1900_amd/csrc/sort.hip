@@ -1,13 +1,14 @@
-// sort.hip - scan, compaction and the stable LSD radix sort of (key, index)
-// pairs (App. A: count, scan offsets, place; radix sort by stable passes from the
-// least significant digit up).
+// sort.hip - compaction and the sorts of (key, index) pairs (App. A: count, scan
+// offsets, place; stable passes).
 //
-// The paper splits one bit per pass; here each pass places an 8-bit digit, which
-// is the same stable partition done for 256 buckets at once: 8 passes over the
-// 60-bit keys.  For a batch of clusters, further stable passes on the cluster of
-// each element follow, so the keys end up sorted within each cluster and the
-// clusters keep their places.  Each pass is reduce-then-scan (no inter-block
-// waiting):
+// Clusters of up to 2^20 particles are sorted through buckets (below): one pass
+// that places the pairs by key range and one workgroup per bucket.  A batch with a
+// larger cluster takes a stable LSD radix sort.  The paper splits one bit per pass;
+// here each pass places an 8-bit digit, which is the same stable partition done for
+// 256 buckets at once: 8 passes over the 60-bit keys.  For a batch of clusters,
+// further stable passes on the cluster of each element follow, so the keys end up
+// sorted within each cluster and the clusters keep their places.  Each pass is
+// reduce-then-scan (no inter-block waiting):
 //   1. hist:    per-block digit counts, stored digit-major;
 //   2. scan:    one block per digit scans that digit's counts over blocks;
 //   3. scatter: each block ranks its keys stably (wavefront match on the digit
@@ -25,18 +26,6 @@ namespace {
 __device__ __forceinline__ uint32_t digit_of(uint64_t k, uint32_t v, const uint32_t *cl, int shift)
 {
     return cl ? ((cl[v] >> shift) & (kRadix - 1)) : ((uint32_t)(k >> shift) & (kRadix - 1));
-}
-
-// bucket of a key among kRadix - 1 ascending splitters (unused ones are ~0):
-// the number of splitters below it, so equal keys share a bucket and buckets
-// follow key order
-__device__ __forceinline__ uint32_t bucket_of(uint64_t k, const uint64_t *spl)
-{
-    uint32_t b = 0;
-#pragma unroll
-    for (uint32_t step = kRadix / 2; step > 0; step >>= 1)
-        if (spl[b + step - 1] < k) b += step;
-    return b;
 }
 
 // The lanes of the wavefront that are valid and hold the same 8-bit digit as
@@ -89,32 +78,22 @@ __device__ uint32_t block_excl_scan_256(uint32_t v, uint32_t *s_tmp, uint32_t *t
     return off + inc - v;
 }
 
-constexpr int kSplitOver = 4;           // candidate keys per bucket of a rebuild's sort
-constexpr int kCand = kRadix * kSplitOver;
-
-// The digit of a pass is a radix digit of the key (or of the element's cluster),
-// or, with splitters (spl != NULL: kRadix - 1 ascending keys, unused ones ~0),
-// the key's bucket.
+// The digit of a pass is a radix digit of the key (or of the element's cluster).
 __global__ void __launch_bounds__(kSortThreads)
 hist_kernel(const uint64_t *__restrict__ keys, const uint32_t *__restrict__ vals,
-            const uint32_t *__restrict__ cl, const uint64_t *__restrict__ spl, int64_t n,
-            int shift, uint32_t *__restrict__ hist, int nblk)
+            const uint32_t *__restrict__ cl, int64_t n, int shift, uint32_t *__restrict__ hist,
+            int nblk)
 {
     __shared__ uint32_t cnt[kRadix];
-    __shared__ uint64_t s_spl[kRadix];
     const int t = threadIdx.x;
     cnt[t] = 0;
-    if (spl && t < kRadix - 1) s_spl[t] = spl[t];
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * kSortTile;
 #pragma unroll
     for (int k = 0; k < kSortItems; ++k) {
         int64_t i = base + (int64_t)k * kSortThreads + t;
         if (i < n) {
-            const uint64_t key = keys[i];
-            const uint32_t d = spl ? bucket_of(key, s_spl)
-                                   : digit_of(key, cl ? vals[i] : 0u, cl, shift);
-            atomicAdd(&cnt[d], 1u);
+            atomicAdd(&cnt[digit_of(keys[i], cl ? vals[i] : 0u, cl, shift)], 1u);
         }
     }
     __syncthreads();
@@ -142,15 +121,13 @@ scan_digit_kernel(uint32_t *__restrict__ hist, int nblk, uint32_t *__restrict__ 
 __global__ void __launch_bounds__(kSortThreads)
 scatter_kernel(const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin,
                uint64_t *__restrict__ kout, uint32_t *__restrict__ vout,
-               const uint32_t *__restrict__ cl, const uint64_t *__restrict__ spl, int64_t n,
-               int shift, const uint32_t *__restrict__ hist,
-               const uint32_t *__restrict__ tot, int nblk)
+               const uint32_t *__restrict__ cl, int64_t n, int shift,
+               const uint32_t *__restrict__ hist, const uint32_t *__restrict__ tot, int nblk)
 {
     __shared__ uint32_t s_wcnt[kSortThreads / kWave][kRadix];  // per-wave digit counts
     __shared__ uint32_t s_base[kRadix];                         // global digit base
     __shared__ uint32_t s_local[kRadix];                        // block-local digit start
     __shared__ uint32_t s_tmp[4];
-    __shared__ uint64_t s_spl[kRadix];
     __shared__ uint64_t s_key[kSortTile];
     __shared__ uint32_t s_val[kSortTile];
     __shared__ uint8_t s_dig[kSortTile];
@@ -168,7 +145,6 @@ scatter_kernel(const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vi
         uint32_t ex = block_excl_scan_256(tot[t], s_tmp, &sum);
         s_base[t] = ex;
     }
-    if (spl && t < kRadix - 1) s_spl[t] = spl[t];
     __syncthreads();
 
     uint64_t key[kSortItems];
@@ -183,7 +159,7 @@ scatter_kernel(const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vi
         key[k] = valid ? kin[base + p] : 0ull;
         val[k] = valid ? vin[base + p] : 0u;
         uint32_t d = 0;
-        if (valid) d = spl ? bucket_of(key[k], s_spl) : digit_of(key[k], val[k], cl, shift);
+        if (valid) d = digit_of(key[k], val[k], cl, shift);
         dig[k] = d;
         const unsigned long long peers = match_digit(d, valid);
         uint32_t before = s_wcnt[w][d];
@@ -355,98 +331,315 @@ compact_down_kernel(const uint8_t *__restrict__ flags, int64_t n,
 
 
 // ---------------------------------------------------------------------------
-// Sort of a rebuild.  The particles are held in the previous build's key order
-// and move little between builds, so the new keys taken at regular positions of
-// that order (the candidates, written by the keys kernel) split the new key
-// range into buckets of similar size.  One stable pass places the pairs by
-// bucket (the same three kernels as a radix pass, with the bucket as the digit),
-// and one workgroup per bucket sorts it by key, stably.  The pairs arrive in the
-// held order (the keys kernel writes them without the scatter to caller order);
-// a bucket holding equal keys orders them by caller index, so the result is the
-// stable radix sort's of the pairs in caller order, bit for bit.
+// Sort through buckets.  A cluster of one chunk is one bucket.  A larger one gets
+// sub buckets per chunk (256 at most), split at keys sampled at about regular places
+// of the pairs' order (the candidates, kOver per bucket, written by the keys
+// kernel; every place is drawn within its stretch, so that inputs with a period
+// of their own are sampled evenly).  One stable pass places the pairs by bucket,
+// and one workgroup per bucket sorts it by key, stably.  A load's pairs arrive in
+// caller order.  A rebuild's arrive in the held order (the keys kernel writes them
+// without the scatter to caller order), and equal keys are then ordered by caller
+// index, so the result is the stable sort's of the pairs in caller order, bit for
+// bit, either way.
+//
+// A bucket is a workgroup's LDS sort, so few pairs make little work but the same
+// chain of passes: sub is chosen so that the device has a workgroup per CU or two
+// (sort_sub).  Loads took eight radix passes (24 launches) before: 100,003
+// particles 138 -> 62 us of kernels, 4096 125 -> 30 us.
 
-constexpr int kBucketTarget = 4096;     // mean bucket size the bucket count aims at
-constexpr int kBucketCap = 12288;       // largest bucket sorted in LDS
+constexpr uint32_t kOver = kSortOver;   // candidate keys per bucket
 constexpr int kBucketThreads = 1024;
 constexpr int kBucketWaves = kBucketThreads / kWave;
+constexpr int kPassThreads = 512;       // workgroup of the bucket pass: one chunk
+constexpr int kPassItems = kChunk / kPassThreads;
+constexpr int kPassWaves = kPassThreads / kWave;
+static_assert(kChunk == 4096, "bucket counts below are per 4096 particles");
 
-// Splitters of nspl + 1 buckets: the ncand candidate keys in sorted order, every
-// kSplitOver-th kept, kRadix - 1 values with the unused ones ~0.  Each workgroup
-// ranks kSplitOver candidates against all of them (ties by index: ranks are a
-// permutation) and the candidate of rank (b + 1) kSplitOver - 1 becomes splitter
-// b; the grid has kRadix workgroups.
-__global__ void __launch_bounds__(kCand)
-splitter_kernel(const uint64_t *__restrict__ cand, int ncand, int nspl, uint64_t *__restrict__ spl)
+// The buckets of a cluster, from its record: none of its own pass for one chunk.
+__device__ __forceinline__ uint32_t cluster_buckets(const DevCluster &cl, uint32_t sub)
 {
-    __shared__ uint32_t s_cnt[kSplitOver][kCand / kWave];
-    const int t = threadIdx.x, w = t / kWave, lane = t % kWave;
-    const uint64_t mine = t < ncand ? cand[t] : 0ull;
-#pragma unroll
-    for (int q = 0; q < kSplitOver; ++q) {
-        const int c = blockIdx.x * kSplitOver + q;      // the candidate ranked
-        uint32_t below = 0;
-        if (c < ncand && t < ncand) {
-            const uint64_t v = cand[c];
-            below = (mine < v || (mine == v && t < c)) ? 1u : 0u;
-        }
-        below = wave_sum_u32(below);
-        if (lane == 0) s_cnt[q][w] = below;
-    }
-    __syncthreads();
-    if (t < kSplitOver) {
-        const int c = blockIdx.x * kSplitOver + t;
-        if (c < ncand) {
-            uint32_t r = 0;
-            for (int q = 0; q < kCand / kWave; ++q) r += s_cnt[t][q];
-            if ((r + 1) % kSplitOver == 0 && (int)(r / kSplitOver) < nspl)
-                spl[r / kSplitOver] = cand[c];
-        }
-    }
-    if (blockIdx.x == 0)
-        for (int b = nspl + t; b < kRadix - 1; b += kCand) spl[b] = ~0ull;
+    return cl.nchunk > 1 ? cl.nchunk * sub : 1u;
 }
 
-// One workgroup per bucket: the bucket's pairs (k1, v1)[lo, lo + L) are sorted
-// stably by key into (k0, v0)[lo, lo + L).  With pid == NULL the pairs arrive in
-// caller order; otherwise in the held order (value = held position, pid[value] =
-// caller index), and equal keys are put in caller order explicitly.  Up to
-// kBucketCap pairs are sorted in LDS by stable 8-bit passes (keys and positions
-// move, values are gathered at the end), skipping the digits every key of the
-// bucket shares; a bucket holding equal keys is then sorted again, by caller index
-// first and by key after it.  A larger bucket (many equal or clustered keys) is
-// sorted by the workgroup with the same passes through (k0, v0) and back.
+// bucket of a key among kRadix - 1 ascending splitters (unused ones are ~0): the
+// number of splitters below it, so equal keys share a bucket and buckets follow
+// key order; a key that two or more splitters equal has the second one's bucket
+// to itself (a bucket of one key needs no sort, however many pairs it holds)
+__device__ __forceinline__ uint32_t bucket_of(uint64_t k, const uint64_t *spl)
+{
+    uint32_t b = 0;
+#pragma unroll
+    for (uint32_t step = kRadix / 2; step > 0; step >>= 1)
+        if (spl[b + step - 1] < k) b += step;
+    if (b < kRadix - 2 && spl[b] == k && spl[b + 1] == k) ++b;
+    return b;
+}
+
+// One workgroup per bucket of a cluster with several chunks: ranks kOver of the
+// cluster's candidates against all of them, a wavefront each (ties by index: ranks
+// are a permutation); the candidate of rank (b + 1) kOver - 1 becomes splitter b.
+// (One workgroup per chunk, with up to 64 candidates: 25 us for 3776 of them, 8 us so.)
+__global__ void __launch_bounds__(1024)
+splitter_kernel(const Chunk *__restrict__ chunks, const DevCluster *__restrict__ clus, uint32_t sub,
+                const uint64_t *__restrict__ cand, uint64_t *__restrict__ spl)
+{
+    constexpr uint32_t kTile = 2048;
+    __shared__ uint64_t s_c[kTile];
+    static_assert(kOver == 1024 / kWave, "a wavefront per candidate");
+    const uint32_t chunk = blockIdx.x / sub;
+    const DevCluster &cl = clus[chunks[chunk].cluster];
+    if (cl.nchunk < 2) return;
+    const uint32_t nb = cl.nchunk * sub, ncand = nb * kOver;
+    const uint64_t *cc = cand + (uint64_t)cl.bucket0 * kOver;
+    const uint32_t b = (chunk - cl.chunk0) * sub + blockIdx.x % sub;
+    const uint32_t c = b * kOver + threadIdx.x / kWave;
+    const uint32_t part = threadIdx.x % kWave;
+    const uint64_t mine = cc[c];
+    uint32_t below = 0;
+    for (uint32_t t0 = 0; t0 < ncand; t0 += kTile) {
+        const uint32_t m = min(kTile, ncand - t0);
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i < m; i += 1024) s_c[i] = cc[t0 + i];
+        __syncthreads();
+#pragma unroll 4
+        for (uint32_t i = part; i < m; i += kWave) {
+            const uint64_t v = s_c[i];
+            below += (v < mine || (v == mine && t0 + i < c)) ? 1u : 0u;
+        }
+    }
+    below = wave_sum_u32(below);
+    if (part == 0 && (below + 1) % kOver == 0 && (below + 1) / kOver < nb)
+        spl[cl.bucket0 + (below + 1) / kOver - 1] = mine;
+}
+
+__device__ __forceinline__ void load_splitters(uint64_t *s_spl, const uint64_t *__restrict__ spl,
+                                               const DevCluster &cl, uint32_t nb)
+{
+    for (uint32_t i = threadIdx.x; i < (uint32_t)kRadix; i += blockDim.x)
+        s_spl[i] = i + 1 < nb ? spl[cl.bucket0 + i] : ~0ull;
+}
+
+// Bucket of every pair (to dig) and the chunk's count of each bucket, stored
+// bucket-major per cluster: hist[hist0 + b nchunk + chunk].
+__global__ void __launch_bounds__(kPassThreads)
+bucket_hist_kernel(const Chunk *__restrict__ chunks, const DevCluster *__restrict__ clus,
+                   uint32_t sub, const uint64_t *__restrict__ keys,
+                   const uint64_t *__restrict__ spl, uint8_t *__restrict__ dig,
+                   uint32_t *__restrict__ hist)
+{
+    __shared__ uint32_t cnt[kRadix];
+    __shared__ uint64_t s_spl[kRadix];
+    const Chunk ch = chunks[blockIdx.x];
+    const DevCluster &cl = clus[ch.cluster];
+    if (cl.nchunk < 2) return;
+    const uint32_t nb = cl.nchunk * sub;
+    uint64_t key[kPassItems];
+#pragma unroll
+    for (int k = 0; k < kPassItems; ++k) {
+        const uint32_t i = ch.begin + (uint32_t)(k * kPassThreads) + threadIdx.x;
+        key[k] = i < ch.end ? keys[i] : 0ull;
+    }
+    if (threadIdx.x < kRadix) cnt[threadIdx.x] = 0;
+    load_splitters(s_spl, spl, cl, nb);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kPassItems; ++k) {
+        const uint32_t i = ch.begin + (uint32_t)(k * kPassThreads) + threadIdx.x;
+        if (i < ch.end) {
+            const uint32_t d = bucket_of(key[k], s_spl);
+            dig[i] = (uint8_t)d;
+            atomicAdd(&cnt[d], 1u);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < nb)
+        hist[cl.hist0 + threadIdx.x * cl.nchunk + (blockIdx.x - cl.chunk0)] = cnt[threadIdx.x];
+}
+
+// One wavefront per bucket: exclusive scan of its counts over the cluster's (at most
+// 256) chunks in place, total -> tot.
+__global__ void __launch_bounds__(kWave)
+bucket_scan_kernel(const Chunk *__restrict__ chunks, const DevCluster *__restrict__ clus,
+                   uint32_t sub, uint32_t *__restrict__ hist, uint32_t *__restrict__ tot)
+{
+    const uint32_t c = blockIdx.x / sub;
+    const DevCluster &cl = clus[chunks[c].cluster];
+    if (cl.nchunk < 2) return;
+    const uint32_t b = (c - cl.chunk0) * sub + blockIdx.x % sub;
+    uint32_t *row = hist + cl.hist0 + b * cl.nchunk;
+    uint32_t v[4], run = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t i = (uint32_t)(k * kWave) + threadIdx.x;
+        v[k] = i < cl.nchunk ? row[i] : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t i = (uint32_t)(k * kWave) + threadIdx.x;
+        const uint32_t inc = wave_incl_scan_add(v[k]);
+        if (i < cl.nchunk) row[i] = run + inc - v[k];
+        run += lane_value(inc, kWave - 1);
+    }
+    if (threadIdx.x == 0) tot[cl.bucket0 + b] = run;
+}
+
+// first position of bucket b of a cluster relative to the cluster (all lanes of the
+// calling wavefront; nb buckets of at most kRadix)
+__device__ __forceinline__ uint32_t bucket_first(const uint32_t *__restrict__ tot, uint32_t b)
+{
+    uint32_t x = 0;
+    for (uint32_t d = threadIdx.x % kWave; d < b; d += kWave) x += tot[d];
+    return wave_sum_u32(x);
+}
+
+// The pairs of a chunk to their buckets, stably.
+__global__ void __launch_bounds__(kPassThreads)
+bucket_scatter_kernel(const Chunk *__restrict__ chunks, const DevCluster *__restrict__ clus,
+                      uint32_t sub, const uint64_t *__restrict__ kin,
+                      const uint32_t *__restrict__ vin, uint64_t *__restrict__ kout,
+                      uint32_t *__restrict__ vout, const uint8_t *__restrict__ dig,
+                      const uint32_t *__restrict__ hist, const uint32_t *__restrict__ tot)
+{
+    __shared__ uint32_t s_wcnt[kPassWaves][kRadix];     // per-wave bucket counts
+    __shared__ uint32_t s_out[kRadix];                  // where the chunk's run of a bucket goes
+    __shared__ uint32_t s_local[kRadix];                // chunk-local bucket start
+    __shared__ uint32_t s_tmp[2][kRadix / kWave];
+    __shared__ uint64_t s_key[kChunk];
+    __shared__ uint32_t s_val[kChunk];
+    __shared__ uint8_t s_dig[kChunk];
+    const Chunk ch = chunks[blockIdx.x];
+    const DevCluster &cl = clus[ch.cluster];
+    if (cl.nchunk < 2) return;
+    const uint32_t nb = cl.nchunk * sub;
+    const int t = threadIdx.x, w = t / kWave, l = t % kWave;
+    const int n = (int)(ch.end - ch.begin);
+    uint64_t key[kPassItems];
+    uint32_t val[kPassItems], rank[kPassItems], d[kPassItems];
+    const int wbase = w * kWave * kPassItems;       // this wave's contiguous part
+#pragma unroll
+    for (int k = 0; k < kPassItems; ++k) {
+        const int p = wbase + k * kWave + l;
+        key[k] = p < n ? kin[ch.begin + p] : 0ull;
+        val[k] = p < n ? vin[ch.begin + p] : 0u;
+        d[k] = p < n ? dig[ch.begin + p] : 0u;
+    }
+    uint32_t total = 0, before = 0;
+    if (t < (int)nb) {
+        total = tot[cl.bucket0 + t];
+        before = hist[cl.hist0 + (uint32_t)t * cl.nchunk + (blockIdx.x - cl.chunk0)];
+    }
+    for (int q = t; q < kPassWaves * kRadix; q += kPassThreads) (&s_wcnt[0][0])[q] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kPassItems; ++k) {
+        const bool valid = wbase + k * kWave + l < n;
+        const unsigned long long peers = match_digit(d[k], valid);
+        const uint32_t run = s_wcnt[w][d[k]];
+        const int r = mask_rank(peers);
+        rank[k] = run + (uint32_t)r;
+        wave_sync();
+        if (valid && r == 0) s_wcnt[w][d[k]] = run + (uint32_t)__popcll(peers);
+        wave_sync();
+    }
+    __syncthreads();
+    // wave offsets within the chunk; bucket starts within the chunk and the cluster
+    uint32_t mine = 0, inc_m = 0, inc_t = 0;
+    if (t < kRadix) {
+#pragma unroll
+        for (int i = 0; i < kPassWaves; ++i) {
+            const uint32_t c = s_wcnt[i][t];
+            s_wcnt[i][t] = mine;
+            mine += c;
+        }
+        inc_m = wave_incl_scan_add(mine);
+        inc_t = wave_incl_scan_add(total);
+        if (l == kWave - 1) {
+            s_tmp[0][w] = inc_m;
+            s_tmp[1][w] = inc_t;
+        }
+    }
+    __syncthreads();
+    if (t < kRadix) {
+        uint32_t om = 0, ot = 0;
+        for (int i = 0; i < w; ++i) {
+            om += s_tmp[0][i];
+            ot += s_tmp[1][i];
+        }
+        s_local[t] = om + inc_m - mine;
+        s_out[t] = cl.first + ot + inc_t - total + before;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kPassItems; ++k) {
+        if (wbase + k * kWave + l < n) {
+            const uint32_t lp = s_local[d[k]] + s_wcnt[w][d[k]] + rank[k];
+            s_key[lp] = key[k];
+            s_val[lp] = val[k];
+            s_dig[lp] = (uint8_t)d[k];
+        }
+    }
+    __syncthreads();
+    for (int p = t; p < n; p += kPassThreads) {
+        const uint32_t b = s_dig[p];
+        const uint32_t g = s_out[b] + (uint32_t)p - s_local[b];
+        kout[g] = s_key[p];
+        vout[g] = s_val[p];
+    }
+}
+
+// One workgroup per bucket: its pairs are sorted stably by key into (k0, v0).  They lie
+// in (k1, v1), or in (k0, v0) for a cluster's only bucket.  With pid == NULL the pairs
+// arrive in caller order; otherwise in the held order (value = held position,
+// pid[value] = caller index), and equal keys are put in caller order explicitly.  Up
+// to kCap pairs are sorted in LDS by stable 8-bit passes (keys and positions move,
+// values are gathered at the end), skipping the digits every key of the bucket
+// shares; a bucket holding equal keys is then sorted again, by caller index first
+// and by key after it.  A larger bucket (clustered keys that the sample missed, or
+// one key) is sorted by the workgroup with the same passes through (k0, v0) and back.
+// (Two workgroups to a CU up to 6144 pairs: LDS and registers are held to that.)
+template <int kCap>
 __global__ void __launch_bounds__(kBucketThreads)
-bucket_sort_kernel(uint64_t *__restrict__ k1, uint32_t *__restrict__ v1, uint64_t *__restrict__ k0,
+__attribute__((amdgpu_waves_per_eu(kCap <= 6144 ? 8 : 4))) bucket_sort_kernel(
+    const Chunk *__restrict__ chunks, const DevCluster *__restrict__ clus, uint32_t sub,
+                   uint64_t *__restrict__ k1, uint32_t *__restrict__ v1, uint64_t *__restrict__ k0,
                    uint32_t *__restrict__ v0, const uint32_t *__restrict__ tot,
                    const uint32_t *__restrict__ pid)
 {
-    constexpr int kItems = kBucketCap / kBucketThreads;   // most pairs per thread in LDS
-    __shared__ uint64_t s_k[kBucketCap];
-    __shared__ uint16_t s_x[kBucketCap];
-    __shared__ uint32_t s_wcnt[kBucketWaves][kRadix];
-    __shared__ uint32_t s_wcnt2[kBucketWaves][kRadix];     // the next LDS pass's counts
+    constexpr int kItems = kCap / kBucketThreads;   // most pairs per thread in LDS
+    __shared__ uint64_t s_k[kCap];
+    __shared__ uint16_t s_x[kCap];
+    __shared__ uint16_t s_wcnt[kBucketWaves][kRadix];
+    __shared__ uint16_t s_wcnt2[kBucketWaves][kRadix];     // the next LDS pass's counts
     __shared__ uint32_t s_off[kRadix];
     __shared__ uint32_t s_ctot[kRadix];
     __shared__ uint32_t s_tmp[kBucketWaves];
     __shared__ uint32_t s_lo;
     __shared__ unsigned long long s_or, s_and;
+    static_assert(kCap < 1 << 16, "positions and counts of a bucket in 16 bits");
     const int t = threadIdx.x, w = t / kWave, lane = t % kWave;
-    const int b = blockIdx.x;
-    if (w == 0) {       // the bucket's first position: the sizes of the buckets before it
-        uint32_t x = 0;
-        for (int d = lane; d < b; d += kWave) x += tot[d];
-        x = wave_sum_u32(x);
+    const uint32_t chunk = blockIdx.x / sub;
+    const DevCluster &cl = clus[chunks[chunk].cluster];
+    const uint32_t b = (chunk - cl.chunk0) * sub + blockIdx.x % sub;
+    if (b >= cluster_buckets(cl, sub)) return;
+    const bool only = cl.nchunk < 2;
+    if (only) {
+        k1 = k0;
+        v1 = v0;
+    } else if (w == 0) {       // the bucket's first position: the sizes of the buckets before it
+        const uint32_t x = bucket_first(tot + cl.bucket0, b);
         if (lane == 0) s_lo = x;
     }
     __syncthreads();
-    const int64_t lo = s_lo;
-    const uint32_t L = tot[b];
+    const int64_t lo = (int64_t)cl.first + (only ? 0u : s_lo);
+    const uint32_t L = only ? cl.n : tot[cl.bucket0 + b];
+    const uint32_t first = cl.first;        // a cluster's caller indices start there
+    if (L == 0) return;
 
-    if (L <= (uint32_t)kBucketCap) {
+    if (L <= (uint32_t)kCap) {
         const int items = (int)((L + kBucketThreads - 1) / kBucketThreads);
         const uint32_t sub = (uint32_t)items * kWave;      // a wavefront's positions
-        uint32_t(*cur)[kRadix] = s_wcnt;       // counts of a pass (zero at its start)
-        uint32_t(*nxt)[kRadix] = s_wcnt2;      // cleared during a pass for the next one
+        uint16_t(*cur)[kRadix] = s_wcnt;       // counts of a pass (zero at its start)
+        uint16_t(*nxt)[kRadix] = s_wcnt2;      // cleared during a pass for the next one
         // s_k[i] = v[j] for positions i = j kBucketThreads + t < L, s_x[i] = i, with
         // every load of the thread in flight at once; returns the bits in which
         // the values differ
@@ -501,7 +694,7 @@ bucket_sort_kernel(uint64_t *__restrict__ k1, uint32_t *__restrict__ v1, uint64_
                         const uint32_t before = j == 0 ? 0u : cur[w][d];
                         rank[j] = before + (uint32_t)r;
                         wave_sync();
-                        if (valid && r == 0) cur[w][d] = before + (uint32_t)__popcll(peers);
+                        if (valid && r == 0) cur[w][d] = (uint16_t)(before + (uint32_t)__popcll(peers));
                         wave_sync();
                     }
                 }
@@ -515,7 +708,7 @@ bucket_sort_kernel(uint64_t *__restrict__ k1, uint32_t *__restrict__ v1, uint64_
                     uint32_t run = 0;
 #pragma unroll
                     for (int q = 0; q < kBucketWaves; ++q) {
-                        cur[q][t] = run;
+                        cur[q][t] = (uint16_t)run;
                         run += x[q];
                     }
                     cnt = run;
@@ -540,7 +733,7 @@ bucket_sort_kernel(uint64_t *__restrict__ k1, uint32_t *__restrict__ v1, uint64_
                     }
                 }
                 __syncthreads();
-                uint32_t(*tmp)[kRadix] = cur;
+                uint16_t(*tmp)[kRadix] = cur;
                 cur = nxt;
                 nxt = tmp;
             }
@@ -561,7 +754,7 @@ bucket_sort_kernel(uint64_t *__restrict__ k1, uint32_t *__restrict__ v1, uint64_
 #pragma unroll
                 for (int j = 0; j < kItems; ++j) {
                     const uint32_t i = (uint32_t)(j * kBucketThreads + t);
-                    v[j] = i < L ? (uint64_t)pid[v1[lo + i]] : 0ull;
+                    v[j] = i < L ? (uint64_t)(pid[v1[lo + i]] - first) : 0ull;
                 }
                 passes(load(v));        // by caller index
 #pragma unroll
@@ -590,7 +783,8 @@ bucket_sort_kernel(uint64_t *__restrict__ k1, uint32_t *__restrict__ v1, uint64_
 #pragma unroll
         for (int j = 0; j < kItems; ++j) {
             const uint32_t i = (uint32_t)(j * kBucketThreads + t);
-            vout[j] = i < L ? v1[lo + s_x[i]] : 0u;
+            // an only bucket's values are its positions as they came
+            vout[j] = i < L ? (only ? (uint32_t)lo + s_x[i] : v1[lo + s_x[i]]) : 0u;
         }
 #pragma unroll
         for (int j = 0; j < kItems; ++j) {
@@ -603,18 +797,37 @@ bucket_sort_kernel(uint64_t *__restrict__ k1, uint32_t *__restrict__ v1, uint64_
         return;
     }
 
-    // Large bucket: stable passes through device memory, (k1, v1) -> (k0, v0) ->
-    // (k1, v1) ...: with pid, three passes on the caller index (below 2^24) first,
-    // then eight on the 60-bit keys; the result is copied to (k0, v0) if it ends in
-    // (k1, v1).
+    // Large bucket (of a cluster with several): stable passes through device memory,
+    // (k1, v1) -> (k0, v0) -> (k1, v1) ...: with pid, three passes on the caller index
+    // in the cluster (below 2^24) first, then one on each byte in which the keys
+    // differ; the result is copied to (k0, v0) if it ends in (k1, v1).
+    unsigned long long o = 0ull, a = ~0ull;
+    for (uint32_t i = t; i < L; i += kBucketThreads) {
+        o |= k1[lo + i];
+        a &= k1[lo + i];
+    }
+    o = wave_or_u64(o);
+    a = wave_and_u64(a);
+    if (t == 0) {
+        s_or = 0ull;
+        s_and = ~0ull;
+    }
+    __syncthreads();
+    if (lane == 0) {
+        atomicOr(&s_or, o);
+        atomicAnd(&s_and, a);
+    }
+    __syncthreads();
+    const uint64_t vary = s_or ^ s_and;
     uint64_t *ks = k1, *kd = k0;
     uint32_t *vs = v1, *vd = v0;
     const int npid = pid ? 3 : 0;
     for (int pass = 0; pass < npid + 8; ++pass) {
         const bool by_pid = pass < npid;
         const int shift = (by_pid ? pass : pass - npid) * kRadixBits;
+        if (!by_pid && ((vary >> shift) & (kRadix - 1)) == 0) continue;
         auto digit = [&](uint64_t key, uint32_t val) -> uint32_t {
-            return by_pid ? (pid[val] >> shift) & (kRadix - 1)
+            return by_pid ? ((pid[val] - first) >> shift) & (kRadix - 1)
                           : (uint32_t)(key >> shift) & (kRadix - 1);
         };
         if (t < kRadix) s_off[t] = 0;
@@ -645,7 +858,7 @@ bucket_sort_kernel(uint64_t *__restrict__ k1, uint32_t *__restrict__ v1, uint64_
             const int r = mask_rank(peers);
             for (int q = t; q < kBucketWaves * kRadix; q += kBucketThreads) (&s_wcnt[0][0])[q] = 0;
             __syncthreads();
-            if (valid && r == 0) s_wcnt[w][d] = (uint32_t)__popcll(peers);
+            if (valid && r == 0) s_wcnt[w][d] = (uint16_t)__popcll(peers);
             __syncthreads();
             if (t < kRadix) {   // wavefronts before each one, per digit
                 uint32_t x[kBucketWaves];
@@ -654,7 +867,7 @@ bucket_sort_kernel(uint64_t *__restrict__ k1, uint32_t *__restrict__ v1, uint64_
                 uint32_t run = 0;
 #pragma unroll
                 for (int q = 0; q < kBucketWaves; ++q) {
-                    s_wcnt[q][t] = run;
+                    s_wcnt[q][t] = (uint16_t)run;
                     run += x[q];
                 }
                 s_ctot[t] = run;
@@ -686,6 +899,8 @@ bucket_sort_kernel(uint64_t *__restrict__ k1, uint32_t *__restrict__ v1, uint64_
 
 }  // namespace
 
+namespace {
+
 hipError_t radix_sort_pairs(bh_ctx *c)
 {
     const int64_t n = c->n;
@@ -701,14 +916,14 @@ hipError_t radix_sort_pairs(bh_ctx *c)
         const int shift = by_cluster ? (pass - 8) * kRadixBits : pass * kRadixBits;
         const uint32_t *cl = by_cluster ? c->pcl : nullptr;
         hipLaunchKernelGGL(hist_kernel, dim3(nblk), dim3(kSortThreads), 0, c->stream,
-                           c->key[src], c->val[src], cl, nullptr, n, shift, hist, nblk);
+                           c->key[src], c->val[src], cl, n, shift, hist, nblk);
         BH_LAUNCH_CHECK();
         hipLaunchKernelGGL(scan_digit_kernel, dim3(kRadix), dim3(256), 0, c->stream, hist, nblk,
                            tot);
         BH_LAUNCH_CHECK();
         hipLaunchKernelGGL(scatter_kernel, dim3(nblk), dim3(kSortThreads), 0, c->stream,
-                           c->key[src], c->val[src], c->key[src ^ 1], c->val[src ^ 1], cl, nullptr,
-                           n, shift, hist, tot, nblk);
+                           c->key[src], c->val[src], c->key[src ^ 1], c->val[src ^ 1], cl, n, shift,
+                           hist, tot, nblk);
         BH_LAUNCH_CHECK();
         src ^= 1;
     }
@@ -721,43 +936,67 @@ hipError_t radix_sort_pairs(bh_ctx *c)
     return hipSuccess;
 }
 
-hipError_t rebuild_sort_pairs(bh_ctx *c)
+}  // namespace
+
+// Buckets per chunk of the clusters with several chunks (0: radix sort).  256 buckets
+// per cluster are the limit of the pass, so larger clusters have larger buckets.
+//   up to 2^18 particles in all: 1024 pairs a bucket.  A bucket's sort is a chain of
+//   passes with little work in each, and 256 workgroups fill the device;
+//   clusters of up to 2^19: 2048 pairs, two workgroups to a CU;
+//   clusters of up to 2^20: 4096 pairs.
+int sort_sub(const bh_ctx *c)
 {
-    const int64_t n = c->n;
-    if (!rebuild_buckets(c)) return radix_sort_pairs(c);
-    const int nb = rebuild_buckets(c);
-    const int nblk = (int)((n + kSortTile - 1) / kSortTile);
+    if (c->max_cluster > (int64_t)kRadix * kChunk) return 0;
+    if (c->n <= (int64_t)kRadix * kChunk / 4) return 4;
+    return c->max_cluster <= (int64_t)kRadix * kChunk / 2 ? 2 : 1;
+}
+
+// candidates and splitters, in the cells' centres of mass (written again after the sort)
+uint64_t *sort_candidates(bh_ctx *c)
+{
+    return reinterpret_cast<uint64_t *>(c->c_com) + c->nbuckets;
+}
+
+template <int kCap>
+void bucket_sort_launch(bh_ctx *c, uint32_t sub, const uint32_t *tot, const uint32_t *pid)
+{
+    hipLaunchKernelGGL(bucket_sort_kernel<kCap>, dim3((unsigned)(c->nchunks * sub)),
+                       dim3(kBucketThreads), 0, c->stream, c->chunks, c->clus, sub, c->key[1],
+                       c->val[1], c->key[0], c->val[0], tot, pid);
+}
+
+hipError_t sort_pairs(bh_ctx *c, bool held)
+{
+    const int sub_max = sort_sub(c);
+    if (!sub_max) return radix_sort_pairs(c);
+    const bool pass = c->nbuckets > 0;
+    const uint32_t sub = pass ? (uint32_t)sub_max : 1u;
     uint32_t *hist = c->blk;
-    uint32_t *tot = c->blk + (int64_t)kRadix * nblk;
-    const uint64_t *cand = c->splt + kRadix;    // written by the keys kernel
-    hipLaunchKernelGGL(splitter_kernel, dim3(kRadix), dim3(kCand), 0, c->stream, cand,
-                       rebuild_candidates(c), nb - 1, c->splt);
-    BH_LAUNCH_CHECK();
-    hipLaunchKernelGGL(hist_kernel, dim3(nblk), dim3(kSortThreads), 0, c->stream, c->key[0],
-                       c->val[0], nullptr, c->splt, n, 0, hist, nblk);
-    BH_LAUNCH_CHECK();
-    hipLaunchKernelGGL(scan_digit_kernel, dim3(kRadix), dim3(256), 0, c->stream, hist, nblk, tot);
-    BH_LAUNCH_CHECK();
-    hipLaunchKernelGGL(scatter_kernel, dim3(nblk), dim3(kSortThreads), 0, c->stream, c->key[0],
-                       c->val[0], c->key[1], c->val[1], nullptr, c->splt, n, 0, hist, tot, nblk);
-    BH_LAUNCH_CHECK();
-    hipLaunchKernelGGL(bucket_sort_kernel, dim3(nb), dim3(kBucketThreads), 0, c->stream, c->key[1],
-                       c->val[1], c->key[0], c->val[0], tot, c->pid[c->cur]);
+    uint32_t *tot = c->blk + c->nhist;
+    if (pass) {
+        const unsigned g = (unsigned)c->nchunks;
+        uint64_t *spl = reinterpret_cast<uint64_t *>(c->c_com);
+        hipLaunchKernelGGL(splitter_kernel, dim3(g * sub), dim3(1024), 0, c->stream, c->chunks, c->clus,
+                           sub, sort_candidates(c), spl);
+        BH_LAUNCH_CHECK();
+        hipLaunchKernelGGL(bucket_hist_kernel, dim3(g), dim3(kPassThreads), 0, c->stream, c->chunks,
+                           c->clus, sub, c->key[0], spl, c->split, hist);
+        BH_LAUNCH_CHECK();
+        hipLaunchKernelGGL(bucket_scan_kernel, dim3(g * sub), dim3(kWave), 0, c->stream, c->chunks,
+                           c->clus, sub, hist, tot);
+        BH_LAUNCH_CHECK();
+        hipLaunchKernelGGL(bucket_scatter_kernel, dim3(g), dim3(kPassThreads), 0, c->stream,
+                           c->chunks, c->clus, sub, c->key[0], c->val[0], c->key[1], c->val[1],
+                           c->split, hist, tot);
+        BH_LAUNCH_CHECK();
+    }
+    // a single chunk is a bucket of up to 4096; others three to four times their mean
+    const uint32_t *pid = held ? c->pid[c->cur] : nullptr;
+    if (sub_max == 4) bucket_sort_launch<4096>(c, sub, tot, pid);
+    else if (sub_max == 2) bucket_sort_launch<6144>(c, sub, tot, pid);
+    else bucket_sort_launch<12288>(c, sub, tot, pid);
     BH_LAUNCH_CHECK();
     return hipSuccess;
-}
-
-int rebuild_buckets(const bh_ctx *c)
-{
-    // one cluster, and few enough particles for at most kRadix buckets
-    if (c->K != 1 || c->n < 2 || c->n > (int64_t)kRadix * kBucketTarget) return 0;
-    return (int)((c->n + kBucketTarget - 1) / kBucketTarget);
-}
-
-int rebuild_candidates(const bh_ctx *c)
-{
-    const int nb = rebuild_buckets(c);
-    return nb > 1 ? nb * kSplitOver - 1 : 0;
 }
 
 hipError_t compact_flags(bh_ctx *c, const uint8_t *flags, int64_t n, uint32_t *idx,
