@@ -348,8 +348,8 @@ compact_down_kernel(const uint8_t *__restrict__ flags, int64_t n,
 // particles 138 -> 62 us of kernels, 4096 125 -> 30 us.
 
 constexpr uint32_t kOver = kSortOver;   // candidate keys per bucket
-constexpr int kBucketThreads = 1024;
-constexpr int kBucketWaves = kBucketThreads / kWave;
+constexpr int kWindow = 40;             // bits a bucket's passes cover
+constexpr uint32_t kShortRun = 16;      // pairs agreeing in them that one thread orders
 constexpr int kPassThreads = 512;       // workgroup of the bucket pass: one chunk
 constexpr int kPassItems = kChunk / kPassThreads;
 constexpr int kPassWaves = kPassThreads / kWave;
@@ -593,19 +593,24 @@ bucket_scatter_kernel(const Chunk *__restrict__ chunks, const DevCluster *__rest
 // pid[value] = caller index), and equal keys are put in caller order explicitly.  Up
 // to kCap pairs are sorted in LDS by stable 8-bit passes (keys and positions move,
 // values are gathered at the end), skipping the digits every key of the bucket
-// shares; a bucket holding equal keys is then sorted again, by caller index first
-// and by key after it.  A larger bucket (clustered keys that the sample missed, or
-// one key) is sorted by the workgroup with the same passes through (k0, v0) and back.
-// (Two workgroups to a CU up to 6144 pairs: LDS and registers are held to that.)
-template <int kCap>
-__global__ void __launch_bounds__(kBucketThreads)
-__attribute__((amdgpu_waves_per_eu(kCap <= 6144 ? 8 : 4))) bucket_sort_kernel(
-    const Chunk *__restrict__ chunks, const DevCluster *__restrict__ clus, uint32_t sub,
+// shares, and what those leave open in a second step (see below).  A larger bucket
+// (clustered keys that the sample missed, or one key) is sorted by the workgroup
+// with the same passes through (k0, v0) and back.
+// A pass costs its workgroup about 3 us whatever it holds (a chain of LDS reads, eight
+// ballots, counts and four barriers), so the passes cover only kWindow bits: buckets of
+// 1024 pairs 31 -> 23 us, of 4096 44 -> 32 us.  Two workgroups share a CU up to 6144
+// pairs: LDS and registers are held to that (4000 buckets of 2048 pairs on average
+// took 258 us with all passes, 211 us with workgroups of 1024, 187 us with 512).
+template <int kCap, int kThreads, int kWavesPerEu>
+__global__ void __launch_bounds__(kThreads)
+__attribute__((amdgpu_waves_per_eu(kWavesPerEu)))
+bucket_sort_kernel(const Chunk *__restrict__ chunks, const DevCluster *__restrict__ clus, uint32_t sub,
                    uint64_t *__restrict__ k1, uint32_t *__restrict__ v1, uint64_t *__restrict__ k0,
                    uint32_t *__restrict__ v0, const uint32_t *__restrict__ tot,
                    const uint32_t *__restrict__ pid)
 {
-    constexpr int kItems = kCap / kBucketThreads;   // most pairs per thread in LDS
+    constexpr int kBucketThreads = kThreads, kBucketWaves = kThreads / kWave;
+    constexpr int kItems = kCap / kThreads;         // most pairs per thread in LDS
     __shared__ uint64_t s_k[kCap];
     __shared__ uint16_t s_x[kCap];
     __shared__ uint16_t s_wcnt[kBucketWaves][kRadix];
@@ -671,10 +676,10 @@ __attribute__((amdgpu_waves_per_eu(kCap <= 6144 ? 8 : 4))) bucket_sort_kernel(
             __syncthreads();
             return s_or ^ s_and;
         };
-        // stable 8-bit passes over the bytes of s_k in which vary has bits
-        auto passes = [&](uint64_t vary) {
-            for (int pass = 0; pass < 8; ++pass) {
-                const int shift = pass * kRadixBits;
+        // stable 8-bit passes over the bits of s_k from bit `from` up in which vary has
+        // bits
+        auto passes = [&](uint64_t vary, int from) {
+            for (int shift = from; shift < 64; shift += kRadixBits) {
                 if (((vary >> shift) & (kRadix - 1)) == 0) continue;    // one digit: order kept
                 // thread (w, lane) takes positions w sub + j kWave + lane: position
                 // order is (wavefront, j, lane) order, which the ranks below keep
@@ -745,18 +750,65 @@ __attribute__((amdgpu_waves_per_eu(kCap <= 6144 ? 8 : 4))) bucket_sort_kernel(
             const uint32_t i = (uint32_t)(j * kBucketThreads + t);
             v[j] = i < L ? k1[lo + i] : 0ull;
         }
-        passes(load(v));
-        if (pid) {
-            // equal keys, if any, are still in the held order
+        // The passes cover the kWindow highest bits in which the keys differ.  Pairs that
+        // agree in those are still in the order they came in; each short run of them is
+        // put in order by the thread of its first pair (by key, and with pid by caller
+        // index among equal keys).  A long run has the whole sort done over.
+        const uint64_t vary = load(v);
+        const int hi = 64 - (int)__clzll((long long)(vary | 1ull));
+        const int from = hi > kWindow ? hi - kWindow : 0;
+        passes(vary, from);
+        bool over = false;
+        if (from > 0 || pid) {
             bool tie = false;
-            for (uint32_t i = t; i + 1 < L; i += kBucketThreads) tie |= s_k[i] == s_k[i + 1];
+            for (uint32_t i = t; i + 1 < L; i += kBucketThreads)
+                tie |= (s_k[i] >> from) == (s_k[i + 1] >> from);
             if (__syncthreads_or(tie)) {
+                bool lng = false;
+                for (uint32_t i = t; i + 1 < L; i += kBucketThreads) {
+                    const uint64_t top = s_k[i] >> from;
+                    if (top != s_k[i + 1] >> from || (i > 0 && top == s_k[i - 1] >> from)) continue;
+                    uint32_t e = i + 2;
+                    while (e < L && e - i <= kShortRun && s_k[e] >> from == top) ++e;
+                    lng |= e - i > kShortRun;
+                }
+                over = __syncthreads_or(lng) != 0;
+                for (uint32_t i = t; i + 1 < L && !over; i += kBucketThreads) {
+                    const uint64_t top = s_k[i] >> from;
+                    if (top != s_k[i + 1] >> from || (i > 0 && top == s_k[i - 1] >> from)) continue;
+                    // (i's own run: a neighbouring run's pairs differ in the bits above)
+                    for (uint32_t e = i + 1; e < L && s_k[e] >> from == top; ++e) {
+                        const uint64_t key = s_k[e];
+                        const uint16_t x = s_x[e];
+                        const uint32_t me = pid ? pid[v1[lo + x]] : 0u;
+                        uint32_t q = e;
+                        while (q > i && (s_k[q - 1] > key ||
+                                         (pid && s_k[q - 1] == key && pid[v1[lo + s_x[q - 1]]] > me))) {
+                            s_k[q] = s_k[q - 1];
+                            s_x[q] = s_x[q - 1];
+                            --q;
+                        }
+                        s_k[q] = key;
+                        s_x[q] = x;
+                    }
+                }
+                __syncthreads();
+            }
+        }
+        if (over) {
+            // every bit: without pid from the order now held (pairs of equal keys are
+            // still in the order they came in), with it from the caller order
+            if (!pid) {
+                for (int q = t; q < kBucketWaves * kRadix; q += kBucketThreads) (&cur[0][0])[q] = 0;
+                __syncthreads();
+                passes(vary, 0);
+            } else {
 #pragma unroll
                 for (int j = 0; j < kItems; ++j) {
                     const uint32_t i = (uint32_t)(j * kBucketThreads + t);
                     v[j] = i < L ? (uint64_t)(pid[v1[lo + i]] - first) : 0ull;
                 }
-                passes(load(v));        // by caller index
+                passes(load(v), 0);     // by caller index
 #pragma unroll
                 for (int j = 0; j < kItems; ++j) {
                     const uint32_t i = (uint32_t)(j * kBucketThreads + t);
@@ -768,14 +820,14 @@ __attribute__((amdgpu_waves_per_eu(kCap <= 6144 ? 8 : 4))) bucket_sort_kernel(
                     const uint32_t i = (uint32_t)(j * kBucketThreads + t);
                     x[j] = i < L ? s_x[i] : 0;
                 }
-                const uint64_t vary = load(v);      // keys in caller-index order ...
+                load(v);                            // keys in caller-index order ...
 #pragma unroll
                 for (int j = 0; j < kItems; ++j) {  // ... with their own positions
                     const uint32_t i = (uint32_t)(j * kBucketThreads + t);
                     if (i < L) s_x[i] = x[j];
                 }
                 __syncthreads();
-                passes(vary);           // then by key
+                passes(vary, 0);        // then by key
             }
         }
         // every value gather of a thread in flight at once
@@ -957,12 +1009,12 @@ uint64_t *sort_candidates(bh_ctx *c)
     return reinterpret_cast<uint64_t *>(c->c_com) + c->nbuckets;
 }
 
-template <int kCap>
+template <int kCap, int kThreads, int kWavesPerEu>
 void bucket_sort_launch(bh_ctx *c, uint32_t sub, const uint32_t *tot, const uint32_t *pid)
 {
-    hipLaunchKernelGGL(bucket_sort_kernel<kCap>, dim3((unsigned)(c->nchunks * sub)),
-                       dim3(kBucketThreads), 0, c->stream, c->chunks, c->clus, sub, c->key[1],
-                       c->val[1], c->key[0], c->val[0], tot, pid);
+    hipLaunchKernelGGL((bucket_sort_kernel<kCap, kThreads, kWavesPerEu>),
+                       dim3((unsigned)(c->nchunks * sub)), dim3(kThreads), 0, c->stream, c->chunks,
+                       c->clus, sub, c->key[1], c->val[1], c->key[0], c->val[0], tot, pid);
 }
 
 hipError_t sort_pairs(bh_ctx *c, bool held)
@@ -992,9 +1044,9 @@ hipError_t sort_pairs(bh_ctx *c, bool held)
     }
     // a single chunk is a bucket of up to 4096; others three to four times their mean
     const uint32_t *pid = held ? c->pid[c->cur] : nullptr;
-    if (sub_max == 4) bucket_sort_launch<4096>(c, sub, tot, pid);
-    else if (sub_max == 2) bucket_sort_launch<6144>(c, sub, tot, pid);
-    else bucket_sort_launch<12288>(c, sub, tot, pid);
+    if (sub_max == 4) bucket_sort_launch<4096, 1024, 8>(c, sub, tot, pid);
+    else if (sub_max == 2) bucket_sort_launch<6144, 512, 4>(c, sub, tot, pid);
+    else bucket_sort_launch<12288, 1024, 4>(c, sub, tot, pid);
     BH_LAUNCH_CHECK();
     return hipSuccess;
 }

@@ -89,3 +89,27 @@ def test_batch_order_loaded_and_rebuilt():
         for p, (_, m) in zip(new, parts):
             _check(ex, first, p, m)
             first += len(m)
+
+
+@pytest.mark.parametrize("deep", [2, 16, 17, 40, 3000])
+def test_pairs_that_agree_in_the_passes_window(deep):
+    # `deep` particles in a cube of 2^-16 of the domain: their keys agree in the first
+    # 48 bits, so the bucket's passes (40 bits below the first in which its keys
+    # differ) leave them in arrival order and they are ordered afterwards, by one
+    # thread or, when they are many, by passes over every bit; some coincide
+    import paper_1106_1900_amd as bh
+    n = 3500
+    say("case window", deep)
+    rng = np.random.default_rng(11)
+    pos = rng.uniform(0.0, 1.0, (n, 3))
+    pos[0], pos[1] = 0.0, 1.0
+    sel = 2 + rng.permutation(n - 2)[:deep]
+    pos[sel] = 0.3 + rng.uniform(0.0, 2.0 ** -17, (deep, 3))
+    pos[sel[: deep // 2]] = pos[sel[0]]
+    mass = np.full(n, 1.0 / n)
+    with bh.Context() as ctx:
+        ctx.build_tree(to_dev(pos), to_dev(mass))
+        _check(ctx.export_tree(), 0, pos, mass)
+        new = pos[rng.permutation(n)]
+        ctx.set_state(to_dev(new), to_dev(np.zeros_like(pos)))
+        _check(ctx.export_tree(), 0, new, mass)
