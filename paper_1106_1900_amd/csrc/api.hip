@@ -94,8 +94,6 @@ void free_buffers(bh_ctx *c)
     dfree(c->c_leaf);
     dfree(c->c_com);
     dfree(c->c_S);
-    dfree(c->c_q0);
-    dfree(c->c_q1);
     dfree(c->c_rcrit2);
     dfree(c->c_rec);
     dfree(c->c_geo);
@@ -149,7 +147,7 @@ Sizes sizes_for(bh_ctx *c, int64_t n, int64_t K, int nleaf_min)
     z.chunks = n / kChunk + K + 1;     // every layout with <= n particles, <= K clusters
     z.cells = cell_bound(n, K, nleaf_min);
     z.blk = std::max(sort_blk_words(n),
-                     (int64_t)(kLevels + 1) * ((n + kTreeTile - 1) / kTreeTile) + kLevels + 1);
+                     level_rows_words(n) + compact_words(n) + run_edge_words(n));
     z.spill_waves = walk_grid_waves(c);
     return z;
 }
@@ -185,8 +183,6 @@ hipError_t each_buffer(bh_ctx *c, const Sizes &z, F f)
     B(c->c_leaf, z.cells);
     B(c->c_com, z.cells);
     B(c->c_S, 6 * z.cells);
-    B(c->c_q0, z.cells);
-    B(c->c_q1, z.cells);
     B(c->c_rcrit2, z.cells);
     B(c->c_rec, z.cells);
     B(c->c_geo, z.cells);

@@ -197,7 +197,6 @@ struct bh_ctx {
     uint8_t *c_level = nullptr, *c_leaf = nullptr;
     double4 *c_com = nullptr;                // centre of mass, mass (float64)
     double *c_S = nullptr;                   // [c][6] float64 second moment
-    float4 *c_q0 = nullptr, *c_q1 = nullptr; // float32 walk multipoles
     float *c_rcrit2 = nullptr;
     bh::WalkCell *c_rec = nullptr;           // per-cell walk record (walk.hip)
     double4 *c_geo = nullptr;                // geometric centre, half side (minimum-distance test)
@@ -276,6 +275,15 @@ constexpr int kSortOver = 16;              // candidates per bucket
 hipError_t compact_flags(bh_ctx *c, const uint8_t *flags, int64_t n, uint32_t *idx,
                          uint32_t *count, uint32_t *order, uint32_t *upto, bool rank);
 int64_t sort_blk_words(int64_t n);
+int64_t compact_words(int64_t n);
+int64_t run_edge_words(int64_t n);         // build.hip
+// words at the front of blk that hold the scanned starts per level and tile and the
+// level totals; the compaction's counts and the runs' edges follow (the edges last from
+// a build to the next: the moments of a refit read them too)
+constexpr int64_t level_rows_words(int64_t n)
+{
+    return (int64_t)(kLevels + 1) * ((n + kTreeTile - 1) / kTreeTile + 1);
+}
 
 // walk.hip
 hipError_t launch_walk(bh_ctx *c, bool timed, bool active_only = false);

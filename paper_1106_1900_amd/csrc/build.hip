@@ -484,10 +484,10 @@ struct Ranks {
 __device__ __forceinline__ void level_ranks(bool valid, uint8_t sp, uint8_t lm,
                                             const uint32_t *__restrict__ blk_scanned, int nblk,
                                             const DevMisc *__restrict__ m, uint32_t (*s_wc)[kLevels],
-                                            int lo, int hi, Ranks &r)
+                                            int lo, int hi, Ranks &r,
+                                            unsigned long long (&balls)[kLevels])
 {
     const int t = threadIdx.x, w = t / kWave, l = t % kWave;
-    unsigned long long balls[kLevels];
 #pragma unroll
     for (int lev = 0; lev < kLevels; ++lev) {
         balls[lev] = ballot(valid && sp <= lev && lev <= lm);
@@ -505,6 +505,16 @@ __device__ __forceinline__ void level_ranks(bool valid, uint8_t sp, uint8_t lm,
     }
 }
 
+// Where a run of the moments kernels begins: the particle with the lowest split level of
+// every kRunTiles-th tile (the first of them), so that few cells reach across, with
+// that level and the starts of each level before it.
+constexpr int kRunTiles = 4;
+struct RunEdge {
+    uint32_t x;
+    uint32_t split;
+    uint32_t c[kLevels];
+};
+
 // Every cell a particle starts: its first particle, level, leaf flag, parent and
 // first child.  The last particle of a cell (the next particle starts a cell at
 // the same or a shallower level, or lies beyond the cluster) writes the cell's
@@ -517,9 +527,10 @@ emit_cells_kernel(const uint8_t *__restrict__ split, const uint8_t *__restrict__
                   uint8_t *__restrict__ c_leaf, uint32_t *__restrict__ c_parent,
                   uint32_t *__restrict__ c_child, uint32_t *__restrict__ c_end,
                   uint32_t *__restrict__ c_cend, const uint32_t *__restrict__ pcl,
-                  uint32_t *__restrict__ c_cl)
+                  uint32_t *__restrict__ c_cl, RunEdge *__restrict__ edges)
 {
     __shared__ uint32_t s_wc[kTreeTile / kWave][kLevels];
+    __shared__ int s_edge[kTreeTile / kWave];
     const int64_t i = (int64_t)blockIdx.x * kTreeTile + threadIdx.x;
     const bool valid = i < n;
     const uint8_t sp = valid ? split[i] : (uint8_t)255;
@@ -532,8 +543,30 @@ emit_cells_kernel(const uint8_t *__restrict__ split, const uint8_t *__restrict__
     const bool used = valid && first_lev <= lm;
     const int lo = wave_min_i32(used ? (first_lev > 0 ? first_lev - 1 : 0) : kLevels);
     const int hi = wave_max_i32(used ? (int)lm : -1);
+    const bool edge = blockIdx.x % kRunTiles == 0;      // a run begins in this tile
+    if (edge) {
+        const int k = wave_min_i32(((int)sp << 8) | (int)threadIdx.x);
+        if (threadIdx.x % kWave == 0) s_edge[threadIdx.x / kWave] = k;
+    }
     Ranks r;
-    level_ranks(valid, sp, lm, blk_scanned, nblk, m, s_wc, lo, hi, r);
+    unsigned long long balls[kLevels];
+    level_ranks(valid, sp, lm, blk_scanned, nblk, m, s_wc, lo, hi, r, balls);
+    if (edge) {
+        int k = s_edge[0];
+        for (int w = 1; w < kTreeTile / kWave; ++w) k = min(k, s_edge[w]);
+        if ((k & 255) == (int)threadIdx.x) {
+            RunEdge &e = edges[blockIdx.x / kRunTiles];
+            e.x = (uint32_t)i;
+            e.split = sp;
+            const unsigned long long lt = (1ull << (threadIdx.x % kWave)) - 1ull;
+#pragma unroll
+            for (int lev = 0; lev < kLevels; ++lev) {
+                uint32_t c = blk_scanned[(int64_t)lev * nblk + blockIdx.x];
+                for (int w = 0; w < (int)threadIdx.x / kWave; ++w) c += s_wc[w][lev];
+                e.c[lev] = c + (uint32_t)__popcll(balls[lev] & lt);
+            }
+        }
+    }
     const uint32_t ncells = m->ncells;
     if (!valid || ncells == 0) return;
     const uint32_t cluster = sp <= lm ? pcl[i] : 0u;
@@ -675,8 +708,8 @@ struct RecOut {
 // y, z, hi x, y, z) after a refit, else null.
 __device__ __forceinline__ void cell_record(uint32_t c, uint32_t f, int lev, uint32_t k, bool leaf,
                                             uint32_t link, uint32_t info, const double4 cm,
-                                            const float4 a, const float4 b, const double *blo,
-                                            const double *bhi, const RecOut &ro)
+                                            const float *s3, const double *blo, const double *bhi,
+                                            const RecOut &ro)
 {
     const DevDomain &cl = ro.dom[k];
     const float theta = ro.clus[k].theta;
@@ -732,121 +765,32 @@ __device__ __forceinline__ void cell_record(uint32_t c, uint32_t f, int lev, uin
     w.rcrit2 = r2;
     w.link = link;
     w.info = leaf ? (info | 0x80000000u) : info;
-    w.s3[0] = a.x;
-    w.s3[1] = a.y;
-    w.s3[2] = a.z;
-    w.s3[3] = a.w;
-    w.s3[4] = b.x;
-    w.s3[5] = b.y;
+#pragma unroll
+    for (int q = 0; q < 6; ++q) w.s3[q] = s3[q];
     ro.rec[c] = w;
 }
 
-__device__ __forceinline__ void store_walk_multipole(uint32_t c, const double *S,
-                                                     float4 *__restrict__ q0, float4 *__restrict__ q1,
-                                                     float4 &a, float4 &b)
-{
-    const double tr = (S[0] + S[1]) + S[2];
-    a = make_float4((float)(3.0 * S[0]), (float)(3.0 * S[1]), (float)(3.0 * S[2]),
-                    (float)(3.0 * S[3]));
-    b = make_float4((float)(3.0 * S[4]), (float)(3.0 * S[5]), (float)(0.5 * tr), (float)(1.5 * tr));
-    q0[c] = a;
-    q1[c] = b;
-}
-
-// Moments of cell c: a leaf from its particles, a node from its children (one
-// level deeper, already done), both in array order.  Each pass over the members
-// loads a run of kRun of them at once (indices past the end repeat the last
-// member and are left out of the sums), so a pass costs one memory latency per
-// run instead of one per member; the sums keep the members' order.
+// Moments of leaf c from its particles [s, s + n), in array order, by one thread.  Each
+// pass over the members loads a run of kRun of them at once (indices past the end
+// repeat the last member and are left out of the sums), so a pass costs one memory
+// latency per run instead of one per member; the sums keep the members' order.
 constexpr int kRun = 8;
-// leaves of up to kLeafFast particles load them once for all three sums
-#ifndef BH_LEAF_FAST
-#define BH_LEAF_FAST 8
-#endif
-constexpr int kLeafFast = BH_LEAF_FAST;
 
-template <bool kLeaf, bool kBox>
-__device__ __forceinline__ void cell_moments(uint32_t c, const uint32_t *__restrict__ c_first,
-                                             const uint32_t *__restrict__ c_count,
-                                             const uint32_t *__restrict__ c_child,
-                                             const uint32_t *__restrict__ c_nchild,
-                                             const double4 *__restrict__ p4,
-                                             double4 *__restrict__ c_com, double *__restrict__ c_S,
-                                             float4 *__restrict__ q0, float4 *__restrict__ q1,
-                                             double2 *__restrict__ box, const RecOut &ro)
+// (m: x, y, z of the centre of mass, mass, second moments, then the box with kBox)
+template <bool kBox, class Src>
+__device__ __forceinline__ void leaf_moments(uint32_t s, uint32_t n, Src p4, double *m)
 {
-    // members [s, s + n): particles of a leaf (position, mass) or children of a
-    // node (centre of mass, mass; second moments in c_S)
-    const uint32_t s = kLeaf ? c_first[c] : c_child[c];
-    const uint32_t n = kLeaf ? c_count[c] : c_nchild[c];
-    // the walk record's inputs, loaded with the cell's own record
-    const int lev = ro.c_level[c];
-    const uint32_t kc = ro.c_cl[c];
-    const uint32_t rlink = kLeaf ? s : c_child[c];
-    const double4 *__restrict__ src = kLeaf ? p4 : c_com;
     double M = 0.0, sx = 0.0, sy = 0.0, sz = 0.0;
-    double S[6] = {0, 0, 0, 0, 0, 0};
-    // kBox: the tight box of the cell's particles (min and max are exact, so the
-    // order of the members does not matter): a leaf's from its particles, a
-    // node's as the union of its children's
+    double *S = m + 4;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) S[k] = 0.0;
+    double4 q[kRun];
+    // the tight box: min and max are exact, so the order of the members does not
+    // matter, nor that the last one may repeat
     double blo[3] = {INFINITY, INFINITY, INFINITY}, bhi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    if (kLeaf && n >= 1u && n <= (uint32_t)kLeafFast) {
-        // one run: its members are loaded once and serve all three passes, with
-        // the operations of the general path below in the same order
-        double4 q[kLeafFast];
-#pragma unroll
-        for (int k = 0; k < kLeafFast; ++k) q[k] = src[s + min((uint32_t)k, n - 1u)];
-#pragma unroll
-        for (int k = 0; k < kLeafFast; ++k)
-            if ((uint32_t)k < n) M = M + q[k].w;
-        if (kBox) {
-#pragma unroll
-            for (int k = 0; k < kLeafFast; ++k) {
-                blo[0] = fmin(blo[0], q[k].x); bhi[0] = fmax(bhi[0], q[k].x);
-                blo[1] = fmin(blo[1], q[k].y); bhi[1] = fmax(bhi[1], q[k].y);
-                blo[2] = fmin(blo[2], q[k].z); bhi[2] = fmax(bhi[2], q[k].z);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < kLeafFast; ++k) {
-            if ((uint32_t)k < n) {
-                sx = sx + q[k].w * q[k].x;
-                sy = sy + q[k].w * q[k].y;
-                sz = sz + q[k].w * q[k].z;
-            }
-        }
-        const double cx = sx / M, cy = sy / M, cz = sz / M;
-#pragma unroll
-        for (int k = 0; k < kLeafFast; ++k) {
-            if ((uint32_t)k < n) {
-                const double dx = q[k].x - cx, dy = q[k].y - cy, dz = q[k].z - cz;
-                const double w = q[k].w;
-                S[0] += w * dx * dx; S[1] += w * dy * dy; S[2] += w * dz * dz;
-                S[3] += w * dx * dy; S[4] += w * dx * dz; S[5] += w * dy * dz;
-            }
-        }
-        c_com[c] = make_double4(cx, cy, cz, M);
-        if (kBox) {
-            double2 *b = box + 3 * (int64_t)c;
-            b[0] = make_double2(blo[0], blo[1]);
-            b[1] = make_double2(blo[2], bhi[0]);
-            b[2] = make_double2(bhi[1], bhi[2]);
-        }
-        double2 *out = reinterpret_cast<double2 *>(c_S + 6 * (int64_t)c);
-        out[0] = make_double2(S[0], S[1]);
-        out[1] = make_double2(S[2], S[3]);
-        out[2] = make_double2(S[4], S[5]);
-        float4 qa, qb;
-        store_walk_multipole(c, S, q0, q1, qa, qb);
-        cell_record(c, s, lev, kc, kLeaf, rlink, n, make_double4(cx, cy, cz, M), qa, qb,
-                    kBox ? blo : nullptr, kBox ? bhi : nullptr, ro);
-        return;
-    }
-    // masses and first moments in one pass (each sum in the members' order)
     for (uint32_t r = 0; r < n; r += kRun) {
-        double4 q[kRun];
 #pragma unroll
-        for (int k = 0; k < kRun; ++k) q[k] = src[s + min(r + k, n - 1)];
+        for (int k = 0; k < kRun; ++k) q[k] = p4[s + min(r + k, n - 1)];
 #pragma unroll
         for (int k = 0; k < kRun; ++k)
             if (r + k < n) M = M + q[k].w;
@@ -858,7 +802,7 @@ __device__ __forceinline__ void cell_moments(uint32_t c, const uint32_t *__restr
                 sz = sz + q[k].w * q[k].z;
             }
         }
-        if (kBox && kLeaf) {
+        if (kBox) {
 #pragma unroll
             for (int k = 0; k < kRun; ++k) {
                 blo[0] = fmin(blo[0], q[k].x); bhi[0] = fmax(bhi[0], q[k].x);
@@ -866,203 +810,545 @@ __device__ __forceinline__ void cell_moments(uint32_t c, const uint32_t *__restr
                 blo[2] = fmin(blo[2], q[k].z); bhi[2] = fmax(bhi[2], q[k].z);
             }
         }
-        if (kBox && !kLeaf) {
-#pragma unroll
-            for (int k = 0; k < kRun; ++k) {
-                const double2 *b = box + 3 * (int64_t)(s + min(r + k, n - 1));
-                const double2 b0 = b[0], b1 = b[1], b2 = b[2];   // lo x, y; lo z, hi x; hi y, z
-                blo[0] = fmin(blo[0], b0.x); blo[1] = fmin(blo[1], b0.y);
-                blo[2] = fmin(blo[2], b1.x); bhi[0] = fmax(bhi[0], b1.y);
-                bhi[1] = fmax(bhi[1], b2.x); bhi[2] = fmax(bhi[2], b2.y);
-            }
-        }
     }
     const double cx = sx / M, cy = sy / M, cz = sz / M;
     for (uint32_t r = 0; r < n; r += kRun) {
-        double4 q[kRun];
+        if (n > (uint32_t)kRun) {       // else they are held from the first pass
 #pragma unroll
-        for (int k = 0; k < kRun; ++k) q[k] = src[s + min(r + k, n - 1)];
-        if (kLeaf) {
+            for (int k = 0; k < kRun; ++k) q[k] = p4[s + min(r + k, n - 1)];
+        }
 #pragma unroll
-            for (int k = 0; k < kRun; ++k) {
-                if (r + k < n) {
-                    const double dx = q[k].x - cx, dy = q[k].y - cy, dz = q[k].z - cz;
-                    const double w = q[k].w;
-                    S[0] += w * dx * dx; S[1] += w * dy * dy; S[2] += w * dz * dz;
-                    S[3] += w * dx * dy; S[4] += w * dx * dz; S[5] += w * dy * dz;
-                }
-            }
-        } else {
-            double2 Sk[kRun][3];
-#pragma unroll
-            for (int k = 0; k < kRun; ++k) {
-                const double2 *p = reinterpret_cast<const double2 *>(c_S + 6 * (int64_t)(s + min(r + k, n - 1)));
-                Sk[k][0] = p[0];
-                Sk[k][1] = p[1];
-                Sk[k][2] = p[2];
-            }
-#pragma unroll
-            for (int k = 0; k < kRun; ++k) {
-                if (r + k < n) {
-                    const double ex = q[k].x - cx, ey = q[k].y - cy, ez = q[k].z - cz;
-                    const double w = q[k].w;
-                    S[0] += Sk[k][0].x + w * ex * ex; S[1] += Sk[k][0].y + w * ey * ey;
-                    S[2] += Sk[k][1].x + w * ez * ez; S[3] += Sk[k][1].y + w * ex * ey;
-                    S[4] += Sk[k][2].x + w * ex * ez; S[5] += Sk[k][2].y + w * ey * ez;
-                }
+        for (int k = 0; k < kRun; ++k) {
+            if (r + k < n) {
+                const double dx = q[k].x - cx, dy = q[k].y - cy, dz = q[k].z - cz;
+                const double w = q[k].w;
+                S[0] += w * dx * dx; S[1] += w * dy * dy; S[2] += w * dz * dz;
+                S[3] += w * dx * dy; S[4] += w * dx * dz; S[5] += w * dy * dz;
             }
         }
     }
-    c_com[c] = make_double4(cx, cy, cz, M);
+    m[0] = cx;
+    m[1] = cy;
+    m[2] = cz;
+    m[3] = M;
     if (kBox) {
-        double2 *b = box + 3 * (int64_t)c;
-        b[0] = make_double2(blo[0], blo[1]);
-        b[1] = make_double2(blo[2], bhi[0]);
-        b[2] = make_double2(bhi[1], bhi[2]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            m[10 + k] = blo[k];
+            m[13 + k] = bhi[k];
+        }
     }
-    double2 *out = reinterpret_cast<double2 *>(c_S + 6 * (int64_t)c);
-    out[0] = make_double2(S[0], S[1]);
-    out[1] = make_double2(S[2], S[3]);
-    out[2] = make_double2(S[4], S[5]);
-    float4 qa, qb;
-    store_walk_multipole(c, S, q0, q1, qa, qb);
-    cell_record(c, s, lev, kc, kLeaf, rlink, n, make_double4(cx, cy, cz, M), qa, qb,
-                kBox ? blo : nullptr, kBox ? bhi : nullptr, ro);
 }
 
-// Moments of node c from its n <= 8 children [s, s + n) (one level deeper,
-// already done), with the same operations in the same order as cell_moments:
-// every child's centre of mass, second moment (and box) is loaded up front in
-// one batch, so a node costs one round of dependent loads after its own record.
 template <bool kBox>
-__device__ __forceinline__ void node_moments(uint32_t c, uint32_t s, uint32_t n, uint32_t f, int lev,
-                                             uint32_t k, double4 *__restrict__ c_com,
-                                             double *__restrict__ c_S, float4 *__restrict__ q0,
-                                             float4 *__restrict__ q1, double2 *__restrict__ box,
-                                             const RecOut &ro)
+__device__ __forceinline__ void leaf_store(uint32_t c, const double *m, double4 *__restrict__ c_com,
+                                           double *__restrict__ c_S, double *__restrict__ box)
 {
-    if (n < 1u || n > 8u) return;      // a node has 1..8 children (checked when the tree is built)
-    double4 q[8];
-    double2 Sk[8][3];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const uint32_t j = s + min((uint32_t)k, n - 1u);
-        q[k] = c_com[j];
-        const double2 *p = reinterpret_cast<const double2 *>(c_S + 6 * (int64_t)j);
-        Sk[k][0] = p[0];
-        Sk[k][1] = p[1];
-        Sk[k][2] = p[2];
-    }
-    double M = 0.0, sx = 0.0, sy = 0.0, sz = 0.0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k)
-        if ((uint32_t)k < n) M = M + q[k].w;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        if ((uint32_t)k < n) {
-            sx = sx + q[k].w * q[k].x;
-            sy = sy + q[k].w * q[k].y;
-            sz = sz + q[k].w * q[k].z;
-        }
-    }
-    const double cx = sx / M, cy = sy / M, cz = sz / M;
-    double S[6] = {0, 0, 0, 0, 0, 0};
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        if ((uint32_t)k < n) {
-            const double ex = q[k].x - cx, ey = q[k].y - cy, ez = q[k].z - cz;
-            const double w = q[k].w;
-            S[0] += Sk[k][0].x + w * ex * ex; S[1] += Sk[k][0].y + w * ey * ey;
-            S[2] += Sk[k][1].x + w * ez * ez; S[3] += Sk[k][1].y + w * ex * ey;
-            S[4] += Sk[k][2].x + w * ex * ez; S[5] += Sk[k][2].y + w * ey * ez;
-        }
-    }
-    c_com[c] = make_double4(cx, cy, cz, M);
-    double blo[3] = {INFINITY, INFINITY, INFINITY}, bhi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    if (kBox) {
-        // the union of the children's boxes (refits only: a second round of
-        // loads keeps the registers of the common path free)
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            // lo x, y; lo z, hi x; hi y, z (repeated members change no min or max)
-            const double2 *bp = box + 3 * (int64_t)(s + min((uint32_t)k, n - 1u));
-            const double2 b0 = bp[0], b1 = bp[1], b2 = bp[2];
-            blo[0] = fmin(blo[0], b0.x); blo[1] = fmin(blo[1], b0.y);
-            blo[2] = fmin(blo[2], b1.x); bhi[0] = fmax(bhi[0], b1.y);
-            bhi[1] = fmax(bhi[1], b2.x); bhi[2] = fmax(bhi[2], b2.y);
-        }
-        double2 *b = box + 3 * (int64_t)c;
-        b[0] = make_double2(blo[0], blo[1]);
-        b[1] = make_double2(blo[2], bhi[0]);
-        b[2] = make_double2(bhi[1], bhi[2]);
-    }
+    c_com[c] = make_double4(m[0], m[1], m[2], m[3]);
     double2 *out = reinterpret_cast<double2 *>(c_S + 6 * (int64_t)c);
-    out[0] = make_double2(S[0], S[1]);
-    out[1] = make_double2(S[2], S[3]);
-    out[2] = make_double2(S[4], S[5]);
-    float4 qa, qb;
-    store_walk_multipole(c, S, q0, q1, qa, qb);
-    cell_record(c, f, lev, k, false, s, n, make_double4(cx, cy, cz, M), qa, qb, kBox ? blo : nullptr,
-                kBox ? bhi : nullptr, ro);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) out[k] = make_double2(m[4 + 2 * k], m[5 + 2 * k]);
+    if (kBox) {
+        double2 *b = reinterpret_cast<double2 *>(box + 6 * (int64_t)c);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) b[k] = make_double2(m[10 + 2 * k], m[11 + 2 * k]);
+    }
 }
 
-// kLeaves: every leaf of the tree (any level); otherwise the nodes of one level.
-// kBox: also the cells' tight boxes (refits).
-template <bool kLeaves, bool kBox>
-__global__ void __launch_bounds__(kBlock)
-moments_kernel(int level, const DevMisc *__restrict__ m, const uint8_t *__restrict__ c_leaf,
-               const uint32_t *__restrict__ c_first, const uint32_t *__restrict__ c_count,
-               const uint32_t *__restrict__ c_child, const uint32_t *__restrict__ c_nchild,
-               const double4 *__restrict__ p4, double4 *__restrict__ c_com,
-               double *__restrict__ c_S, float4 *__restrict__ q0, float4 *__restrict__ q1,
-               double2 *__restrict__ box, RecOut ro)
+// Moments of node c from its n <= 8 children [s, s + n) (one level deeper, already done)
+// by eight lanes of a wavefront (a team), in array order.  Each lane loads a child and
+// forms its terms; lane q of the team then adds the children's terms of sum q one
+// after the other, so every sum keeps the children's order.  (A thread per node
+// gathers its children's records itself, 64 lanes and as many cache lines to an
+// instruction, 40 instructions a node, and does every sum in turn: a level of nodes
+// took 5 to 9 us in one workgroup.)
+// Every lane of the wavefront calls with its team's node; n = 0: none.
+constexpr int kTeam = 8;
+constexpr int kTermRow = kWave + 1;     // odd: lanes of a team read different banks
+struct TeamTerms {
+    double v[6][kTermRow];
+};
+
+// the team's sums in lanes q < kQ: the terms of m members added in order
+template <int kQ>
+__device__ __forceinline__ double team_sum(const TeamTerms &L, int lane, int m)
 {
-    const uint32_t begin = kLeaves ? 0u : m->level_offset[level];
-    const uint32_t count = kLeaves ? m->ncells : m->level_count[level];
-    for (uint32_t t = blockIdx.x * kBlock + threadIdx.x; t < count; t += gridDim.x * kBlock) {
-        const uint32_t c = begin + t;
-        const bool leaf = c_leaf[c] != 0;
-        if (kLeaves) {
-            if (leaf)
-                cell_moments<true, kBox>(c, c_first, c_count, c_child, c_nchild, p4, c_com, c_S,
-                                         q0, q1, box, ro);
-        } else {
-            // the node's own record, loaded with its leaf flag in one round
-            const uint32_t ch = c_child[c], nc = c_nchild[c], f = c_first[c], k = ro.c_cl[c];
-            const int lev = ro.c_level[c];
-            if (!leaf) node_moments<kBox>(c, ch, nc, f, lev, k, c_com, c_S, q0, q1, box, ro);
+    const int q = lane % kTeam, base = lane - q;
+    double v[kTeam], acc = 0.0;
+#pragma unroll
+    for (int k = 0; k < kTeam; ++k) v[k] = L.v[q < kQ ? q : 0][base + k];
+#pragma unroll
+    for (int k = 0; k < kTeam; ++k) acc = k < m ? acc + v[k] : acc;
+    return acc;
+}
+
+// p, Sk, blo, bhi: the lane's child (zeros and an empty box if it has none).  Returns in
+// lane q of the team: M, then x, y, z of the centre of mass (q < 4); second moment q;
+// bound q of the box (lo x, y, z, hi x, y, z).
+struct NodeOut {
+    double com, S, box;
+};
+
+template <bool kBox>
+__device__ __forceinline__ NodeOut node_moments(TeamTerms &L, uint32_t n, const double4 p,
+                                                const double *Sk, double *blo, double *bhi)
+{
+    const int lane = lane_id();
+    const int j = lane % kTeam, base = lane - j;
+    NodeOut out;
+    L.v[0][lane] = p.w;
+    L.v[1][lane] = p.w * p.x;
+    L.v[2][lane] = p.w * p.y;
+    L.v[3][lane] = p.w * p.z;
+    wave_sync();
+    const double sum = team_sum<4>(L, lane, (int)n);    // M; sums of m x, m y, m z
+    wave_sync();
+    const double M = __shfl(sum, base, kWave);
+    const double com = sum / M;
+    const double dx = p.x - __shfl(com, base + 1, kWave), dy = p.y - __shfl(com, base + 2, kWave),
+                 dz = p.z - __shfl(com, base + 3, kWave), w = p.w;
+    L.v[0][lane] = Sk[0] + w * dx * dx;
+    L.v[1][lane] = Sk[1] + w * dy * dy;
+    L.v[2][lane] = Sk[2] + w * dz * dz;
+    L.v[3][lane] = Sk[3] + w * dx * dy;
+    L.v[4][lane] = Sk[4] + w * dx * dz;
+    L.v[5][lane] = Sk[5] + w * dy * dz;
+    wave_sync();
+    out.S = team_sum<6>(L, lane, (int)n);       // xx, yy, zz, xy, xz, yz
+    wave_sync();
+    out.com = j == 0 ? M : com;
+    out.box = 0.0;
+    if (kBox) {
+        // the union of the children's boxes
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+#pragma unroll
+            for (int d = kTeam / 2; d > 0; d >>= 1) {
+                blo[i] = fmin(blo[i], __shfl_xor(blo[i], d, kWave));
+                bhi[i] = fmax(bhi[i], __shfl_xor(bhi[i], d, kWave));
+            }
+            if (j == i) out.box = blo[i];
+            if (j == i + 3) out.box = bhi[i];
+        }
+    }
+    return out;
+}
+
+template <bool kBox>
+__device__ __forceinline__ void node_store(const NodeOut &o, uint32_t c, double4 *__restrict__ c_com,
+                                           double *__restrict__ c_S, double *__restrict__ box)
+{
+    const int j = lane_id() % kTeam;
+    if (j < 4) reinterpret_cast<double *>(c_com + c)[j == 0 ? 3 : j - 1] = o.com;
+    if (j < 6) c_S[6 * (int64_t)c + j] = o.S;
+    if (kBox && j < 6) box[6 * (int64_t)c + j] = o.box;
+}
+
+// The same for a node whose children [s, s + n) have their moments in device memory.
+template <bool kBox>
+__device__ __forceinline__ void node_from_memory(TeamTerms &L, uint32_t c, uint32_t s, uint32_t n,
+                                                 double4 *__restrict__ c_com,
+                                                 double *__restrict__ c_S, double *__restrict__ box)
+{
+    const uint32_t j = (uint32_t)(lane_id() % kTeam);
+    double4 p = make_double4(0.0, 0.0, 0.0, 0.0);
+    double Sk[6] = {0, 0, 0, 0, 0, 0};
+    double blo[3] = {INFINITY, INFINITY, INFINITY}, bhi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    if (j < n) {
+        p = c_com[s + j];
+        const double2 *q = reinterpret_cast<const double2 *>(c_S + 6 * (int64_t)(s + j));
+        const double2 a = q[0], b = q[1], d = q[2];
+        Sk[0] = a.x; Sk[1] = a.y; Sk[2] = b.x; Sk[3] = b.y; Sk[4] = d.x; Sk[5] = d.y;
+        if (kBox) {
+            const double2 *bx = reinterpret_cast<const double2 *>(box + 6 * (int64_t)(s + j));
+            const double2 b0 = bx[0], b1 = bx[1], b2 = bx[2];
+            blo[0] = b0.x; blo[1] = b0.y; blo[2] = b1.x;
+            bhi[0] = b1.y; bhi[1] = b2.x; bhi[2] = b2.y;
+        }
+    }
+    const NodeOut o = node_moments<kBox>(L, n, p, Sk, blo, bhi);
+    if (n) node_store<kBox>(o, c, c_com, c_S, box);
+}
+
+template <bool kBox>
+__device__ __forceinline__ void load_moments(uint32_t c, const double4 *__restrict__ c_com,
+                                             const double *__restrict__ c_S,
+                                             const double *__restrict__ box, double *m)
+{
+    const double4 cm = c_com[c];
+    m[0] = cm.x;
+    m[1] = cm.y;
+    m[2] = cm.z;
+    m[3] = cm.w;
+    const double2 *s = reinterpret_cast<const double2 *>(c_S + 6 * (int64_t)c);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const double2 v = s[k];
+        m[4 + 2 * k] = v.x;
+        m[5 + 2 * k] = v.y;
+    }
+    if (kBox) {
+        const double2 *b = reinterpret_cast<const double2 *>(box + 6 * (int64_t)c);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const double2 v = b[k];
+            m[10 + 2 * k] = v.x;
+            m[11 + 2 * k] = v.y;
         }
     }
 }
 
-// The nodes of levels hi down to lo in one workgroup of kThreads, a barrier
-// between levels: for the levels below the tree's expected depth, which normally
-// hold no cells, and for the small levels next to the root, where a launch per
-// level would cost more than the work.
-constexpr int kLevelsBlock = 256;
-constexpr int kTopBlock = 512;
-constexpr uint32_t kTopCells = 512;     // top levels of at most this many cells share a launch
-
-template <bool kBox, int kThreads>
-__global__ void __launch_bounds__(kThreads)
-moments_levels_kernel(int hi, int lo, const DevMisc *__restrict__ m,
-                      const uint8_t *__restrict__ c_leaf, const uint32_t *__restrict__ c_first,
-                      const uint32_t *__restrict__ c_count, const uint32_t *__restrict__ c_child,
-                      const uint32_t *__restrict__ c_nchild, const double4 *__restrict__ p4,
-                      double4 *__restrict__ c_com, double *__restrict__ c_S,
-                      float4 *__restrict__ q0, float4 *__restrict__ q1, double2 *__restrict__ box,
-                      RecOut ro)
+// The opening radius and walk record of cell c (of level lev in cluster k, first
+// particle f) from its moments m (see leaf_moments); link, info: see WalkCell.
+template <bool kBox>
+__device__ __forceinline__ void moments_record(uint32_t c, uint32_t f, int lev, uint32_t k, bool leaf,
+                                               uint32_t link, uint32_t info, const double *m,
+                                               const RecOut &ro)
 {
-    for (int level = hi; level >= lo; --level) {
-        const uint32_t begin = m->level_offset[level];
-        const uint32_t count = m->level_count[level];
-        for (uint32_t t = threadIdx.x; t < count; t += kThreads) {
-            const uint32_t c = begin + t;
-            const uint32_t ch = c_child[c], nc = c_nchild[c], f = c_first[c], k = ro.c_cl[c];
-            if (c_leaf[c] == 0)
-                node_moments<kBox>(c, ch, nc, f, level, k, c_com, c_S, q0, q1, box, ro);
+    float s3[6];            // 3 S in float32
+#pragma unroll
+    for (int i = 0; i < 6; ++i) s3[i] = (float)(3.0 * m[4 + i]);
+    cell_record(c, f, lev, k, leaf, link, info, make_double4(m[0], m[1], m[2], m[3]), s3,
+                kBox ? m + 10 : nullptr, kBox ? m + 13 : nullptr, ro);
+}
+
+// What the moments kernels read of the cells.
+struct CellIn {
+    const DevMisc *m;
+    const RunEdge *edges;
+    uint32_t nedges;            // runs
+    int64_t n;
+    const uint8_t *lam;         // see split_leaf_kernel
+    const uint8_t *leaf;
+    const uint32_t *first, *count, *child, *nchild;
+    const double4 *p4;
+};
+
+// the starts of level lev before run e (all of the level's after the last run)
+__device__ __forceinline__ uint32_t starts_before(const CellIn &in, int lev, uint32_t e)
+{
+    return e < in.nedges ? in.edges[e].c[lev] : in.m->level_count[lev];
+}
+
+__device__ __forceinline__ int64_t run_begin(const CellIn &in, uint32_t e)
+{
+    return e < in.nedges ? (int64_t)in.edges[e].x : in.n;
+}
+
+// A barrier that orders LDS only: loads ahead and stores of results stay in flight.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Moments, opening radii and walk records of every leaf and of every node that lies
+// within one workgroup's kRuns runs.  The cells of a level that start in them are
+// consecutive, and the runs' edges say which; only the last of them can reach beyond
+// (span_moments_kernel does those).  Leaves of all levels first, a
+// thread each, then the nodes level by level from the deepest, a team each: a node's
+// children lie in the run if the node does.  The moments pass from level to level
+// through LDS (stores to device memory and the loads behind them cost a level 2 us),
+// a run of more than kCap cells through device memory.  The records, which no other
+// cell waits for, come last.  kBox: also the cells' tight boxes (refits).
+template <bool kBox, int kThreads, int kCap, int kRuns>
+__global__ void __launch_bounds__(kThreads)
+run_moments_kernel(CellIn in, double4 *__restrict__ c_com, double *__restrict__ c_S,
+                   double *__restrict__ box, RecOut ro)
+{
+    constexpr uint32_t kTeams = kThreads / kTeam;
+    constexpr int kFields = kBox ? 16 : 10;
+    static_assert(kCap % 2 == 1, "a cell's fields in different banks");
+    // the staged particles (a run's and as many more as an ordinary leaf can take it
+    // past its end), then the moments of the run's cells (see leaf_moments)
+    constexpr int kStage = (kRuns == 1 ? (kRunTiles + 1) * kTreeTile : kRuns * kRunTiles * kTreeTile) + 64;
+    constexpr int kStore = kFields * kCap + (kThreads / kWave) * 6 * kTermRow;
+    __shared__ double4 s_raw[(kStore / 4 + 1) > kStage ? kStore / 4 + 1 : kStage];
+    double(*s_m)[kCap] = reinterpret_cast<double(*)[kCap]>(s_raw);
+    TeamTerms *s_terms = reinterpret_cast<TeamTerms *>(&s_m[kFields][0]);
+    __shared__ uint16_t s_list[kCap];           // the run's leaves (places in the run)
+    __shared__ uint32_t s_leaves;
+    __shared__ uint16_t s_ch[kCap];             // first child (place in the run)
+    __shared__ uint8_t s_nc[kCap];              // children; 0: not a node of the run
+    __shared__ uint32_t s_b[kLevels], s_pre[kLevels + 1];
+    if (in.m->ncells == 0) return;      // only after an internal error
+    const uint32_t e0 = blockIdx.x * kRuns, e1 = e0 + kRuns;
+    const int64_t end = run_begin(in, e1);
+    const int t = threadIdx.x;
+    TeamTerms &L = s_terms[t / kWave];
+    if (t < kWave) {
+        uint32_t b = 0, e = 0;
+        if (t < kLevels) {
+            const uint32_t off = in.m->level_offset[t];
+            b = off + starts_before(in, t, e0);
+            e = off + starts_before(in, t, e1);
+            s_b[t] = b;
+        }
+        const uint32_t inc = wave_incl_scan_add(e - b);
+        if (t < kLevels) s_pre[t + 1] = inc;
+        if (t == 0) s_pre[0] = 0;
+    }
+    __syncthreads();
+    const uint32_t total = s_pre[kLevels];
+    const bool lds = total <= (uint32_t)kCap;
+    auto cell_of = [&](uint32_t i, int &lev) -> uint32_t {
+        lev = 0;
+        while (i >= s_pre[lev + 1]) ++lev;
+        return s_b[lev] + (i - s_pre[lev]);
+    };
+    // a node of the run: all of its particles lie in it
+    auto inside = [&](uint32_t i, int lev, uint32_t f, uint32_t cnt) {
+        return i + 1 < s_pre[lev + 1] || (int64_t)f + cnt <= end;
+    };
+    const uint32_t start = (uint32_t)run_begin(in, e0);
+    if (lds) {
+        const uint32_t staged = (uint32_t)min((int64_t)kStage, in.n - start);
+        for (uint32_t i = t; i < staged; i += kThreads) s_raw[i] = in.p4[start + i];
+        if (t == 0) s_leaves = 0;
+        __syncthreads();
+        for (uint32_t i = t; i < total; i += kThreads) {
+            int lev;
+            const uint32_t c = cell_of(i, lev);
+            const bool leaf = in.leaf[c] != 0;
+            const uint32_t f = in.first[c], cnt = in.count[c], ch = in.child[c], nc = in.nchild[c];
+            s_nc[i] = !leaf && inside(i, lev, f, cnt) ? (uint8_t)min(nc, 8u) : (uint8_t)0;
+            if (!leaf) s_ch[i] = (uint16_t)(s_pre[lev + 1] + (ch - s_b[lev + 1]));
+            if (leaf && cnt) s_list[atomicAdd(&s_leaves, 1u)] = (uint16_t)i;
         }
         __syncthreads();
+        // the moments take the particles' place when the leaves (all of them but in
+        // odd trees: the first kThreads) have read them
+        const uint32_t leaves = s_leaves;
+        double m[kFields];
+        if ((uint32_t)t < leaves) {
+            int lev;
+            const uint32_t c = cell_of(s_list[t], lev);
+            const uint32_t f = in.first[c], cnt = in.count[c];
+            if (f - start + cnt <= staged) leaf_moments<kBox>(f - start, cnt, s_raw, m);
+            else leaf_moments<kBox>(f, cnt, in.p4, m);
+            leaf_store<kBox>(c, m, c_com, c_S, box);
+        }
+        lds_barrier();
+        for (uint32_t q = t; q < leaves; q += kThreads) {
+            const uint32_t i = s_list[q];
+            if (q != (uint32_t)t) {
+                int lev;
+                const uint32_t c = cell_of(i, lev);
+                leaf_moments<kBox>(in.first[c], in.count[c], in.p4, m);
+                leaf_store<kBox>(c, m, c_com, c_S, box);
+            }
+#pragma unroll
+            for (int d = 0; d < kFields; ++d) s_m[d][i] = m[d];
+        }
+    } else {
+        for (uint32_t i = t; i < total; i += kThreads) {
+            int lev;
+            const uint32_t c = cell_of(i, lev);
+            const uint32_t f = in.first[c], cnt = in.count[c];
+            if (!in.leaf[c] || cnt == 0u) continue;
+            double m[kFields];
+            leaf_moments<kBox>(f, cnt, in.p4, m);
+            leaf_store<kBox>(c, m, c_com, c_S, box);
+        }
+    }
+    // (a wavefront's trips are uniform: its teams past the end have no node)
+    const uint32_t team = (uint32_t)t / kTeam, team0 = (uint32_t)t / kWave * (kWave / kTeam);
+    const uint32_t j = (uint32_t)t % kTeam;
+    int lev = kMaxLevel - 1;            // level 20 holds only leaves
+    while (lev >= 0 && s_pre[lev] == s_pre[lev + 1]) --lev;
+    if (lds) {
+        for (; lev >= 0; --lev) {
+            lds_barrier();
+            const uint32_t e = s_pre[lev + 1];
+            for (uint32_t i0 = s_pre[lev]; i0 + team0 < e; i0 += kTeams) {
+                const uint32_t i = i0 + team;
+                const uint32_t n = i < e ? s_nc[i] : 0u;
+                if (ballot(n != 0u) == 0ull) continue;
+                double4 p = make_double4(0.0, 0.0, 0.0, 0.0);
+                double Sk[6] = {0, 0, 0, 0, 0, 0};
+                double blo[3] = {INFINITY, INFINITY, INFINITY};
+                double bhi[3] = {-INFINITY, -INFINITY, -INFINITY};
+                if (j < n) {
+                    const uint32_t k = s_ch[i] + j;
+                    p = make_double4(s_m[0][k], s_m[1][k], s_m[2][k], s_m[3][k]);
+#pragma unroll
+                    for (int q = 0; q < 6; ++q) Sk[q] = s_m[4 + q][k];
+                    if (kBox) {
+#pragma unroll
+                        for (int q = 0; q < 3; ++q) {
+                            blo[q] = s_m[kFields - 6 + q][k];
+                            bhi[q] = s_m[kFields - 3 + q][k];
+                        }
+                    }
+                }
+                const NodeOut o = node_moments<kBox>(L, n, p, Sk, blo, bhi);
+                if (n) {
+                    if (j < 4u) s_m[j == 0u ? 3u : j - 1u][i] = o.com;
+                    if (j < 6u) s_m[4u + j][i] = o.S;
+                    if (kBox && j < 6u) s_m[kFields - 6u + j][i] = o.box;
+                    node_store<kBox>(o, s_b[lev] + (i - s_pre[lev]), c_com, c_S, box);
+                }
+            }
+        }
+    } else {
+        for (; lev >= 0; --lev) {
+            __syncthreads();
+            const uint32_t e = s_pre[lev + 1];
+            for (uint32_t i0 = s_pre[lev]; i0 + team0 < e; i0 += kTeams) {
+                const uint32_t i = i0 + team;
+                uint32_t n = 0, ch = 0;
+                const uint32_t c = s_b[lev] + (i - s_pre[lev]);
+                if (i < e && !in.leaf[c] && inside(i, lev, in.first[c], in.count[c])) {
+                    ch = in.child[c];
+                    n = min(in.nchild[c], 8u);
+                }
+                node_from_memory<kBox>(L, c, ch, n, c_com, c_S, box);
+            }
+        }
+    }
+    if (lds) lds_barrier();
+    else __syncthreads();
+    for (uint32_t i = t; i < total; i += kThreads) {
+        const uint32_t c = cell_of(i, lev);
+        const bool leaf = in.leaf[c] != 0;
+        const uint32_t f = in.first[c], cnt = in.count[c], kc = ro.c_cl[c];
+        const uint32_t ch = in.child[c], nc = in.nchild[c];
+        if (cnt == 0u || (!leaf && !inside(i, lev, f, cnt))) continue;
+        double m[kFields];
+        if (lds) {
+#pragma unroll
+            for (int k = 0; k < kFields; ++k) m[k] = s_m[k][i];
+        } else {
+            load_moments<kBox>(c, c_com, c_S, box, m);
+        }
+        moments_record<kBox>(c, f, lev, kc, leaf, leaf ? f : ch, leaf ? cnt : nc, m, ro);
+    }
+}
+
+// Units of several sizes: runs (depth 0), about 64 runs (depth 1), about 64 of those
+// (depth 2) and so on.  A unit begins at that one of the first 16 lesser units of its 64
+// whose edge has the lowest split level, again so that few cells reach across.
+constexpr uint32_t kUnitLog = 6, kWindowLog = 4;
+constexpr uint32_t kUnitMost = (1u << kUnitLog) + (1u << kWindowLog) - 1;   // lesser units in one
+
+// the first run of unit u
+__device__ __forceinline__ uint32_t unit_begin(const CellIn &in, uint32_t depth, uint32_t u)
+{
+    const uint64_t b = (uint64_t)u << (kUnitLog * depth);
+    if (b >= in.nedges) return in.nedges;
+    uint32_t best = (uint32_t)b, low = 255;
+    // the candidates in order: digits of kWindowLog bits in places of kUnitLog bits
+    for (uint32_t k = 0; k < 1u << (kWindowLog * depth); ++k) {
+        uint64_t e = b;
+        for (uint32_t d = 0; d < depth; ++d)
+            e += (uint64_t)((k >> (kWindowLog * d)) & ((1u << kWindowLog) - 1)) << (kUnitLog * d);
+        const uint32_t s = e < in.nedges ? in.edges[e].split : 255u;
+        if (s < low) {
+            low = s;
+            best = (uint32_t)e;
+        }
+    }
+    return best;
+}
+
+// The nodes that reach beyond a unit but lie within the workgroup's next larger unit
+// (kAll: one workgroup, all of the rest): in each level at most one per unit, the last
+// cell that starts in it.  Level by level like a run's own nodes; which nodes there are,
+// and their children, is looked up for all levels first, for the chain of levels is
+// what bounds it.  As units begin between large cells, each launch has a part of the
+// tree's levels.
+template <bool kBox, int kUnits, int kThreads, bool kAll>
+__global__ void __launch_bounds__(kThreads)
+span_moments_kernel(CellIn in, uint32_t depth, double4 *__restrict__ c_com, double *__restrict__ c_S,
+                    double *__restrict__ box, RecOut ro)
+{
+    constexpr uint32_t kTeams = kThreads / kTeam;
+    static_assert(kUnits <= kThreads && (kAll || kUnits >= (int)kUnitMost), "a thread per unit");
+    __shared__ TeamTerms s_terms[kThreads / kWave];
+    __shared__ uint32_t s_cell[kMaxLevel][kUnits], s_ch[kMaxLevel][kUnits];
+    __shared__ uint8_t s_nc[kMaxLevel][kUnits];
+    __shared__ uint32_t s_cnt[kMaxLevel];               // such nodes of a level
+    if (in.m->ncells == 0) return;
+    const int t = threadIdx.x;
+    // the runs [r0, r1) of the workgroup
+    uint32_t r1 = in.nedges, e0 = 0, e1 = 0;            // [e0, e1): the thread's unit
+    if (kAll) {
+        if (t < kUnits) {
+            e0 = unit_begin(in, depth, (uint32_t)t);
+            e1 = unit_begin(in, depth, (uint32_t)t + 1u);
+        }
+    } else {
+        const uint32_t r0 = unit_begin(in, depth + 1u, blockIdx.x);
+        r1 = unit_begin(in, depth + 1u, blockIdx.x + 1u);
+        // r0 begins the lesser unit r0 >> (kUnitLog * depth)
+        if (t < kUnits) {
+            const uint32_t u = (r0 >> (kUnitLog * depth)) + (uint32_t)t;
+            e0 = unit_begin(in, depth, u);
+            e1 = unit_begin(in, depth, u + 1u);
+        }
+    }
+    const int64_t range_end = run_begin(in, r1);
+    if (t < kMaxLevel) s_cnt[t] = 0;
+    __syncthreads();
+    // nothing reaches beyond the last unit, and what reaches beyond the larger one is not
+    // done here
+    if (e1 > e0 && e1 < r1) {
+        // the nodes holding both the unit's last particle and the next one: those of the
+        // levels above the one where the two part and above the last one's leaf
+        const RunEdge &a = in.edges[e0], &b = in.edges[e1];
+        const int top = min((int)b.split, (int)in.lam[b.x - 1]);
+        uint32_t c[kMaxLevel], ch[kMaxLevel], nc[kMaxLevel], f[kMaxLevel], cnt[kMaxLevel];
+#pragma unroll
+        for (int lev = 0; lev < kMaxLevel; ++lev) {
+            c[lev] = 0;
+            if (lev >= top) continue;
+            const uint32_t e = b.c[lev];
+            c[lev] = e > a.c[lev] ? in.m->level_offset[lev] + e : 0u;   // one past the last start
+        }
+#pragma unroll
+        for (int lev = 0; lev < kMaxLevel; ++lev) {
+            const uint32_t q = c[lev] ? c[lev] - 1u : 0u;
+            f[lev] = cnt[lev] = ch[lev] = nc[lev] = 0;
+            if (!c[lev]) continue;
+            if (!kAll) {
+                f[lev] = in.first[q];
+                cnt[lev] = in.count[q];
+            }
+            ch[lev] = in.child[q];
+            nc[lev] = in.nchild[q];
+        }
+#pragma unroll
+        for (int lev = 0; lev < kMaxLevel; ++lev) {
+            if (!c[lev] || (!kAll && (int64_t)f[lev] + cnt[lev] > range_end)) continue;
+            const uint32_t i = atomicAdd(&s_cnt[lev], 1u);
+            s_cell[lev][i] = c[lev] - 1u;
+            s_ch[lev][i] = ch[lev];
+            s_nc[lev][i] = (uint8_t)min(nc[lev], 8u);
+        }
+    }
+    __syncthreads();
+    TeamTerms &L = s_terms[t / kWave];
+    const uint32_t team = (uint32_t)t / kTeam, team0 = (uint32_t)t / kWave * (kWave / kTeam);
+    for (int lev = kMaxLevel - 1; lev >= 0; --lev) {
+        const uint32_t count = s_cnt[lev];
+        if (count == 0u) continue;          // uniform
+        for (uint32_t i0 = 0; i0 + team0 < count; i0 += kTeams) {
+            const uint32_t i = i0 + team;
+            const bool has = i < count;
+            node_from_memory<kBox>(L, has ? s_cell[lev][i] : 0u, has ? s_ch[lev][i] : 0u,
+                                   has ? s_nc[lev][i] : 0u, c_com, c_S, box);
+        }
+        __syncthreads();
+    }
+    for (int i = t; i < kMaxLevel * kUnits; i += kThreads) {
+        const int lev = i / kUnits, q = i % kUnits;
+        if ((uint32_t)q >= s_cnt[lev]) continue;
+        const uint32_t c = s_cell[lev][q];
+        double m[kBox ? 16 : 10];
+        load_moments<kBox>(c, c_com, c_S, box, m);
+        moments_record<kBox>(c, in.first[c], lev, ro.c_cl[c], false, s_ch[lev][q], s_nc[lev][q], m,
+                             ro);
     }
 }
 
@@ -1073,23 +1359,23 @@ __global__ void __launch_bounds__(kBlock)
 rcrit_kernel(DevMisc *__restrict__ m, RecOut ro, const uint32_t *__restrict__ c_first,
              const uint32_t *__restrict__ c_count, const uint32_t *__restrict__ c_child,
              const uint32_t *__restrict__ c_nchild, const uint8_t *__restrict__ c_leaf,
-             const double4 *__restrict__ c_com, const float4 *__restrict__ q0,
-             const float4 *__restrict__ q1, const double2 *__restrict__ box)
+             const double4 *__restrict__ c_com, const double *__restrict__ box)
 {
     const uint32_t ncells = m->ncells;
     for (uint32_t c = blockIdx.x * kBlock + threadIdx.x; c < ncells; c += gridDim.x * kBlock) {
         const uint32_t f = c_first[c];
         const bool leaf = c_leaf[c] != 0;
-        double blo[3], bhi[3];
+        double bx[6];
         if (box) {
-            const double2 b0 = box[3 * (int64_t)c], b1 = box[3 * (int64_t)c + 1],
-                          b2 = box[3 * (int64_t)c + 2];
-            blo[0] = b0.x; blo[1] = b0.y; blo[2] = b1.x;
-            bhi[0] = b1.y; bhi[1] = b2.x; bhi[2] = b2.y;
+#pragma unroll
+            for (int i = 0; i < 6; ++i) bx[i] = box[6 * (int64_t)c + i];
         }
+        float s3[6];        // 3 S stays as it is in the record
+#pragma unroll
+        for (int q = 0; q < 6; ++q) s3[q] = ro.rec[c].s3[q];
         cell_record(c, f, ro.c_level[c], ro.c_cl[c], leaf, leaf ? f : c_child[c],
-                    leaf ? c_count[c] : c_nchild[c], c_com[c], q0[c], q1[c], box ? blo : nullptr,
-                    box ? bhi : nullptr, ro);
+                    leaf ? c_count[c] : c_nchild[c], c_com[c], s3, box ? bx : nullptr,
+                    box ? bx + 3 : nullptr, ro);
     }
 }
 
@@ -1163,6 +1449,21 @@ hipError_t launch_reorder(bh_ctx *c, const uint32_t *perm)
     return hipSuccess;
 }
 
+namespace {
+
+// the runs' edges, behind the level rows and the compaction's counts
+RunEdge *run_edges(const bh_ctx *c)
+{
+    return reinterpret_cast<RunEdge *>(c->blk + level_rows_words(c->n) + compact_words(c->n));
+}
+
+}  // namespace
+
+int64_t run_edge_words(int64_t n)
+{
+    return (int64_t)(sizeof(RunEdge) / sizeof(uint32_t)) * (n / (kRunTiles * kTreeTile) + 1);
+}
+
 hipError_t launch_tree(bh_ctx *c)
 {
     const int64_t n = c->n;
@@ -1180,7 +1481,8 @@ hipError_t launch_tree(bh_ctx *c)
     BH_LAUNCH_CHECK();
     hipLaunchKernelGGL(emit_cells_kernel, dim3(nblk), dim3(kTreeTile), 0, c->stream, c->split,
                        c->lam, n, blk, nblk, c->misc, c->c_first, c->c_level, c->c_leaf,
-                       c->c_parent, c->c_child, c->c_end, c->c_nchild, c->pcl, c->c_cl);
+                       c->c_parent, c->c_child, c->c_end, c->c_nchild, c->pcl, c->c_cl,
+                       run_edges(c));
     BH_LAUNCH_CHECK();
     int g = grid_for(c->cap_c, kBlock);
     if (g > kFixedGrid) g = kFixedGrid;
@@ -1207,53 +1509,48 @@ hipError_t launch_group_boxes(bh_ctx *c)
     return hipSuccess;
 }
 
+// The leaves and nodes within runs of about 1024 particles, then the nodes across runs:
+// of up to kSpanUnits runs in one workgroup, of more first in units of about 64 runs, a
+// workgroup each, and then across those.  The time is the chain of levels, not the
+// bytes (a level's barrier, its LDS or L2 reads, two divisions): leaves and nodes in one
+// launch per level or group of levels took 28, 89, 110 and 412 us at 1500, 240K and 2^20
+// particles and for 512 clusters of 3.2M, this 19, 43, 96 and 354.  Units beginning
+// at any multiple of their size, not between large cells: 19, 61, 103, 386.
+// Up to 4096 particles one workgroup's four runs hold the whole system (whole builds:
+// 140 us at 1500 particles and 162 at 4000; four workgroups and one across them 150 and
+// 168), except with boxes, whose moments need more LDS than there is.
+// kSpanUnits: as many as the lists of their nodes leave LDS for (builds of 300,000 and
+// 500,000 particles 232 and 261 us, with 256 units, so one launch more, 255 and 286).
+constexpr int kSpanUnits = 512;
+
 template <bool kBox>
-hipError_t moments_launches(bh_ctx *c, double2 *box)
+hipError_t moments_launches(bh_ctx *c, double *box)
 {
-    int g = grid_for(c->cap_c, kBlock);
-    if (g > kFixedGrid) g = kFixedGrid;
     // every cell's opening radius and walk record are written with its moments
     const RecOut ro{c->clus, c->dom, c->c_level, c->c_cl, c->key[0], c->c_rcrit2, c->c_rec, c->c_geo};
-    // every leaf, whatever its level, from its particles
-    hipLaunchKernelGGL((moments_kernel<true, kBox>), dim3(g), dim3(kBlock), 0, c->stream, 0, c->misc,
-                       c->c_leaf, c->c_first, c->c_count, c->c_child, c->c_nchild, c->p4[c->cur],
-                       c->c_com, c->c_S, c->c_q0, c->c_q1, box, ro);
+    const uint32_t runs = (uint32_t)grid_for(c->n, kRunTiles * kTreeTile);
+    const CellIn in{c->misc, run_edges(c), runs, c->n, c->lam, c->c_leaf, c->c_first, c->c_count,
+                    c->c_child, c->c_nchild, c->p4[c->cur]};
+    if (!kBox && runs <= 4) {
+        hipLaunchKernelGGL((run_moments_kernel<false, 1024, 1279, 4>), dim3(1), dim3(1024), 0,
+                           c->stream, in, c->c_com, c->c_S, box, ro);
+        BH_LAUNCH_CHECK();
+        c->rec_fresh = true;
+        return hipSuccess;
+    }
+    hipLaunchKernelGGL((run_moments_kernel<kBox, 512, 511, 1>), dim3(runs), dim3(512), 0, c->stream,
+                       in, c->c_com, c->c_S, box, ro);
     BH_LAUNCH_CHECK();
-    // nodes from their children, deepest level first (level 20 holds only leaves).
-    // The level sizes are known on the device only; the host takes those seen at
-    // its last synchronisation as hints: levels below the hinted depth (normally
-    // empty; a tree that grew deeper since) share one workgroup, and so do the
-    // levels next to the root while each holds at most kTopCells cells; every
-    // other level gets a launch of its own with a grid sized for twice its hinted
-    // count.  The kernels read the true counts and loop over them, so any tree is
-    // handled whatever the hints.
-    const DevMisc &hint = *c->misc_h;
-    const int deep = hint.depth ? std::min(kMaxLevel - 1, (int)hint.depth) : kMaxLevel - 1;
-    if (deep < kMaxLevel - 1) {
-        hipLaunchKernelGGL((moments_levels_kernel<kBox, kLevelsBlock>), dim3(1), dim3(kLevelsBlock),
-                           0, c->stream, kMaxLevel - 1, deep + 1, c->misc, c->c_leaf, c->c_first,
-                           c->c_count, c->c_child, c->c_nchild, c->p4[c->cur], c->c_com, c->c_S,
-                           c->c_q0, c->c_q1, box, ro);
-        BH_LAUNCH_CHECK();
-    }
-    // the small levels next to the root: 0 .. top
-    int top = -1;
-    if (hint.depth)
-        while (top < deep && hint.level_count[top + 1] <= kTopCells) ++top;
-    for (int lev = deep; lev > top; --lev) {
-        int gl = g;
-        if (hint.depth && hint.level_count[lev])
-            gl = (int)std::min<int64_t>(g, grid_for(2 * (int64_t)hint.level_count[lev], kBlock));
-        hipLaunchKernelGGL((moments_kernel<false, kBox>), dim3(gl), dim3(kBlock), 0, c->stream, lev,
-                           c->misc, c->c_leaf, c->c_first, c->c_count, c->c_child, c->c_nchild,
-                           c->p4[c->cur], c->c_com, c->c_S, c->c_q0, c->c_q1, box, ro);
-        BH_LAUNCH_CHECK();
-    }
-    if (top >= 0) {
-        hipLaunchKernelGGL((moments_levels_kernel<kBox, kTopBlock>), dim3(1), dim3(kTopBlock), 0,
-                           c->stream, top, 0, c->misc, c->c_leaf, c->c_first, c->c_count,
-                           c->c_child, c->c_nchild, c->p4[c->cur], c->c_com, c->c_S, c->c_q0,
-                           c->c_q1, box, ro);
+    if (runs > 1) {
+        uint32_t depth = 0, units = runs;
+        for (; units > kSpanUnits; ++depth) {
+            units = (uint32_t)grid_for(units, 1 << kUnitLog);
+            hipLaunchKernelGGL((span_moments_kernel<kBox, 80, 512, false>), dim3(units), dim3(512), 0,
+                               c->stream, in, depth, c->c_com, c->c_S, box, ro);
+            BH_LAUNCH_CHECK();
+        }
+        hipLaunchKernelGGL((span_moments_kernel<kBox, kSpanUnits, 1024, true>), dim3(1), dim3(1024), 0,
+                           c->stream, in, depth, c->c_com, c->c_S, box, ro);
         BH_LAUNCH_CHECK();
     }
     c->rec_fresh = true;
@@ -1262,7 +1559,7 @@ hipError_t moments_launches(bh_ctx *c, double2 *box)
 
 hipError_t launch_moments(bh_ctx *c, bool boxes)
 {
-    if (boxes) return moments_launches<true>(c, reinterpret_cast<double2 *>(c->c_box));
+    if (boxes) return moments_launches<true>(c, c->c_box);
     return moments_launches<false>(c, nullptr);
 }
 
@@ -1274,8 +1571,8 @@ hipError_t launch_rcrit(bh_ctx *c)
     if (g > kFixedGrid) g = kFixedGrid;
     const RecOut ro{c->clus, c->dom, c->c_level, c->c_cl, c->key[0], c->c_rcrit2, c->c_rec, c->c_geo};
     hipLaunchKernelGGL(rcrit_kernel, dim3(g), dim3(kBlock), 0, c->stream, c->misc, ro, c->c_first,
-                       c->c_count, c->c_child, c->c_nchild, c->c_leaf, c->c_com, c->c_q0, c->c_q1,
-                       c->refitted ? reinterpret_cast<const double2 *>(c->c_box) : nullptr);
+                       c->c_count, c->c_child, c->c_nchild, c->c_leaf, c->c_com,
+                       c->refitted ? c->c_box : nullptr);
     BH_LAUNCH_CHECK();
     c->rec_fresh = true;
     return hipSuccess;

@@ -184,7 +184,7 @@ int bh_forces_static(const double *pos, const double *mass, int64_t n, float the
         return fail(BH_EDEVICE, "launch of the build failed");
     }
     // the build's error bits are checked before the walk runs on its tree, as
-    // bh_build_tree does; the counts also refresh the launch hints
+    // bh_build_tree does
     TRY_ST(wait_check(s, false));
     if (ctx_enqueue_forces_out(&c, acc, pot) != hipSuccess) {
         (void)hipGetLastError();

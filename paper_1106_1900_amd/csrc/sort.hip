@@ -1056,8 +1056,8 @@ hipError_t compact_flags(bh_ctx *c, const uint8_t *flags, int64_t n, uint32_t *i
 {
     // one block at least, so that the counts are written for n = 0 too
     const int nblk = std::max(1, (int)((n + kScanTile - 1) / kScanTile));
-    // the level and digit counts' buffer: free between the level ranks and the next sort
-    ClassCounts *part = reinterpret_cast<ClassCounts *>(c->blk);
+    // behind the level rows (which the cells are made from) and before the runs' edges
+    ClassCounts *part = reinterpret_cast<ClassCounts *>(c->blk + level_rows_words(c->n));
     hipLaunchKernelGGL(scan_reduce_kernel, dim3(nblk), dim3(kScanThreads), 0, c->stream, flags, n,
                        part);
     BH_LAUNCH_CHECK();
@@ -1065,6 +1065,11 @@ hipError_t compact_flags(bh_ctx *c, const uint8_t *flags, int64_t n, uint32_t *i
                        part, idx, count, order, upto, rank);
     BH_LAUNCH_CHECK();
     return hipSuccess;
+}
+
+int64_t compact_words(int64_t n)
+{
+    return kClassWords * ((n + kScanTile - 1) / kScanTile + 1);
 }
 
 int64_t sort_blk_words(int64_t n)
