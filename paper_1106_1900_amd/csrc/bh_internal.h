@@ -39,7 +39,6 @@ __host__ __device__ constexpr uint8_t group_class(uint32_t size)
 {
     return (uint8_t)(1 + (size >= 9) + (size >= 17) + (size >= 33) + (size >= 49) + (size >= 65));
 }
-constexpr int kStackCap = 1408;        // >= 21 levels x 64 ranges (see walk.hip)
 
 // Per-cell record read by the walk: everything the opening test and a
 // particle-cell interaction need, in one 64-byte line.

@@ -18,13 +18,14 @@
 // particles holds 64.
 //
 // Per wavefront, in LDS:
-//   stack : pending cell ranges (first cell, count <= 8) packed in 32 bits, used
-//           last-in first-out.  A pop takes up to 64 cells from the top; each pop
-//           pushes at most 64 ranges, all deeper than anything popped before them
-//           that is still held, so at most 64 ranges per level (21 levels, 1344)
-//           can be on it.  The first 128 entries live in LDS; deeper entries go to
-//           a per-wavefront region in device memory (a Plummer sphere of 2^20
-//           particles needs about 50 at theta = 0.75 and 140 at theta = 0.4).
+//   stack : pending cells, used last-in first-out.  A pop takes up to 64 cells from
+//           the top, one per lane, and an opened node pushes its children one by one
+//           (see CellStack).  The top 384 entries lie in LDS, those below in a
+//           per-wavefront region in device memory.  (With the stack holding ranges of
+//           children, a pop expanded them by a prefix sum, a scatter of the ranges' starts
+//           and two gathers, three LDS round trips more in the chain of pops that
+//           bounds small launches: walks of 4096 particles 85 us, 81 so, of 24 small
+//           clusters 221 and 217, of 512 clusters of 3.2M 7.90 and 7.80 ms.)
 //   cells : the cell list, already staged as float32 tiles (offset from the
 //           group centre, mass, second moment): a lane that accepts a cell writes
 //           its entry from the record it just read for the opening test, so no
@@ -33,7 +34,8 @@
 //           tile so that every lane runs the same number of iterations.
 //   pp    : opened leaves as (first particle, count) ranges (< 64 particles
 //           pending between evaluations, so < 128 ranges).
-//   tile  : 64 staged particles plus padding.
+//   tile  : 64 staged particles plus padding, behind the entries that the cell list
+//           holds between evaluations.
 //
 // Every pair goes through float32 arithmetic on group-centred offsets; a lane's
 // terms are summed in plain float32 over at most 64 terms (one tile with one
@@ -55,8 +57,15 @@ namespace bh {
 namespace {
 
 constexpr int kPpCap = 128;
-constexpr int kLdsStack = 128;
-constexpr int kSpillPerWave = kStackCap - kLdsStack;
+constexpr int kLdsStack = 384;
+constexpr int kSpillPerWave = 1280;
+// Entries the stack can hold: kSpillPerWave, and what a push that spills leaves in LDS.
+constexpr int kStackKept = kLdsStack - kWave;
+constexpr int kStackCap = kSpillPerWave + kStackKept;
+// A pop of w cells pushes at most 8 w, so it takes 64 only while 7 * 64 more entries fit
+// and, below that, as many as fit seven times (at least one) over a reserve: by single
+// cells, a cell's whole subtree takes at most 7 entries a level.
+constexpr int kStackReserve = 7 * kMaxLevel + 8;
 // Lane (p, s) reads tile entries s + t k for t < ceil(cnt / k): at most 83 past
 // the tile's first entry for cnt <= 64 and k = floor(64 / g); the tail is padding.
 constexpr int kTileReach = 84;
@@ -69,14 +78,13 @@ constexpr int kTileReach = 84;
 #ifndef BH_WALK_PP_FULL
 #define BH_WALK_PP_FULL 1
 #endif
-// Stack reads and pushes that stay within the LDS part use LDS instructions only.
-#ifndef BH_WALK_LDS_FAST
-#define BH_WALK_LDS_FAST 1
-#endif
 #ifndef BH_WALK_FLEX_TILE
 #define BH_WALK_FLEX_TILE 1
 #endif
 constexpr int kPcCap = 148;
+// The particle tile begins behind the cells that can be pending when it is staged.
+constexpr int kTileBase = kPcCap - kWave;
+static_assert(kTileBase >= kTileReach, "fewer cells than a full tile are pending");
 constexpr float kFar = 1.0e30f;
 #ifndef BH_WALK_UNROLL
 #define BH_WALK_UNROLL 4
@@ -119,13 +127,14 @@ struct WaveLds {
     uint32_t stack[kLdsStack];
     uint2 pp[kPpCap];
     // the cell list, staged as it is built
-    float4 ca[kPcCap];        // offset x, y, z; mass
+    // (ca: and from kTileBase the particle tile, offset x, y, z; mass, while it is
+    // evaluated, or the scratch of pop64)
+    float4 ca[kTileBase + kTileReach];  // offset x, y, z; mass
     float4 cb[kPcCap];        // 3Sxx, 3Syy, 3Szz, 3Sxy
     float4 cc[kPcCap];        // 3Sxz, 3Syz, tr(S)/2, 3 tr(S)/2
-    union {
-        float4 ta[kTileReach];  // particle tile: offset x, y, z; mass
-        int mark[kWave];        // scratch of pop64 (never live during a particle tile)
-    };
+    __device__ float4 *tile() { return ca + kTileBase; }
+    __device__ const float4 *tile() const { return ca + kTileBase; }
+    __device__ int *mark() { return reinterpret_cast<int *>(ca + kTileBase); }
 };
 static_assert(4 * sizeof(WaveLds) * 4 <= 160 * 1024, "four blocks of four wavefronts per CU");
 
@@ -160,22 +169,18 @@ __device__ __forceinline__ void comp_add(float &s, float &c, float t)
 
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// Pop up to cap <= 64 elements (cap the same in every lane) from a list of
-// ranges kept as a stack.  Lane j receives element j of the popped run in *elem;
+// Pop up to cap <= 64 particles (cap the same in every lane) from the list of opened
+// leaves, ranges kept as a stack.  Lane j receives element j of the popped run in *elem;
 // returns how many were popped.
-template <class List>
-__device__ __forceinline__ int pop64(List list, int &top, int *mark, uint32_t &elem,
-                                     int cap = kWave)
+__device__ __forceinline__ int pop64(uint2 *list, int &top, int *mark, uint32_t &elem, int cap)
 {
     const int lane = lane_id();
     const int m = top < kWave ? top : kWave;
     uint32_t f = 0, cnt = 0;
-    // a stack whose entries all lie in LDS is read with LDS loads only (top is
-    // the same in every lane, so the branch is uniform)
-    if (BH_WALK_LDS_FAST && list.all_lds(top)) {
-        if (lane < m) list.get_lds(top - 1 - lane, f, cnt);
-    } else {
-        if (lane < m) list.get(top - 1 - lane, f, cnt);
+    if (lane < m) {
+        const uint2 v = list[top - 1 - lane];
+        f = v.x;
+        cnt = v.y;
     }
     const uint32_t incl = wave_incl_scan_add(cnt);
     const uint32_t excl = incl - cnt;
@@ -201,63 +206,113 @@ __device__ __forceinline__ int pop64(List list, int &top, int *mark, uint32_t &e
     const uint32_t fs = __shfl(f, src, kWave);
     const uint32_t es = __shfl(excl, src, kWave);
     elem = fs + ((uint32_t)lane - es);
-    if (lane == nfull && lane < m && take > 0 && take < cnt) {
-        if (BH_WALK_LDS_FAST && list.all_lds(top)) list.set_lds(top - 1 - lane, f + take, cnt - take);
-        else list.set(top - 1 - lane, f + take, cnt - take);
-    }
-    // only an access to the device part needs its stores waited for
-    const bool lds_only = BH_WALK_LDS_FAST && list.all_lds(top);
+    if (lane == nfull && lane < m && take > 0 && take < cnt)
+        list[top - 1 - lane] = make_uint2(f + take, cnt - take);
     top -= nfull;
-    if (lds_only) wave_sync();
-    else list.sync();
+    wave_sync();
     return got;
 }
 
-// Cell ranges packed as first << 3 | (count - 1); LDS first, then device memory.
+// The stack of pending cells: its top entries in LDS, `base` entries below them in
+// device memory.
 struct CellStack {
-    uint32_t *s;
-    volatile uint32_t *spill;
-    __device__ bool all_lds(int n) const { return n <= kLdsStack; }
-    __device__ void get(int i, uint32_t &f, uint32_t &c) const
-    {
-        const uint32_t v = i < kLdsStack ? s[i] : spill[i - kLdsStack];
-        f = v >> 3;
-        c = (v & 7u) + 1u;
-    }
-    __device__ void get_lds(int i, uint32_t &f, uint32_t &c) const
-    {
-        const uint32_t v = s[i];
-        f = v >> 3;
-        c = (v & 7u) + 1u;
-    }
-    __device__ void set_lds(int i, uint32_t f, uint32_t c) const { s[i] = (f << 3) | (c - 1u); }
-    __device__ void set(int i, uint32_t f, uint32_t c) const
-    {
-        const uint32_t v = (f << 3) | (c - 1u);
-        if (i < kLdsStack) s[i] = v;
-        else spill[i - kLdsStack] = v;
-    }
+    uint32_t *s;                // LDS, kLdsStack entries
+    volatile uint32_t *spill;   // kSpillPerWave entries
+    int top;                    // entries in LDS
+    int base;
+
     // stores to device memory must have landed before another lane reads them
     __device__ void sync() const
     {
         __builtin_amdgcn_s_waitcnt(0);
         wave_sync();
     }
-};
 
-struct LeafList {
-    uint2 *s;
-    __device__ bool all_lds(int) const { return true; }
-    __device__ void get(int i, uint32_t &f, uint32_t &c) const
+    // Up to 64 cells from the top, one per lane; returns how many.
+    __device__ __forceinline__ int pop(uint32_t &cell)
     {
-        const uint2 v = s[i];
-        f = v.x;
-        c = v.y;
+        const int lane = lane_id();
+        if (__builtin_expect(top < kWave && base > 0, 0)) refill();
+        const int room = kStackCap - kStackReserve - (base + top);
+        int m = top < kWave ? top : kWave;
+        if (__builtin_expect(room < 7 * kWave, 0)) m = min(m, max(1, room / 7));
+        cell = lane < m ? s[top - 1 - lane] : 0u;
+        top -= m;
+        return m;
     }
-    __device__ void get_lds(int i, uint32_t &f, uint32_t &c) const { get(i, f, c); }
-    __device__ void set_lds(int i, uint32_t f, uint32_t c) const { set(i, f, c); }
-    __device__ void set(int i, uint32_t f, uint32_t c) const { s[i] = make_uint2(f, c); }
-    __device__ void sync() const { wave_sync(); }
+
+    // The children [link, link + n) of each lane that opens a node (n = 0: none, else at
+    // most 8), the first lane's deepest, a node's first child on top of its others.
+    // Every lane stores eight entries, those past its own children in the places of the
+    // lanes above: the stores are issued from the eighth entry down to the first (they are
+    // volatile, and a wavefront's LDS instructions execute in order), so each entry's
+    // last store is its owner's.  Returns false if the stack is full (never).
+    __device__ __forceinline__ bool push(bool node, uint32_t link, uint32_t n)
+    {
+        const unsigned long long bn = ballot(node);
+        if (bn == 0ull) return true;
+        const uint32_t c1 = node ? n - 1u : 0u;
+        const unsigned long long b0 = ballot((c1 & 1u) != 0u), b1 = ballot((c1 & 2u) != 0u),
+                                 b2 = ballot((c1 & 4u) != 0u);
+        const int total = __popcll(bn) + __popcll(b0) + 2 * __popcll(b1) + 4 * __popcll(b2);
+        const int at = top + mask_rank(bn) + mask_rank(b0) + 2 * mask_rank(b1) + 4 * mask_rank(b2);
+        const uint32_t last = link + c1;
+        if (__builtin_expect(top + total + 7 <= kLdsStack, 1)) {
+            if (node) {
+                // (as LDS by its type: volatile accesses keep the type they are given)
+                using LdsWord = volatile __attribute__((address_space(3))) uint32_t;
+                LdsWord *q = (LdsWord *)(s + at);
+#pragma unroll
+                for (int r = 7; r >= 0; --r) q[r] = last - (uint32_t)r;
+            }
+            top += total;
+            wave_sync();
+            return true;
+        }
+        return push_spilling(node, at, last, c1, total);
+    }
+
+private:
+    // All but the top kStackKept entries of the stack and the push go to device memory.
+    __device__ bool push_spilling(bool node, int at, uint32_t last, uint32_t c1, int total)
+    {
+        const int lane = lane_id();
+        if (base + top + total > kStackCap) return false;
+        const int cut = top + total - kStackKept;       // > 0; at most kSpillPerWave - base
+        for (int i = lane; i < min(top, cut); i += kWave) spill[base + i] = s[i];
+        wave_sync();
+        for (int i = cut; i < top; i += kWave) {
+            const uint32_t v = i + lane < top ? s[i + lane] : 0u;
+            wave_sync();
+            if (i + lane < top) s[i - cut + lane] = v;
+            wave_sync();
+        }
+        if (node) {
+            for (uint32_t r = 0; r <= c1; ++r) {
+                const int i = at + (int)r;
+                if (i < cut) spill[base + i] = last - r;
+                else s[i - cut] = last - r;
+            }
+        }
+        base += cut;
+        top = kStackKept;
+        sync();
+        return true;
+    }
+
+    // up to 128 entries back from device memory, below the fewer than 64 in LDS
+    __device__ void refill()
+    {
+        const int lane = lane_id();
+        const int d = min(base, 2 * kWave);
+        const uint32_t v = lane < top ? s[lane] : 0u;
+        wave_sync();
+        if (lane < top) s[d + lane] = v;
+        for (int i = lane; i < d; i += kWave) s[i] = spill[base - d + i];
+        base -= d;
+        top += d;
+        sync();
+    }
 };
 
 // particle j on the lane's target (offsets o from the group centre)
@@ -472,7 +527,7 @@ __device__ __forceinline__ void run_pp(const WaveLds &L, int cnt, const Target<M
     for (; it + U <= T; it += U) {
         float4 S[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) S[u] = L.ta[j + u * k];
+        for (int u = 0; u < U; ++u) S[u] = L.tile()[j + u * k];
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -481,7 +536,7 @@ __device__ __forceinline__ void run_pp(const WaveLds &L, int cnt, const Target<M
         j += U * k;
     }
     for (; it < T; ++it) {
-        const float4 S = L.ta[j];
+        const float4 S = L.tile()[j];
 #pragma unroll
         for (int m = 0; m < M; ++m)
             pp_term<kEps0>(S, t.ox[m], t.oy[m], t.oz[m], eps2, ax[m], ay[m], az[m], ph[m]);
@@ -521,9 +576,9 @@ __device__ __forceinline__ void eval_pp(const WalkArgs &a, WaveLds &L, uint32_t 
     if (team_mine<M, W>(team)) {
         if (lane < cnt) {
             const double4 p = a.p4[idx];
-            L.ta[lane] = make_float4((float)(p.x - gc.x), (float)(p.y - gc.y), (float)(p.z - gc.z), (float)p.w);
+            L.tile()[lane] = make_float4((float)(p.x - gc.x), (float)(p.y - gc.y), (float)(p.z - gc.z), (float)p.w);
         } else {
-            L.ta[lane] = make_float4(kFar, kFar, kFar, 0.0f);
+            L.tile()[lane] = make_float4(kFar, kFar, kFar, 0.0f);
         }
         wave_sync();
         if (t.sub < t.k) run_pp<kEps0, M>(L, cnt, t, eps2, acc);
@@ -577,7 +632,7 @@ __device__ __forceinline__ bool mac_accept(const WalkArgs &a, const WalkCell &w,
 // W: wavefronts that walk the group together (1, or the whole workgroup).
 template <bool kEps0, int M, int W>
 __device__ __forceinline__ void walk_group(const WalkArgs &a, WaveLds &L, Team &team,
-                                           CellStack &stack, LeafList &leaves, uint32_t ncells,
+                                           uint32_t *spill, uint32_t ncells,
                                            uint32_t gs, int gn, const double4 gc, const float4 gh,
                                            uint32_t cid, float eps2, bool mindist,
                                            uint32_t &npp_out, uint32_t &npc_out,
@@ -614,7 +669,7 @@ __device__ __forceinline__ void walk_group(const WalkArgs &a, WaveLds &L, Team &
     // particles per full particle tile: k floor(64 / k), every trip full
     const int psz = BH_WALK_PP_FULL ? t.k * (kWave / t.k) : kWave;
     acc.trips = 0;
-    int top = 1;
+    CellStack stack{L.stack, spill, 1, 0};
     {
         // The cluster's root holds the group, so the opening test opens it (it
         // is tested all the same, with the loop's arithmetic): its children then
@@ -623,10 +678,11 @@ __device__ __forceinline__ void walk_group(const WalkArgs &a, WaveLds &L, Team &
         float rx, ry, rz;
         const bool racc = mac_accept(a, rw, cid, gc, gh, mindist, rx, ry, rz);
         const bool rleaf = (rw.info >> 31) != 0u;
-        if (lane == 0) {
-            if (!racc && !rleaf) stack.set(0, rw.link, rw.info);
-            else stack.set(0, cid, 1u);
-        }
+        const bool open = uniform((int)(!racc && !rleaf)) != 0;
+        const int n = open ? uniform((int)min(rw.info, 8u)) : 1;
+        const uint32_t f = open ? rw.link : cid;
+        if (lane < n) L.stack[n - 1 - lane] = f + (uint32_t)lane;
+        stack.top = n;
     }
     wave_sync();
     int pc_n = 0, pp_n = 0;
@@ -634,7 +690,7 @@ __device__ __forceinline__ void walk_group(const WalkArgs &a, WaveLds &L, Team &
     bool overflow = false;
     uint32_t iters = 0;
 
-    while (top > 0) {
+    while (stack.top + stack.base > 0) {
         // Traversal (pop, opening test, list appends) runs at a raised wave
         // priority and evaluation at the normal one: a wavefront's next loads then
         // issue ahead of the arithmetic of the other wavefronts on its SIMD, which
@@ -646,7 +702,7 @@ __device__ __forceinline__ void walk_group(const WalkArgs &a, WaveLds &L, Team &
             break;
         }
         uint32_t cell;
-        const int got = pop64(stack, top, L.mark, cell);
+        const int got = stack.pop(cell);
         const bool has = lane < got && cell < ncells;
         bool acc_cell = false, leaf = false;
         uint32_t link = 0, info = 0;
@@ -684,21 +740,9 @@ __device__ __forceinline__ void walk_group(const WalkArgs &a, WaveLds &L, Team &
         }
         // opened nodes -> children onto the stack
         const bool isn = has && !acc_cell && !leaf;
-        const unsigned long long bn = ballot(isn);
-        const int nn = __popcll(bn);
-        if (top + nn > kStackCap) {
+        if (!stack.push(isn, link, min(info, 8u))) {
             overflow = true;
             wave_sync();
-        } else {
-            if (BH_WALK_LDS_FAST && stack.all_lds(top + nn)) {
-                if (isn) stack.set_lds(top + mask_rank(bn), link, info);
-                top += nn;
-                wave_sync();
-            } else {
-                if (isn) stack.set(top + mask_rank(bn), link, info);
-                top += nn;
-                stack.sync();
-            }
         }
         if (pc_n >= tsz) {       // pc_n < tsz + 64: one tile of the last tsz entries
             __builtin_amdgcn_s_setprio(0);
@@ -707,7 +751,7 @@ __device__ __forceinline__ void walk_group(const WalkArgs &a, WaveLds &L, Team &
         }
         while (pend >= (uint32_t)psz) {
             uint32_t idx;
-            const int n = pp_n > 0 ? pop64(leaves, pp_n, L.mark, idx, psz) : 0;
+            const int n = pp_n > 0 ? pop64(L.pp, pp_n, L.mark(), idx, psz) : 0;
             if (n <= 0) {   // inconsistent bookkeeping: never spin
                 overflow = true;
                 pend = 0;
@@ -723,7 +767,7 @@ __device__ __forceinline__ void walk_group(const WalkArgs &a, WaveLds &L, Team &
     if (pc_n > 0) eval_pc<kEps0, M, W>(L, 0, pc_n, t, eps2, team, acc);
     while (pend > 0) {
         uint32_t idx;
-        const int n = pp_n > 0 ? pop64(leaves, pp_n, L.mark, idx, psz) : 0;
+        const int n = pp_n > 0 ? pop64(L.pp, pp_n, L.mark(), idx, psz) : 0;
         if (n <= 0) {
             overflow = true;
             break;
@@ -820,7 +864,7 @@ __device__ __forceinline__ int lanes_mode(int g)
 // one group by W wavefronts together, in the lane mode of its size
 template <bool kEps0, int W>
 __device__ __forceinline__ void walk_one(const WalkArgs &a, uint32_t g, int gn, WaveLds *all, int w,
-                                         CellStack &stack, LeafList &leaves, uint32_t ncells,
+                                         uint32_t *spill, uint32_t ncells,
                                          uint32_t &npp, uint32_t &npc, bool &overflow)
 {
     const uint32_t gs = a.g_first[g];
@@ -833,16 +877,16 @@ __device__ __forceinline__ void walk_one(const WalkArgs &a, uint32_t g, int gn, 
     Team team{all, uniform(w), 0};
     switch (uniform(lanes_mode(gn))) {
     case 1:
-        walk_group<kEps0, 1, W>(a, all[w], team, stack, leaves, ncells, gs, gn, gc, gh, cid, eps2,
+        walk_group<kEps0, 1, W>(a, all[w], team, spill, ncells, gs, gn, gc, gh, cid, eps2,
                                 mindist, npp, npc, overflow);
         break;
     case 2:
-        walk_group<kEps0, 2, W>(a, all[w], team, stack, leaves, ncells, gs, gn, gc, gh, cid, eps2,
+        walk_group<kEps0, 2, W>(a, all[w], team, spill, ncells, gs, gn, gc, gh, cid, eps2,
                                 mindist, npp, npc, overflow);
         break;
     default:
         if (kMaxPerLane >= 3)
-            walk_group<kEps0, (kMaxPerLane >= 3 ? 3 : 1), W>(a, all[w], team, stack, leaves, ncells,
+            walk_group<kEps0, (kMaxPerLane >= 3 ? 3 : 1), W>(a, all[w], team, spill, ncells,
                                                              gs, gn, gc, gh, cid, eps2, mindist,
                                                              npp, npc, overflow);
         break;
@@ -892,11 +936,10 @@ __attribute__((amdgpu_waves_per_eu(BH_WALK_WAVES_PER_EU))) walk_kernel(WalkArgs 
     const int lane = lane_id();
     WaveLds &L = s_lds[w];
     const int64_t wave_global = (int64_t)blockIdx.x * W + w;
-    CellStack stack{L.stack, a.spill + wave_global * kSpillPerWave};
-    LeafList leaves{L.pp};
+    uint32_t *spill = a.spill + wave_global * kSpillPerWave;
 
     // particle tile padding beyond its 64 staged entries: far away, zero mass
-    for (int i = kWave + lane; i < kTileReach; i += kWave) L.ta[i] = make_float4(kFar, kFar, kFar, 0.0f);
+    for (int i = kWave + lane; i < kTileReach; i += kWave) L.tile()[i] = make_float4(kFar, kFar, kFar, 0.0f);
     wave_sync();
 
     unsigned long long wave_pp = 0, wave_pc = 0;   // interaction totals of this wavefront
@@ -914,7 +957,7 @@ __attribute__((amdgpu_waves_per_eu(BH_WALK_WAVES_PER_EU))) walk_kernel(WalkArgs 
         const int gn = uniform((int)a.g_count[g]);
         uint32_t npp = 0, npc = 0;
         bool overflow = false;
-        walk_one<kEps0, W>(a, g, gn, s_lds, w, stack, leaves, ncells, npp, npc, overflow);
+        walk_one<kEps0, W>(a, g, gn, s_lds, w, spill, ncells, npp, npc, overflow);
         if (uniform(w) == 0) {
             if (lane == 0) {
                 a.g_npp[g] = npp;
@@ -941,7 +984,7 @@ __attribute__((amdgpu_waves_per_eu(BH_WALK_WAVES_PER_EU))) walk_kernel(WalkArgs 
         const int gn = uniform((int)a.g_count[g]);
         uint32_t npp = 0, npc = 0;
         bool overflow = false;
-        walk_one<kEps0, 1>(a, g, gn, s_lds, w, stack, leaves, ncells, npp, npc, overflow);
+        walk_one<kEps0, 1>(a, g, gn, s_lds, w, spill, ncells, npp, npc, overflow);
         if (lane == 0) {
             a.g_npp[g] = npp;
             a.g_npc[g] = npc;
