@@ -99,7 +99,6 @@ void free_buffers(bh_ctx *c)
     dfree(c->c_geo);
     dfree(c->c_box);
     dfree(c->bins);
-    dfree(c->due);
     dfree(c->pbase);
     dfree(c->walk_spill);
     dfree(c->walk_part);
@@ -188,7 +187,6 @@ hipError_t each_buffer(bh_ctx *c, const Sizes &z, F f)
     B(c->c_geo, z.cells);
     B(c->c_box, 6 * z.cells);
     B(c->bins, z.n);
-    B(c->due, z.n);
     B(c->pbase, z.n);
     B(c->walk_spill, walk_spill_words(z.spill_waves));
     B(c->walk_part, 2 * z.spill_waves);

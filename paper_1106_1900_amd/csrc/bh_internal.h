@@ -201,7 +201,6 @@ struct bh_ctx {
     double4 *c_geo = nullptr;                // geometric centre, half side (minimum-distance test)
     double *c_box = nullptr;                 // [c][6] tight box of a refitted cell: lo x, y, z, hi x, y, z
     uint8_t *bins = nullptr;                 // block time-step bin per particle (caller order)
-    uint8_t *due = nullptr;                  // particles due for forces at a substep (caller order)
     uint32_t *pbase = nullptr;               // per particle (caller order): interactions of its group
                                              // in the last walk covering it on a freshly built tree
     bool pbase_valid = false;                // pbase recorded for the current system
@@ -287,6 +286,7 @@ constexpr int64_t level_rows_words(int64_t n)
 // walk.hip
 hipError_t launch_walk(bh_ctx *c, bool timed, bool active_only = false);
 hipError_t launch_active_groups(bh_ctx *c, const uint8_t *active);   // list for active_only
+hipError_t launch_due_groups(bh_ctx *c, const uint8_t *bins, int64_t s, int levels);   // the same
 uint32_t *walk_order(bh_ctx *c, bool active);  // the groups in the order a walk takes them
 void walk_timer_harvest(bh_ctx *c, bool block);
 hipEvent_t *walk_timer_slot(bh_ctx *c);

@@ -74,31 +74,17 @@ __global__ void clear_bins_kernel(DevMisc *m)
     if (threadIdx.x == 0) m->walked_groups = 0;
 }
 
-__global__ void count_walked_kernel(DevMisc *m)
-{
-    if (threadIdx.x == 0) m->walked_groups += m->nactive;
-}
-
-// caller order: due[j] = the step of particle j ends at substep s
-__global__ void __launch_bounds__(kBlock)
-due_kernel(int64_t n, const uint8_t *__restrict__ bins, int64_t s, int levels,
-           uint8_t *__restrict__ due)
-{
-    const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (j >= n) return;
-    const int b = bins[j];
-    due[j] = (uint8_t)((s & (((int64_t)1 << (levels - b)) - 1)) == 0);
-}
-
 // half kicks v += a dt_b / 2 with dt_b = dt_max 2^-bin.  s = 0: one half kick of
 // every particle; s > 0: the particles due at substep s get two (the closing
-// kick of the step that ends and the opening kick of the next).
+// kick of the step that ends and the opening kick of the next).  Also clears the sum of
+// bases for the next evaluation (the last one's has been read by then).
 __global__ void __launch_bounds__(kBlock)
 kick_bins_kernel(int64_t n, const uint32_t *__restrict__ pid, const uint8_t *__restrict__ bins,
                  const float4 *__restrict__ acc4, double4 *__restrict__ v4, double dt_max,
-                 int levels, int64_t s)
+                 int levels, int64_t s, DevMisc *__restrict__ m)
 {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i == 0) m->base_sum = 0ull;
     if (i >= n) return;
     const int b = bins[pid[i]];
     if (s > 0 && (s & (((int64_t)1 << (levels - b)) - 1)) != 0) return;
@@ -116,50 +102,59 @@ kick_bins_kernel(int64_t n, const uint32_t *__restrict__ pid, const uint8_t *__r
     v4[i] = v;
 }
 
-// base of the particles of the walked groups (the active list, or every group):
-// their group's interaction count in the walk just finished on a fresh tree
+// The kernels below go over the walked groups, 16 lanes each (a thread per group, with its
+// chain of up to ncrit pairs of dependent loads, took 26 us for the sum of 130,000
+// particles' bases, this 6), and count them: an active list's (null: every group, not
+// counted) as those of a partial walk.
+constexpr uint32_t kSeg = 16;
+
+// base of the particles of the walked groups: their group's interaction count in the
+// walk just finished on a fresh tree
 __global__ void __launch_bounds__(kBlock)
-base_record_kernel(const DevMisc *__restrict__ m, const uint32_t *__restrict__ glist,
+base_record_kernel(DevMisc *__restrict__ m, const uint32_t *__restrict__ glist,
                    const uint32_t *__restrict__ g_first, const uint32_t *__restrict__ g_count,
                    const uint32_t *__restrict__ g_npp, const uint32_t *__restrict__ g_npc,
                    const uint32_t *__restrict__ pid, uint32_t *__restrict__ pbase)
 {
     const uint32_t ng = glist ? m->nactive : m->ngroups;
-    for (uint32_t k = blockIdx.x * kBlock + threadIdx.x; k < ng; k += gridDim.x * kBlock) {
+    const uint32_t t = blockIdx.x * kBlock + threadIdx.x, l = t % kSeg;
+    if (glist && t == 0) m->walked_groups += ng;
+    for (uint32_t k = t / kSeg; k < ng; k += gridDim.x * (kBlock / kSeg)) {
         const uint32_t g = glist ? glist[k] : k;
         const uint32_t cnt = g_npp[g] + g_npc[g];
         const uint32_t s = g_first[g], e = s + g_count[g];
-        for (uint32_t i = s; i < e; ++i) pbase[pid[i]] = cnt;
+        for (uint32_t i = s + l; i < e; i += kSeg) pbase[pid[i]] = cnt;
     }
 }
 
-__global__ void clear_base_sum_kernel(DevMisc *m)
-{
-    if (threadIdx.x == 0) m->base_sum = 0ull;
-}
-
-// summed base of the particles of the walked groups -> m->base_sum (a small
-// fixed grid: one addition per workgroup)
+// summed base of the particles of the walked groups -> m->base_sum, which is clear
+// before it (a small fixed grid: one addition per workgroup)
 __global__ void __launch_bounds__(kBlock)
-base_sum_kernel(DevMisc *__restrict__ m, const uint32_t *__restrict__ glist,
+base_sum_kernel(DevMisc *__restrict__ m, const uint32_t *__restrict__ glist, int64_t n,
                 const uint32_t *__restrict__ g_first, const uint32_t *__restrict__ g_count,
                 const uint32_t *__restrict__ pid, const uint32_t *__restrict__ pbase)
 {
     __shared__ unsigned long long s_sum[kBlock / kWave];
-    const uint32_t ng = glist ? m->nactive : m->ngroups;
+    const uint32_t t = blockIdx.x * kBlock + threadIdx.x, l = t % kSeg;
     unsigned long long sum = 0;
-    for (uint32_t k = blockIdx.x * kBlock + threadIdx.x; k < ng; k += gridDim.x * kBlock) {
-        const uint32_t g = glist ? glist[k] : k;
-        const uint32_t s = g_first[g], e = s + g_count[g];
-        for (uint32_t i = s; i < e; ++i) sum += pbase[pid[i]];
+    if (glist) {
+        const uint32_t ng = m->nactive;
+        if (t == 0) m->walked_groups += ng;
+        for (uint32_t k = t / kSeg; k < ng; k += gridDim.x * (kBlock / kSeg)) {
+            const uint32_t g = glist[k];
+            const uint32_t s = g_first[g], e = s + g_count[g];
+            for (uint32_t i = s + l; i < e; i += kSeg) sum += pbase[pid[i]];
+        }
+    } else {
+        for (int64_t j = t; j < n; j += gridDim.x * kBlock) sum += pbase[j];
     }
     for (int off = kWave / 2; off > 0; off >>= 1) sum += __shfl_down(sum, off, kWave);
     if (threadIdx.x % kWave == 0) s_sum[threadIdx.x / kWave] = sum;
     __syncthreads();
     if (threadIdx.x == 0) {
-        unsigned long long t = 0;
-        for (int i = 0; i < kBlock / kWave; ++i) t += s_sum[i];
-        if (t) atomicAdd(&m->base_sum, t);
+        unsigned long long total = 0;
+        for (int i = 0; i < kBlock / kWave; ++i) total += s_sum[i];
+        if (total) atomicAdd(&m->base_sum, total);
     }
 }
 
@@ -190,7 +185,7 @@ hipError_t enqueue_kick(bh_ctx *c, const bh_block_params *p, int64_t s)
 {
     hipLaunchKernelGGL(kick_bins_kernel, dim3(grid_for(c->n)), dim3(kBlock), 0, c->stream, c->n,
                        c->pid[c->cur], c->bins, c->acc4, c->v4[c->cur], p->dt_max,
-                       (int)p->max_level, s);
+                       (int)p->max_level, s, c->misc);
     return hipGetLastError();
 }
 
@@ -227,10 +222,8 @@ hipError_t enqueue_base_record(bh_ctx *c, bool active)
 
 hipError_t enqueue_base_sum(bh_ctx *c, bool active)
 {
-    hipLaunchKernelGGL(clear_base_sum_kernel, dim3(1), dim3(64), 0, c->stream, c->misc);
-    BH_HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL(base_sum_kernel, dim3(kBinsGrid), dim3(kBlock), 0, c->stream, c->misc,
-                       active ? c->val[1] : nullptr, c->g_first, c->g_count, c->pid[c->cur],
+                       active ? c->val[1] : nullptr, c->n, c->g_first, c->g_count, c->pid[c->cur],
                        c->pbase);
     return hipGetLastError();
 }
@@ -302,14 +295,9 @@ int bh_block_step(bh_ctx *c, const bh_block_params *p, bh_block_stats *out)
             BTRY(ctx_enqueue_refit(c));
         }
         if (!last) {
-            hipLaunchKernelGGL(due_kernel, dim3(grid_for(c->n)), dim3(kBlock), 0, c->stream, c->n,
-                               c->bins, s, B, c->due);
-            BTRY(hipGetLastError());
             BTRY(launch_rcrit(c));
-            BTRY(launch_active_groups(c, c->due));
+            BTRY(launch_due_groups(c, c->bins, s, B));
             BTRY(launch_walk(c, false, true));
-            hipLaunchKernelGGL(count_walked_kernel, dim3(1), dim3(64), 0, c->stream, c->misc);
-            BTRY(hipGetLastError());
         } else {
             BTRY(ctx_enqueue_forces(c));
         }

@@ -1124,25 +1124,45 @@ int64_t walk_grid_waves(bh_ctx *c)
 // The work counter starts at zero (set when the context's device scalars are
 // cleared and at the start of every build) and walk_sum_kernel clears it after
 // each walk; the interaction sums are written by walk_sum_kernel.
+// Which particles (in caller order) are active: those of a mask, or those whose step
+// ends at substep s of 2^levels (a particle of bin b steps every 2^(levels - b)).
+struct MaskActive {
+    const uint8_t *mask;
+    __device__ bool operator()(uint32_t j) const { return mask[j] != 0; }
+};
+
+struct DueActive {
+    const uint8_t *bins;
+    int64_t s;
+    int levels;
+    __device__ bool operator()(uint32_t j) const
+    {
+        return (s & (((int64_t)1 << (levels - (int)bins[j])) - 1)) == 0;
+    }
+};
+
 // Flags the groups that hold at least one active particle with their size class
 // (flags[g]; zero for the others and for g >= ngroups up to n, so that the flags
-// can be compacted over n entries).
+// can be compacted over n entries).  16 lanes per group: a thread per group, with its
+// chain of up to ncrit pairs of dependent loads, took 18 us at 130,000 particles and
+// 21 at 2^20, this 5 and 9.
+template <class Active>
 __global__ void __launch_bounds__(256)
 mark_active_groups_kernel(const DevMisc *__restrict__ m, const uint32_t *__restrict__ g_first,
                           const uint32_t *__restrict__ g_count, const uint32_t *__restrict__ pid,
-                          const uint8_t *__restrict__ active, int64_t n, uint8_t *__restrict__ flags)
+                          Active active, int64_t n, uint8_t *__restrict__ flags)
 {
+    constexpr uint32_t kSeg = 16;
     const uint32_t ngroups = m->ngroups;
-    for (int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x; g < n;
-         g += (int64_t)gridDim.x * 256) {
-        uint8_t f = 0;
-        if (g < (int64_t)ngroups) {
-            const uint32_t s = g_first[g], e = s + g_count[g];
-            for (uint32_t i = s; i < e && !f; ++i) f = active[pid[i]] != 0;
-            if (f) f = group_class(e - s);
-        }
-        flags[g] = f;
+    const uint32_t t = blockIdx.x * 256 + threadIdx.x, l = t % kSeg, step = gridDim.x * (256 / kSeg);
+    for (uint32_t g = t / kSeg; g < ngroups; g += step) {
+        const uint32_t s = g_first[g], cnt = g_count[g];
+        bool any = false;
+        for (uint32_t i = l; i < cnt; i += kSeg) any |= active(pid[s + i]);
+        const uint32_t seg = (uint32_t)(ballot(any) >> (lane_id() & ~(int)(kSeg - 1))) & 0xffffu;
+        if (l == 0) flags[g] = seg ? group_class(cnt) : (uint8_t)0;
     }
+    for (int64_t g = (int64_t)ngroups + t; g < n; g += (int64_t)gridDim.x * 256) flags[g] = 0;
 }
 
 // the order in which a walk takes the tree's groups, or those of the last active
@@ -1153,16 +1173,27 @@ uint32_t *walk_order(bh_ctx *c, bool active)
     return active ? p + c->n : p;
 }
 
-hipError_t launch_active_groups(bh_ctx *c, const uint8_t *active)
+template <class Active>
+static hipError_t active_groups(bh_ctx *c, const Active &active)
 {
     int g = (int)((c->n + 255) / 256);
     if (g > 2048) g = 2048;
-    hipLaunchKernelGGL(mark_active_groups_kernel, dim3(g), dim3(256), 0, c->stream, c->misc,
+    hipLaunchKernelGGL(mark_active_groups_kernel<Active>, dim3(g), dim3(256), 0, c->stream, c->misc,
                        c->g_first, c->g_count, c->pid[c->cur], active, c->n, c->gflag);
     BH_LAUNCH_CHECK();
     // the active group list goes to the sort's spare value buffer
     return compact_flags(c, c->gflag, c->n, c->val[1], &c->misc->nactive, walk_order(c, true),
                          c->misc->upto_active, false);
+}
+
+hipError_t launch_active_groups(bh_ctx *c, const uint8_t *active)
+{
+    return active_groups(c, MaskActive{active});
+}
+
+hipError_t launch_due_groups(bh_ctx *c, const uint8_t *bins, int64_t s, int levels)
+{
+    return active_groups(c, DueActive{bins, s, levels});
 }
 
 // Wavefronts of a workgroup: four, or eight for systems whose few hundred groups
