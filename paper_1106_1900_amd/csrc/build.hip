@@ -134,13 +134,11 @@ bbox_kernel(Src src, const Chunk *__restrict__ chunks, double *__restrict__ part
     box_partial(lo, hi, bad, part, m);
 }
 
-// One block per cluster: reduce its chunk partials; cube side = largest extent
-// (1 if all extents vanish); scale = 2^20 / side.
-__global__ void __launch_bounds__(kBlock)
-domain_kernel(const double *__restrict__ part, const DevCluster *__restrict__ clus,
-              DevDomain *__restrict__ dom)
+// The cluster's cube by a workgroup, from its chunks' partials: side = largest extent (1 if
+// all extents vanish); scale = 2^20 / side.  In thread 0's return value.
+__device__ __forceinline__ DevDomain cluster_domain(const double *__restrict__ part,
+                                                    const DevCluster &cl)
 {
-    const DevCluster &cl = clus[blockIdx.x];
     const uint32_t b0 = cl.chunk0, b1 = cl.chunk0 + cl.nchunk;
     double v[6] = {INFINITY, INFINITY, INFINITY, -INFINITY, -INFINITY, -INFINITY};
     for (uint32_t b = b0 + threadIdx.x; b < b1; b += kBlock) {
@@ -163,29 +161,40 @@ domain_kernel(const double *__restrict__ part, const DevCluster *__restrict__ cl
         if (l == 0) s_v[k][w] = a;
     }
     __syncthreads();
-    if (threadIdx.x != 0) return;
-    double lo[3], hi[3];
-    for (int k = 0; k < 3; ++k) {
-        lo[k] = s_v[k][0];
-        hi[k] = s_v[3 + k][0];
-        for (int i = 1; i < kBlock / kWave; ++i) {
-            lo[k] = fmin(lo[k], s_v[k][i]);
-            hi[k] = fmax(hi[k], s_v[3 + k][i]);
-        }
-    }
-    DevDomain d;
+    DevDomain d{};
+    if (threadIdx.x != 0) return d;
     double side = 0.0;
     for (int k = 0; k < 3; ++k) {
-        d.lo[k] = lo[k];
-        d.hi[k] = hi[k];
-        const double e = hi[k] - lo[k];
+        d.lo[k] = s_v[k][0];
+        d.hi[k] = s_v[3 + k][0];
+        for (int i = 1; i < kBlock / kWave; ++i) {
+            d.lo[k] = fmin(d.lo[k], s_v[k][i]);
+            d.hi[k] = fmax(d.hi[k], s_v[3 + k][i]);
+        }
+        const double e = d.hi[k] - d.lo[k];
         if (e > side) side = e;
     }
     if (side == 0.0) side = 1.0;
     d.L = side;
     d.scale = 1048576.0 / side;
-    dom[blockIdx.x] = d;
+    return d;
 }
+
+// One block per cluster (clusters of so many chunks that the keys kernel does not
+// reduce the partials itself).
+__global__ void __launch_bounds__(kBlock)
+domain_kernel(const double *__restrict__ part, const DevCluster *__restrict__ clus,
+              DevDomain *__restrict__ dom)
+{
+    const DevDomain d = cluster_domain(part, clus[blockIdx.x]);
+    if (threadIdx.x == 0) dom[blockIdx.x] = d;
+}
+
+// Chunks of a cluster up to which every workgroup of the keys kernel reduces the
+// partials (up to four 48-byte records a thread, from the L2) and no launch does so
+// before it: keys 6.3 -> 8.7 us at 4096 particles, 13.1 -> 14.8 at 2^20 and no change
+// at 2^22, where the launch of their own took 4.4 us and more.
+constexpr int64_t kKeysChunks = 4 * kBlock;
 
 // Keys of the particles, written in caller order: the pair of the particle at
 // position i goes to slot pid[i] (its caller index; pid == null: the positions
@@ -196,15 +205,29 @@ domain_kernel(const double *__restrict__ part, const DevCluster *__restrict__ cl
 // by pid itself).  With sub > 0 (buckets per chunk) the clusters of several chunks
 // also get their candidate splitters: kSortOver keys per bucket, one from each of
 // as many equal stretches of the cluster, its place drawn from a hash of its number.
+// With part the cluster's cube is reduced here (and written by its first workgroup).
 template <typename Src>
 __global__ void __launch_bounds__(kBlock)
-keys_kernel(Src src, const Chunk *__restrict__ chunks, const DevDomain *__restrict__ dom,
+keys_kernel(Src src, const Chunk *__restrict__ chunks, const double *__restrict__ part,
+            DevDomain *__restrict__ dom,
             const uint32_t *__restrict__ pid, uint32_t n, uint64_t *__restrict__ key,
             uint32_t *__restrict__ val, uint32_t held, const DevCluster *__restrict__ clus,
             uint32_t sub, uint64_t *__restrict__ cand, DevMisc *m)
 {
     const Chunk ch = chunks[blockIdx.x];
-    const DevDomain &cl = dom[ch.cluster];
+    __shared__ DevDomain s_dom;
+    if (part) {
+        const DevCluster &dc = clus[ch.cluster];
+        const DevDomain d = cluster_domain(part, dc);
+        if (threadIdx.x == 0) {
+            s_dom = d;
+            if (blockIdx.x == dc.chunk0) dom[ch.cluster] = d;
+        }
+    } else if (threadIdx.x == 0) {
+        s_dom = dom[ch.cluster];
+    }
+    __syncthreads();
+    const DevDomain &cl = s_dom;
     uint32_t ncand = 0, stretch = 1, first = 0;
     if (sub) {
         const DevCluster &dc = clus[ch.cluster];
@@ -431,6 +454,11 @@ __device__ void level_finalize(const uint32_t *__restrict__ tot, DevMisc *m, int
     m->nleaves = __hip_atomic_load(&tot[kLevels], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Up to this many tiles the workgroups of emit_cells_kernel add the rows up themselves, a
+// thread per level with all its loads at once, and no launch scans them first: 4096
+// particles 9.1 us for scan and cells, 5.9 + 9.5 with two launches.
+constexpr int kEmitTiles = 16;
+
 // one block per level (and one for the leaf row): exclusive scan of the row's
 // block counts in place; the last block to finish derives the level offsets
 constexpr int kScanLevelsBlock = 1024;
@@ -481,9 +509,10 @@ struct Ranks {
 
 // Only the levels lo..hi (wavefront-uniform) get their ranks; the starts of every
 // level are counted, as other wavefronts of the block may need them.
+// base[lev]: the starts of level lev before this block; off[lev]: the level's offset.
 __device__ __forceinline__ void level_ranks(bool valid, uint8_t sp, uint8_t lm,
-                                            const uint32_t *__restrict__ blk_scanned, int nblk,
-                                            const DevMisc *__restrict__ m, uint32_t (*s_wc)[kLevels],
+                                            const uint32_t *base, const uint32_t *off0,
+                                            uint32_t (*s_wc)[kLevels],
                                             int lo, int hi, Ranks &r,
                                             unsigned long long (&balls)[kLevels])
 {
@@ -498,10 +527,10 @@ __device__ __forceinline__ void level_ranks(bool valid, uint8_t sp, uint8_t lm,
 #pragma unroll
     for (int lev = 0; lev < kLevels; ++lev) {
         if (lev < lo || lev > hi) continue;
-        uint32_t off = blk_scanned[(int64_t)lev * nblk + blockIdx.x];
+        uint32_t off = base[lev];
         for (int ww = 0; ww < w; ++ww) off += s_wc[ww][lev];
         uint32_t incl = off + (uint32_t)__popcll(balls[lev] & le);
-        r.anc[lev] = m->level_offset[lev] + incl - 1u;
+        r.anc[lev] = off0[lev] + incl - 1u;
     }
 }
 
@@ -520,10 +549,12 @@ struct RunEdge {
 // the same or a shallower level, or lies beyond the cluster) writes the cell's
 // end; the last particle of a node also writes one past the node's last child
 // (the child holding that particle).  Counts follow as end - first.
+// kScan: the rows of blk are not scanned yet, and this kernel does it (see kEmitTiles).
+template <bool kScan>
 __global__ void __launch_bounds__(kTreeTile)
 emit_cells_kernel(const uint8_t *__restrict__ split, const uint8_t *__restrict__ lam, int64_t n,
-                  const uint32_t *__restrict__ blk_scanned, int nblk, const DevMisc *__restrict__ m,
-                  uint32_t *__restrict__ c_first, uint8_t *__restrict__ c_level,
+                  const uint32_t *__restrict__ blk, int nblk, DevMisc *__restrict__ m,
+                  int64_t cap_c, uint32_t *__restrict__ c_first, uint8_t *__restrict__ c_level,
                   uint8_t *__restrict__ c_leaf, uint32_t *__restrict__ c_parent,
                   uint32_t *__restrict__ c_child, uint32_t *__restrict__ c_end,
                   uint32_t *__restrict__ c_cend, const uint32_t *__restrict__ pcl,
@@ -531,6 +562,7 @@ emit_cells_kernel(const uint8_t *__restrict__ split, const uint8_t *__restrict__
 {
     __shared__ uint32_t s_wc[kTreeTile / kWave][kLevels];
     __shared__ int s_edge[kTreeTile / kWave];
+    __shared__ uint32_t s_base[kLevels], s_off[kLevels + 1], s_tot[kLevels + 1];
     const int64_t i = (int64_t)blockIdx.x * kTreeTile + threadIdx.x;
     const bool valid = i < n;
     const uint8_t sp = valid ? split[i] : (uint8_t)255;
@@ -548,9 +580,53 @@ emit_cells_kernel(const uint8_t *__restrict__ split, const uint8_t *__restrict__
         const int k = wave_min_i32(((int)sp << 8) | (int)threadIdx.x);
         if (threadIdx.x % kWave == 0) s_edge[threadIdx.x / kWave] = k;
     }
+    if (kScan) {
+        if (threadIdx.x < kLevels + 1) {
+            const uint32_t *row = blk + (int64_t)threadIdx.x * nblk;
+            uint32_t v[kEmitTiles], before = 0, total = 0;
+#pragma unroll
+            for (int q = 0; q < kEmitTiles; ++q) v[q] = q < nblk ? row[q] : 0u;
+#pragma unroll
+            for (int q = 0; q < kEmitTiles; ++q) {
+                if (q < (int)blockIdx.x) before += v[q];
+                total += v[q];
+            }
+            s_tot[threadIdx.x] = total;
+            if (threadIdx.x < kLevels) s_base[threadIdx.x] = before;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            uint32_t off = 0, depth = 0;
+            for (int l = 0; l < kLevels; ++l) {
+                s_off[l] = off;
+                if (s_tot[l]) depth = (uint32_t)l;
+                off += s_tot[l];
+            }
+            // cannot happen for a consistent tree; keeps every later write in bounds
+            const bool over = (int64_t)off > cap_c;
+            s_off[kLevels] = over ? 0u : off;
+            if (blockIdx.x == 0) {
+                for (int l = 0; l < kLevels; ++l) {
+                    m->level_offset[l] = s_off[l];
+                    m->level_count[l] = over ? 0u : s_tot[l];
+                }
+                m->level_offset[kLevels] = m->ncells = s_off[kLevels];
+                m->depth = depth;
+                m->nleaves = s_tot[kLevels];
+                if (over) m->nonfinite |= 4u;
+            }
+        }
+    } else {
+        if (threadIdx.x < kLevels) {
+            s_base[threadIdx.x] = blk[(int64_t)threadIdx.x * nblk + blockIdx.x];
+            s_off[threadIdx.x] = m->level_offset[threadIdx.x];
+        }
+        if (threadIdx.x == 0) s_off[kLevels] = m->ncells;
+    }
+    // (the barrier of level_ranks comes before the first use of s_base and s_off)
     Ranks r;
     unsigned long long balls[kLevels];
-    level_ranks(valid, sp, lm, blk_scanned, nblk, m, s_wc, lo, hi, r, balls);
+    level_ranks(valid, sp, lm, s_base, s_off, s_wc, lo, hi, r, balls);
     if (edge) {
         int k = s_edge[0];
         for (int w = 1; w < kTreeTile / kWave; ++w) k = min(k, s_edge[w]);
@@ -561,13 +637,13 @@ emit_cells_kernel(const uint8_t *__restrict__ split, const uint8_t *__restrict__
             const unsigned long long lt = (1ull << (threadIdx.x % kWave)) - 1ull;
 #pragma unroll
             for (int lev = 0; lev < kLevels; ++lev) {
-                uint32_t c = blk_scanned[(int64_t)lev * nblk + blockIdx.x];
+                uint32_t c = s_base[lev];
                 for (int w = 0; w < (int)threadIdx.x / kWave; ++w) c += s_wc[w][lev];
                 e.c[lev] = c + (uint32_t)__popcll(balls[lev] & lt);
             }
         }
     }
-    const uint32_t ncells = m->ncells;
+    const uint32_t ncells = s_off[kLevels];
     if (!valid || ncells == 0) return;
     const uint32_t cluster = sp <= lm ? pcl[i] : 0u;
 #pragma unroll
@@ -1391,6 +1467,10 @@ hipError_t launch_cluster_ids(bh_ctx *c)
     return hipSuccess;
 }
 
+// whether the keys kernel makes the clusters' cubes
+static bool domain_with_keys(const bh_ctx *c) { return c->max_cluster <= kKeysChunks * kChunk; }
+
+// the chunks' boxes and, unless the keys kernel makes them, the clusters' cubes
 hipError_t launch_domain(bh_ctx *c, const double *pos_aos)
 {
     if (!pos_aos && c->box_ready) {
@@ -1403,9 +1483,11 @@ hipError_t launch_domain(bh_ctx *c, const double *pos_aos)
         hipLaunchKernelGGL(bbox_kernel<P4Src>, dim3((unsigned)c->nchunks), dim3(kBlock), 0,
                            c->stream, P4Src{c->p4[c->cur]}, c->chunks, c->bb_part, c->misc);
     BH_LAUNCH_CHECK();
-    hipLaunchKernelGGL(domain_kernel, dim3((unsigned)c->K), dim3(kBlock), 0, c->stream, c->bb_part,
-                       c->clus, c->dom);
-    BH_LAUNCH_CHECK();
+    if (!domain_with_keys(c)) {
+        hipLaunchKernelGGL(domain_kernel, dim3((unsigned)c->K), dim3(kBlock), 0, c->stream,
+                           c->bb_part, c->clus, c->dom);
+        BH_LAUNCH_CHECK();
+    }
     return hipSuccess;
 }
 
@@ -1413,15 +1495,16 @@ hipError_t launch_keys(bh_ctx *c, const double *pos_aos)
 {
     const uint32_t sub = c->nbuckets > 0 ? (uint32_t)sort_sub(c) : 0u;
     const uint32_t held = sort_sub(c) > 0 ? 1u : 0u;
+    const double *part = domain_with_keys(c) ? c->bb_part : nullptr;
     if (pos_aos)
         hipLaunchKernelGGL(keys_kernel<AosSrc>, dim3((unsigned)c->nchunks), dim3(kBlock), 0,
-                           c->stream, AosSrc{pos_aos}, c->chunks, c->dom, nullptr, (uint32_t)c->n,
+                           c->stream, AosSrc{pos_aos}, c->chunks, part, c->dom, nullptr, (uint32_t)c->n,
                            c->key[0], c->val[0], 0u, c->clus, sub, sort_candidates(c), c->misc);
     else
         // a rebuild: held-order pairs for the bucket sort, caller-order pairs for
         // the radix sort
         hipLaunchKernelGGL(keys_kernel<P4Src>, dim3((unsigned)c->nchunks), dim3(kBlock), 0,
-                           c->stream, P4Src{c->p4[c->cur]}, c->chunks, c->dom, c->pid[c->cur],
+                           c->stream, P4Src{c->p4[c->cur]}, c->chunks, part, c->dom, c->pid[c->cur],
                            (uint32_t)c->n, c->key[0], c->val[0], held, c->clus, sub,
                            sort_candidates(c), c->misc);
     BH_LAUNCH_CHECK();
@@ -1475,14 +1558,16 @@ hipError_t launch_tree(bh_ctx *c)
     hipLaunchKernelGGL(split_leaf_kernel, dim3(nblk), dim3(kTreeTile), lds, c->stream, c->key[0],
                        c->pcl, n, H, c->clus, c->split, c->lam, c->gflag, blk, nblk, c->misc);
     BH_LAUNCH_CHECK();
-    hipLaunchKernelGGL(scan_levels_kernel, dim3(kLevels + 1), dim3(kScanLevelsBlock), 0, c->stream,
-                       blk, nblk, tot,
-                       c->misc, c->cap_c);
-    BH_LAUNCH_CHECK();
-    hipLaunchKernelGGL(emit_cells_kernel, dim3(nblk), dim3(kTreeTile), 0, c->stream, c->split,
-                       c->lam, n, blk, nblk, c->misc, c->c_first, c->c_level, c->c_leaf,
-                       c->c_parent, c->c_child, c->c_end, c->c_nchild, c->pcl, c->c_cl,
-                       run_edges(c));
+    const bool scan = nblk <= kEmitTiles;
+    if (!scan) {
+        hipLaunchKernelGGL(scan_levels_kernel, dim3(kLevels + 1), dim3(kScanLevelsBlock), 0,
+                           c->stream, blk, nblk, tot, c->misc, c->cap_c);
+        BH_LAUNCH_CHECK();
+    }
+    hipLaunchKernelGGL(scan ? emit_cells_kernel<true> : emit_cells_kernel<false>, dim3(nblk),
+                       dim3(kTreeTile), 0, c->stream, c->split, c->lam, n, blk, nblk, c->misc,
+                       c->cap_c, c->c_first, c->c_level, c->c_leaf, c->c_parent, c->c_child,
+                       c->c_end, c->c_nchild, c->pcl, c->c_cl, run_edges(c));
     BH_LAUNCH_CHECK();
     int g = grid_for(c->cap_c, kBlock);
     if (g > kFixedGrid) g = kFixedGrid;

@@ -224,7 +224,7 @@ copy_pairs_kernel(const uint64_t *__restrict__ kin, const uint32_t *__restrict__
 // generic exclusive scan of u32 / compaction of u8 flags
 
 constexpr int kScanThreads = 256;
-constexpr int kScanItems = 8;
+constexpr int kScanItems = 8;       // flags of a thread: one 64-bit load
 constexpr int kScanTile = kScanThreads * kScanItems;
 static_assert(kScanTile < 1 << 16, "two counts of a block in one word");
 
@@ -241,6 +241,20 @@ __device__ __forceinline__ void add_flag(ClassCounts &c, uint8_t f)
         c.w[q] += f == 2 * q + 1 ? 1u : (f == 2 * q + 2 ? 1u << 16 : 0u);
 }
 
+// a thread's flags of a tile (0 past the end); the tiles begin at multiples of 8
+__device__ __forceinline__ void load_flags(const uint8_t *__restrict__ in, int64_t base, int64_t n,
+                                           uint8_t *f)
+{
+    if (base + kScanItems <= n) {
+        const uint64_t v = *reinterpret_cast<const uint64_t *>(in + base);
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) f[k] = (uint8_t)(v >> (8 * k));
+    } else {
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) f[k] = base + k < n ? in[base + k] : (uint8_t)0;
+    }
+}
+
 __device__ __forceinline__ uint32_t class_count(const ClassCounts &c, int k)
 {
     return (k & 1) ? c.w[k / 2] >> 16 : c.w[k / 2] & 0xffffu;
@@ -253,9 +267,10 @@ scan_reduce_kernel(const uint8_t *__restrict__ in, int64_t n, ClassCounts *__res
     __shared__ uint32_t s_tmp[4];
     const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
     ClassCounts c{};
+    uint8_t f[kScanItems];
+    load_flags(in, base, n, f);
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k)
-        if (base + k < n) add_flag(c, in[base + k]);
+    for (int k = 0; k < kScanItems; ++k) add_flag(c, f[k]);
     ClassCounts sum;
 #pragma unroll
     for (int q = 0; q < kClassWords; ++q) block_excl_scan_256(c.w[q], s_tmp, &sum.w[q]);
@@ -265,8 +280,9 @@ scan_reduce_kernel(const uint8_t *__restrict__ in, int64_t n, ClassCounts *__res
 // Writes the positions of set flags, in order, to idx[0..count), and the same items
 // (their positions, or with rank their places in idx) to order: the highest class
 // first, each class in order.  Each block adds up the class counts of the blocks
-// before it and of all blocks (part, from scan_reduce_kernel); the last block also
-// writes count and upto[c] = the items of class c + 1 or more.
+// before it and of all blocks (part, from scan_reduce_kernel; null for a few blocks,
+// which count the flags themselves); the last block also writes count and upto[c] = the
+// items of class c + 1 or more.
 __global__ void __launch_bounds__(kScanThreads)
 compact_down_kernel(const uint8_t *__restrict__ flags, int64_t n,
                     const ClassCounts *__restrict__ part, uint32_t *__restrict__ idx,
@@ -277,13 +293,29 @@ compact_down_kernel(const uint8_t *__restrict__ flags, int64_t n,
     __shared__ uint32_t s_sum[2][kGroupClasses];    // before this block, in all blocks
     if (threadIdx.x < 2 * kGroupClasses) (&s_sum[0][0])[threadIdx.x] = 0;
     uint32_t before[kGroupClasses] = {}, all[kGroupClasses] = {};
-    for (uint32_t b = threadIdx.x; b < gridDim.x; b += kScanThreads) {
-        const ClassCounts c = part[b];
+    if (part) {
+        for (uint32_t b = threadIdx.x; b < gridDim.x; b += kScanThreads) {
+            const ClassCounts c = part[b];
 #pragma unroll
-        for (int k = 0; k < kGroupClasses; ++k) {
-            const uint32_t v = class_count(c, k);
-            all[k] += v;
-            if (b < blockIdx.x) before[k] += v;
+            for (int k = 0; k < kGroupClasses; ++k) {
+                const uint32_t v = class_count(c, k);
+                all[k] += v;
+                if (b < blockIdx.x) before[k] += v;
+            }
+        }
+    } else {
+        for (uint32_t b = 0; b < gridDim.x; ++b) {
+            uint8_t f[kScanItems];
+            load_flags(flags, (int64_t)b * kScanTile + (int64_t)threadIdx.x * kScanItems, n, f);
+            ClassCounts c{};
+#pragma unroll
+            for (int k = 0; k < kScanItems; ++k) add_flag(c, f[k]);
+#pragma unroll
+            for (int k = 0; k < kGroupClasses; ++k) {
+                const uint32_t v = class_count(c, k);
+                all[k] += v;
+                if (b < blockIdx.x) before[k] += v;
+            }
         }
     }
     __syncthreads();
@@ -298,12 +330,10 @@ compact_down_kernel(const uint8_t *__restrict__ flags, int64_t n,
     const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
     uint8_t f[kScanItems];
     ClassCounts c{}, x;
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        f[k] = base + k < n ? flags[base + k] : (uint8_t)0;
-        add_flag(c, f[k]);
-    }
     uint32_t sum;
+    load_flags(flags, base, n, f);
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) add_flag(c, f[k]);
 #pragma unroll
     for (int q = 0; q < kClassWords; ++q) x.w[q] = block_excl_scan_256(c.w[q], s_tmp, &sum);
     __syncthreads();
@@ -1051,16 +1081,23 @@ hipError_t sort_pairs(bh_ctx *c, bool held)
     return hipSuccess;
 }
 
+// Blocks that count all flags themselves rather than take a launch to count them first
+// (4.5 us; each block then reads the others' flags, 8 bytes a thread and block).
+constexpr int kCountBlocks = 4;
+
 hipError_t compact_flags(bh_ctx *c, const uint8_t *flags, int64_t n, uint32_t *idx,
                          uint32_t *count, uint32_t *order, uint32_t *upto, bool rank)
 {
     // one block at least, so that the counts are written for n = 0 too
     const int nblk = std::max(1, (int)((n + kScanTile - 1) / kScanTile));
     // behind the level rows (which the cells are made from) and before the runs' edges
-    ClassCounts *part = reinterpret_cast<ClassCounts *>(c->blk + level_rows_words(c->n));
-    hipLaunchKernelGGL(scan_reduce_kernel, dim3(nblk), dim3(kScanThreads), 0, c->stream, flags, n,
-                       part);
-    BH_LAUNCH_CHECK();
+    ClassCounts *part = nullptr;
+    if (nblk > kCountBlocks) {
+        part = reinterpret_cast<ClassCounts *>(c->blk + level_rows_words(c->n));
+        hipLaunchKernelGGL(scan_reduce_kernel, dim3(nblk), dim3(kScanThreads), 0, c->stream, flags, n,
+                           part);
+        BH_LAUNCH_CHECK();
+    }
     hipLaunchKernelGGL(compact_down_kernel, dim3(nblk), dim3(kScanThreads), 0, c->stream, flags, n,
                        part, idx, count, order, upto, rank);
     BH_LAUNCH_CHECK();
