@@ -1599,7 +1599,7 @@ hipError_t launch_group_boxes(bh_ctx *c)
 // workgroup each, and then across those.  The time is the chain of levels, not the
 // bytes (a level's barrier, its LDS or L2 reads, two divisions): leaves and nodes in one
 // launch per level or group of levels took 28, 89, 110 and 412 us at 1500, 240K and 2^20
-// particles and for 512 clusters of 3.2M, this 19, 43, 96 and 354.  Units beginning
+// particles and for 512 clusters of 1024 to 65,536, this 19, 43, 96 and 354.  Units beginning
 // at any multiple of their size, not between large cells: 19, 61, 103, 386.
 // Up to 4096 particles one workgroup's four runs hold the whole system (whole builds:
 // 140 us at 1500 particles and 162 at 4000; four workgroups and one across them 150 and

@@ -25,7 +25,7 @@
 //           children, a pop expanded them by a prefix sum, a scatter of the ranges' starts
 //           and two gathers, three LDS round trips more in the chain of pops that
 //           bounds small launches: walks of 4096 particles 85 us, 81 so, of 24 small
-//           clusters 221 and 217, of 512 clusters of 3.2M 7.90 and 7.80 ms.)
+//           clusters 221 and 217, of 512 clusters 7.90 and 7.80 ms.)
 //   cells : the cell list, already staged as float32 tiles (offset from the
 //           group centre, mass, second moment): a lane that accepts a cell writes
 //           its entry from the record it just read for the opening test, so no
@@ -1059,7 +1059,7 @@ __global__ void __launch_bounds__(256)
 scatter_kernel(int64_t n, const float4 *__restrict__ acc4, const uint32_t *__restrict__ pid,
                float *__restrict__ acc, float *__restrict__ pot)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t i = xcd_block() * 256 + threadIdx.x;
     if (i >= n) return;
     const float4 v = acc4[i];
     const int64_t o = pid[i];
@@ -1263,7 +1263,7 @@ hipError_t launch_zero_acc(bh_ctx *c)
 hipError_t launch_scatter(bh_ctx *c, float *acc, float *pot)
 {
     if (!acc && !pot) return hipSuccess;
-    hipLaunchKernelGGL(scatter_kernel, dim3((unsigned)((c->n + 255) / 256)), dim3(256), 0, c->stream,
+    hipLaunchKernelGGL(scatter_kernel, dim3(xcd_blocks(c->n, 256)), dim3(256), 0, c->stream,
                        c->n, c->acc4, c->pid[c->cur], acc, pot);
     BH_LAUNCH_CHECK();
     return hipSuccess;
