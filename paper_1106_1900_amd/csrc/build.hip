@@ -456,7 +456,7 @@ __device__ void level_finalize(const uint32_t *__restrict__ tot, DevMisc *m, int
 
 // Up to this many tiles the workgroups of emit_cells_kernel add the rows up themselves, a
 // thread per level with all its loads at once, and no launch scans them first: 4096
-// particles 9.1 us for scan and cells, 5.9 + 9.5 with two launches.
+// particles 7.4 us for scan and cells, 5.9 + 9.5 with two launches.
 constexpr int kEmitTiles = 16;
 
 // one block per level (and one for the leaf row): exclusive scan of the row's
@@ -513,10 +513,10 @@ struct Ranks {
 __device__ __forceinline__ void level_ranks(bool valid, uint8_t sp, uint8_t lm,
                                             const uint32_t *base, const uint32_t *off0,
                                             uint32_t (*s_wc)[kLevels],
-                                            int lo, int hi, Ranks &r,
-                                            unsigned long long (&balls)[kLevels])
+                                            int lo, int hi, Ranks &r)
 {
     const int t = threadIdx.x, w = t / kWave, l = t % kWave;
+    unsigned long long balls[kLevels];
 #pragma unroll
     for (int lev = 0; lev < kLevels; ++lev) {
         balls[lev] = ballot(valid && sp <= lev && lev <= lm);
@@ -625,21 +625,27 @@ emit_cells_kernel(const uint8_t *__restrict__ split, const uint8_t *__restrict__
     }
     // (the barrier of level_ranks comes before the first use of s_base and s_off)
     Ranks r;
-    unsigned long long balls[kLevels];
-    level_ranks(valid, sp, lm, s_base, s_off, s_wc, lo, hi, r, balls);
+    level_ranks(valid, sp, lm, s_base, s_off, s_wc, lo, hi, r);
     if (edge) {
         int k = s_edge[0];
         for (int w = 1; w < kTreeTile / kWave; ++w) k = min(k, s_edge[w]);
-        if ((k & 255) == (int)threadIdx.x) {
+        const int t0 = k & 255, l = threadIdx.x % kWave;
+        if ((int)threadIdx.x / kWave == t0 / kWave) {       // its wavefront: a lane per level
             RunEdge &e = edges[blockIdx.x / kRunTiles];
-            e.x = (uint32_t)i;
-            e.split = sp;
-            const unsigned long long lt = (1ull << (threadIdx.x % kWave)) - 1ull;
-#pragma unroll
+            const unsigned long long lt = (1ull << (t0 % kWave)) - 1ull;
+            uint32_t c = 0;
             for (int lev = 0; lev < kLevels; ++lev) {
-                uint32_t c = s_base[lev];
-                for (int w = 0; w < (int)threadIdx.x / kWave; ++w) c += s_wc[w][lev];
-                e.c[lev] = c + (uint32_t)__popcll(balls[lev] & lt);
+                const unsigned long long b = ballot(valid && sp <= lev && lev <= lm);
+                if (l == lev) c = (uint32_t)__popcll(b & lt);
+            }
+            if (l < kLevels) {
+                c += s_base[l];
+                for (int w = 0; w < t0 / kWave; ++w) c += s_wc[w][l];
+                e.c[l] = c;
+            }
+            if (l == 0) {
+                e.x = blockIdx.x * kTreeTile + (uint32_t)t0;
+                e.split = (uint32_t)(k >> 8);
             }
         }
     }
@@ -760,7 +766,7 @@ group_boxes_kernel(const uint32_t *__restrict__ g_first, const DevMisc *__restri
 // ---------------------------------------------------------------------------
 // moments: float64 monopole and second moment, level by level from the deepest
 // (Sect. 3.2): a leaf from its particles, a node from its children (one level
-// deeper, finished by the previous launch), both in array order.
+// deeper, finished before it), both in array order.
 
 // Where the opening radii and walk records go, and what they are computed from.
 struct RecOut {

@@ -375,7 +375,7 @@ compact_down_kernel(const uint8_t *__restrict__ flags, int64_t n,
 // A bucket is a workgroup's LDS sort, so few pairs make little work but the same
 // chain of passes: sub is chosen so that the device has a workgroup per CU or two
 // (sort_sub).  Loads took eight radix passes (24 launches) before: 100,003
-// particles 138 -> 62 us of kernels, 4096 125 -> 30 us.
+// particles 138 -> 39 us of kernels, 4096 125 -> 23 us.
 
 constexpr uint32_t kOver = kSortOver;   // candidate keys per bucket
 constexpr int kWindow = 40;             // bits a bucket's passes cover
