@@ -46,7 +46,7 @@ FLOPS_PP = 20
 FLOPS_PC = 57
 PAPER_TRAVERSE_RATE = 2.8e6          # particles/s, tree traverse only, GTX480 (Sect. 4.1)
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "walk_plummer_1m_traffic.json")
-WALK_SRC = os.path.join(ROOT, "paper_1106_1900_amd", "csrc", "walk.hip")
+WALK_SRC = [os.path.join(ROOT, "paper_1106_1900_amd", "csrc", f) for f in ("walk.hip", "walk_stack.h")]
 
 
 _T0 = time.perf_counter()
@@ -59,8 +59,10 @@ def log(*a):
 def walk_source_hash():
     """Fingerprint of the walk kernel: its source and its compile flags."""
     from paper_1106_1900_amd.build import SOURCE_FLAGS
-    with open(WALK_SRC, "rb") as f:
-        src = f.read()
+    src = b""
+    for path in WALK_SRC:
+        with open(path, "rb") as f:
+            src += f.read()
     return hashlib.sha256(src + b"\0" + " ".join(SOURCE_FLAGS.get("walk.hip", ())).encode()).hexdigest()[:16]
 
 
