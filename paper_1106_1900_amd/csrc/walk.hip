@@ -20,7 +20,7 @@
 // Per wavefront, in LDS:
 //   stack : pending cells, used last-in first-out.  A pop takes up to 64 cells from
 //           the top, one per lane, and an opened node pushes its children one by one
-//           (see CellStack).  The top 384 entries lie in LDS, those below in a
+//           (see CellStack).  The top 384 lie in LDS, those below, as ranges, in a
 //           per-wavefront region in device memory.  (With the stack holding ranges of
 //           children, a pop expanded them by a prefix sum, a scatter of the ranges' starts
 //           and two gathers, three LDS round trips more in the chain of pops that

@@ -8,21 +8,31 @@ namespace {
 
 constexpr int kLdsStack = 384;
 constexpr int kSpillPerWave = 1280;
-// Entries the stack can hold: kSpillPerWave, and what a push that spills leaves in LDS.
+// Cells and ranges the stack can hold: kSpillPerWave, and what a push that spills leaves
+// in LDS.
 constexpr int kStackKept = kLdsStack - kWave;
 constexpr int kStackCap = kSpillPerWave + kStackKept;
 // A pop of w cells pushes at most 8 w, so it takes 64 only while 7 * 64 more entries fit
 // and, below that, as many as fit seven times (at least one) over a reserve: by single
-// cells, a cell's whole subtree takes at most 7 entries a level.
-constexpr int kStackReserve = 7 * kMaxLevel + 8;
+// cells, a cell's whole subtree takes at most 7 entries a level, and so do those of a
+// range that comes back to an empty LDS part.
+constexpr int kStackReserve = 7 * kMaxLevel + 16;
+constexpr int kRefill = 256;    // most cells that come back at once
 
-// The stack of pending cells: its top entries in LDS, `base` entries below them in
-// device memory.
+// The stack of pending cells: the top ones in LDS, a word each, those below in device
+// memory as ranges of up to 8 consecutive cells (a node's children, mostly), packed in
+// 32 bits as first cell << 3 | count - 1.  So the stack is about as deep as its nodes are
+// many, and pops take 64 cells wherever 64 are pending but in trees that none of the
+// models comes near (20 levels of nodes, all with eight children and all opened).  With a
+// word per cell in device memory too, walks that open many cells filled it and popped
+// fewer and fewer cells at a time: 200,000 particles of a Hernquist sphere at theta = 0.2
+// by the minimum distance (leaves of 8) 21.6 ms, 7.9 so, 262,144 of a galaxy at 0.2 8.7
+// ms, 5.2 so.
 struct CellStack {
     uint32_t *s;                // LDS, kLdsStack entries
     volatile uint32_t *spill;   // kSpillPerWave entries
     int top;                    // entries in LDS
-    int base;
+    int base;                   // ranges in device memory
 
     // stores to device memory must have landed before another lane reads them
     __device__ void sync() const
@@ -80,13 +90,29 @@ struct CellStack {
     }
 
 private:
-    // All but the top kStackKept entries of the stack and the push go to device memory.
+    // All but the top kStackKept cells of the stack and the push go to device memory.
     __device__ bool push_spilling(bool node, int at, uint32_t last, uint32_t c1, int total)
     {
         const int lane = lane_id();
         if (base + top + total > kStackCap) return false;
         const int cut = top + total - kStackKept;       // > 0; at most kSpillPerWave - base
-        for (int i = lane; i < min(top, cut); i += kWave) spill[base + i] = s[i];
+        // the cells held, 64 at a time, by runs of descending numbers, eight to a range
+        const int old = min(top, cut);
+        for (int i = 0; i < old; i += kWave) {
+            const int m = min(old - i, kWave);
+            const uint32_t v = lane < m ? s[i + lane] : 0u;
+            const uint32_t below = lane > 0 && lane < m ? s[i + lane - 1] : 0u;
+            const unsigned long long runs = ballot(lane < m && (lane == 0 || v + 1u != below));
+            const int in_run = __builtin_clzll((runs << (kWave - 1 - lane)) | 1ull);
+            const bool first = lane < m && (in_run & 7) == 0;
+            const unsigned long long b = ballot(first);
+            if (first) {
+                const unsigned long long next = (b >> lane) >> 1;
+                const uint32_t c = next ? (uint32_t)__builtin_ctzll(next) : (uint32_t)(m - 1 - lane);
+                spill[base + mask_rank(b)] = ((v - c) << 3) | c;
+            }
+            base += __popcll(b);
+        }
         wave_sync();
         for (int i = cut; i < top; i += kWave) {
             const uint32_t v = i + lane < top ? s[i + lane] : 0u;
@@ -94,30 +120,39 @@ private:
             if (i + lane < top) s[i - cut + lane] = v;
             wave_sync();
         }
-        if (node) {
-            for (uint32_t r = 0; r <= c1; ++r) {
-                const int i = at + (int)r;
-                if (i < cut) spill[base + i] = last - r;
-                else s[i - cut] = last - r;
-            }
-        }
-        base += cut;
+        // the push: of a node's children those below the cut, then the others
+        const int deep = node ? min((int)c1 + 1, max(0, cut - at)) : 0;
+        const unsigned long long b = ballot(deep > 0);
+        if (deep > 0) spill[base + mask_rank(b)] = ((last - (uint32_t)(deep - 1)) << 3) | (uint32_t)(deep - 1);
+        base += __popcll(b);
+        if (node)
+            for (int r = deep; r <= (int)c1; ++r) s[at + r - cut] = last - (uint32_t)r;
         top = kStackKept;
         sync();
         return true;
     }
 
-    // up to 128 entries back from device memory, below the fewer than 64 in LDS
+    // Ranges back from device memory, below the fewer than 64 cells in LDS: up to kRefill
+    // cells, and no more than leave the next pop its full width.
     __device__ void refill()
     {
         const int lane = lane_id();
-        const int d = min(base, 2 * kWave);
+        const int m = min(base, kWave);
+        const uint32_t w = lane < m ? spill[base - 1 - lane] : 0u;
+        const int n = lane < m ? (int)(w & 7u) + 1 : 0;
+        const int incl = (int)wave_incl_scan_add((uint32_t)n);
+        const int room = kStackCap - kStackReserve - 7 * kWave - (base + top);
+        const bool take = lane < m && incl <= kRefill && (incl - (lane + 1) <= room || (lane == 0 && top == 0));
+        const int words = __popcll(ballot(take));       // the first lanes
+        if (words == 0) return;
+        const int cells = (int)lane_value((uint32_t)incl, words - 1);
         const uint32_t v = lane < top ? s[lane] : 0u;
         wave_sync();
-        if (lane < top) s[d + lane] = v;
-        for (int i = lane; i < d; i += kWave) s[i] = spill[base - d + i];
-        base -= d;
-        top += d;
+        if (lane < top) s[cells + lane] = v;
+        if (take)
+            for (int r = 0; r < n; ++r) s[cells - incl + r] = (w >> 3) + (uint32_t)(n - 1 - r);
+        base -= words;
+        top += cells;
         sync();
     }
 };

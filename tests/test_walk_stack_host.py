@@ -32,3 +32,19 @@ def test_nodes_without_children_push_nothing(host):
 @pytest.mark.parametrize("children,levels", [(1, 60), (2, 12), (5, 6), (8, 5)])
 def test_every_cell_is_popped_once(host, children, levels):
     host("tree", children, levels)
+
+
+@pytest.mark.parametrize("children,levels", [(3, 9), (5, 7), (8, 6)])
+def test_pops_keep_their_width(host, children, levels):
+    # more cells pending than the LDS part holds, all of them opened
+    most, spilled, narrowest = host("tree", children, levels)
+    assert most > 384 and spilled > 0
+    assert narrowest == 64
+
+
+def test_stack_never_fills(host):
+    # 20 levels of nodes with eight children each: the words in device memory run out, and
+    # pops narrow instead
+    most, spilled, narrowest = host("deep", 20)
+    assert most > 5000 and 800 < spilled <= 1280
+    assert narrowest < 64

@@ -8,8 +8,8 @@
 //   walk_stack_host deep P           nodes of eight children down to level 20 for P pops,
 //                                    then leaves: the stack holds them, each popped once
 //
-// Prints "ok" and the deepest stack, its words in device memory and the narrowest pop taken
-// while 64 cells were pending; exits with 1 and a message otherwise.
+// Prints "ok" and the most cells pending, the most words in device memory and the narrowest
+// pop while 64 cells were pending; exits with 1 and a message otherwise.
 #include <ucontext.h>
 
 #include <algorithm>
@@ -135,7 +135,9 @@ struct Node {
 };
 std::vector<Node> cells;
 std::vector<uint8_t> popped;
-int deepest = 0, spilled = 0, narrowest = kWave;
+int64_t pending = 0;                // cells
+int64_t deepest = 0;
+int spilled = 0, narrowest = kWave;
 
 void check()
 {
@@ -148,7 +150,7 @@ void check()
             emu::die("lanes hold different stacks");
     const int top = lane_stack[0].top, base = lane_stack[0].base;
     if (top < 0 || top > kLdsStack || base < 0 || base > kSpillPerWave) emu::die("stack out of range");
-    deepest = max(deepest, top + base);
+    deepest = max(deepest, pending);
     spilled = max(spilled, base);
 }
 
@@ -157,12 +159,12 @@ void start(uint32_t root)
     for (int l = 0; l < kWave; ++l)
         lane_stack[l] = CellStack{lds.data() + kPad, mem.data() + kPad, 1, 0};
     lds[kPad] = root;
+    pending = 1;
 }
 
 // the cells of a pop, one per lane
 int pop(uint32_t *cell)
 {
-    const int pending = lane_stack[0].top + lane_stack[0].base;
     int got[kWave];
     emu::run([&] {
         const int l = lane_id();
@@ -170,9 +172,10 @@ int pop(uint32_t *cell)
     });
     for (int l = 1; l < kWave; ++l)
         if (got[l] != got[0]) emu::die("lanes popped different numbers");
-    check();
     if (got[0] < 1 || got[0] > kWave) emu::die("nothing popped from a stack that holds cells");
     if (pending >= kWave) narrowest = min(narrowest, got[0]);
+    pending -= got[0];
+    check();
     return got[0];
 }
 
@@ -184,6 +187,8 @@ void push(const bool *node, const Node *v)
         if (!lane_stack[l].push(node[l], v[l].link, v[l].n)) full = true;
     });
     if (full) emu::die("stack full");
+    for (int l = 0; l < kWave; ++l)
+        if (node[l]) pending += min(v[l].n, 8u);
     check();
 }
 
@@ -191,7 +196,7 @@ void push(const bool *node, const Node *v)
 template <class Open>
 void walk(Open open)
 {
-    while (lane_stack[0].top + lane_stack[0].base > 0) {
+    while (pending > 0) {
         uint32_t cell[kWave];
         const int got = pop(cell);
         bool node[kWave] = {};
@@ -204,6 +209,7 @@ void walk(Open open)
         }
         push(node, v);
     }
+    if (lane_stack[0].top || lane_stack[0].base) emu::die("entries left");
     for (uint8_t p : popped)
         if (p != 1) emu::die("a cell lost");
 }
@@ -224,6 +230,7 @@ void childless()
         start(0);
         for (int i = 0; i < fill; ++i) lds[kPad + i] = 1000000u + (uint32_t)i;
         for (int l = 0; l < kWave; ++l) lane_stack[l].top = fill;
+        pending = fill;
         bool node[kWave];
         Node v[kWave];
         int want = fill;
@@ -240,7 +247,7 @@ void childless()
             for (uint32_t c = 0; node[l] && c < v[l].n; ++c) kids.push_back(v[l].link + c);
         exp.insert(exp.begin(), kids.begin(), kids.end());
         if ((int)exp.size() != want) emu::die("model");
-        while (lane_stack[0].top + lane_stack[0].base > 0) {
+        while (pending > 0) {
             uint32_t cell[kWave];
             const int n = pop(cell);
             got.insert(got.end(), cell, cell + n);
@@ -289,6 +296,6 @@ int main(int argc, char **argv)
     else if (argc > 3 && !strcmp(argv[1], "tree")) tree((uint32_t)atoi(argv[2]), atoi(argv[3]));
     else if (argc > 2 && !strcmp(argv[1], "deep")) deep(atoi(argv[2]));
     else return 2;
-    printf("ok %d %d %d\n", deepest, spilled, narrowest);
+    printf("ok %d %d %d\n", (int)deepest, spilled, narrowest);
     return 0;
 }
