@@ -46,7 +46,7 @@ FLOPS_PP = 20
 FLOPS_PC = 57
 PAPER_TRAVERSE_RATE = 2.8e6          # particles/s, tree traverse only, GTX480 (Sect. 4.1)
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "walk_plummer_1m_traffic.json")
-WALK_SRC = [os.path.join(ROOT, "paper_1106_1900_amd", "csrc", f) for f in ("walk.hip", "walk_stack.h")]
+WALK_SRC = [os.path.join(ROOT, "paper_1106_1900_amd", "csrc", f) for f in ("walk.hip", "walk_stack.h", "walk_handout.h")]
 
 
 _T0 = time.perf_counter()

@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "../../include/bh.h"
+#include "walk_handout.h"
 
 namespace bh {
 
@@ -33,13 +34,6 @@ constexpr int kTreeTile = 256;
 // kMaxGroup particles: a lane carries up to two (or three) of them.
 constexpr int kWalkWaves = 4;
 constexpr int kMaxGroup = 128;
-// Size classes 1..6 of the groups: a walk takes the large ones first.
-constexpr int kGroupClasses = 6;
-__host__ __device__ constexpr uint8_t group_class(uint32_t size)
-{
-    return (uint8_t)(1 + (size >= 9) + (size >= 17) + (size >= 33) + (size >= 49) + (size >= 65));
-}
-
 // Per-cell record read by the walk: everything the opening test and a
 // particle-cell interaction need, in one 64-byte line.
 struct alignas(64) WalkCell {

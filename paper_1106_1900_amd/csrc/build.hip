@@ -707,16 +707,17 @@ cell_finish_kernel(DevMisc *__restrict__ m, const uint32_t *__restrict__ pcl,
         const uint32_t cnt = e - f;
         c_count[c] = cnt;
         c_nchild[c] = nc;
-        const uint32_t ncrit = clus[pcl[f]].ncrit;
+        const DevCluster &cl = clus[pcl[f]];
+        const uint32_t ncrit = cl.ncrit, cn = cl.n;
         bool top = c_level[c] == 0;
         if (!top) {
             const uint32_t p = c_parent[c];
             top = p < ncells && c_end[p] - c_first[p] > ncrit;
         }
-        if (cnt <= ncrit && top) gflag[f] = group_class(cnt);
+        if (cnt <= ncrit && top) gflag[f] = group_class(cnt, cn);
         if (leaf && cnt > ncrit)
             for (uint32_t o = 0; o < cnt; o += ncrit)
-                gflag[f + o] = group_class(min(ncrit, cnt - o));
+                gflag[f + o] = group_class(min(ncrit, cnt - o), cn);
     }
 }
 

@@ -44,7 +44,7 @@
 // accumulation).
 //
 // Groups are handed out by size class and in Morton order within a class (see
-// team_groups), from one device-wide counter after each wavefront's first, so at any
+// walk_handout.h), from one device-wide counter after each wavefront's first, so at any
 // moment all 256 CUs work on neighbouring groups whose interaction lists overlap:
 // the active part of the tree stays small and shared in the Infinity Cache.
 // (Splitting the groups into per-XCD ranges, so that each XCD's L2 sees one
@@ -782,33 +782,6 @@ __device__ __forceinline__ void walk_one(const WalkArgs &a, uint32_t g, int gn, 
     }
 }
 
-// The hand-out.  A group's time grows with its size, up to several times the mean, so
-// a launch ends with wavefronts idle behind the last large groups: all of a small
-// launch, a tenth of one of 55,000 groups.  With V wavefronts in the grid (4096: all
-// that are resident at once), by the number of groups:
-//   up to 24 V    the groups are taken by descending size class (group_class), each
-//                 class in Morton order.  2^20 particles (55,388 groups): 1.69 ->
-//                 1.56 ms; 240,002: 0.38 -> 0.29 ms.  Above, Morton order alone: the
-//                 groups at work then span less of the tree, and 470,942 groups of a
-//                 batch took 7.97 ms so, 8.6 ms by size (the rest of a launch is
-//                 long enough to hide its end);
-//   up to 4 V     the groups of 65 and more (two or three particles per lane) are
-//                 walked first, each by a whole workgroup (a team, see Team): 7210
-//                 groups of up to 128: 0.40 -> 0.23 ms;
-//   up to 1.5 V   so are those of 49 and more: 5376 groups 0.60 -> 0.54 ms (with 33
-//                 and more 0.57: each of a team's wavefronts walks the whole tree);
-//   up to 0.625 V so are those of 33 and more: 1891 groups 0.164 -> 0.106 ms;
-//   up to 0.25 V  all groups are: 926 groups 0.145 -> 0.10 ms.
-// The results do not depend on it bit for bit.
-__device__ __forceinline__ uint32_t team_groups(const WalkArgs &a, uint32_t ngroups, uint32_t waves)
-{
-    if (4 * (uint64_t)ngroups <= waves) return ngroups;
-    if (8 * (uint64_t)ngroups <= 5 * (uint64_t)waves) return a.upto[group_class(33) - 1];
-    if (2 * (uint64_t)ngroups <= 3 * (uint64_t)waves) return a.upto[group_class(49) - 1];
-    if (ngroups <= 4 * (uint64_t)waves) return a.upto[group_class(65) - 1];
-    return 0;
-}
-
 // kEps0: some cluster of the launch has zero softening, so pairs at zero
 // distance (a particle with itself) must be skipped explicitly.
 // W: wavefronts per workgroup.  The index of the wavefront is left in a vector register:
@@ -834,9 +807,10 @@ __attribute__((amdgpu_waves_per_eu(BH_WALK_WAVES_PER_EU))) walk_kernel(WalkArgs 
     unsigned long long wave_pp = 0, wave_pc = 0;   // interaction totals of this wavefront
     bool wave_overflow = false;
     const uint32_t grid_waves = gridDim.x * W;
-    const bool sorted = ngroups <= 24 * (uint64_t)grid_waves;
+    const bool sorted = by_class(ngroups, grid_waves);
     // groups at the front of the order that whole workgroups take
-    const uint32_t teams = readfirst(team_groups(a, ngroups, grid_waves));
+    const int team = team_class(ngroups, grid_waves);
+    const uint32_t teams = team ? readfirst(a.upto[team - 1]) : 0u;
     __shared__ uint32_t s_next[2];
     int turn = 0;
     for (uint32_t slot = blockIdx.x; slot < teams;) {
@@ -863,9 +837,12 @@ __attribute__((amdgpu_waves_per_eu(BH_WALK_WAVES_PER_EU))) walk_kernel(WalkArgs 
     // the workgroups without a team group start with the next slots
     const uint32_t busy = teams < gridDim.x ? teams : gridDim.x;
     const uint32_t waves = teams + (gridDim.x - busy) * W;
-    for (uint32_t slot = blockIdx.x < busy
-                             ? next_slot(a, waves)
-                             : teams + (blockIdx.x - busy) * W + readfirst((uint32_t)w);
+    // (side by side in a workgroup, or in wide ones, where a launch may have fewer groups than
+    // wavefronts, each workgroup's first before any workgroup's second: 1900 groups of up
+    // to 16 122 -> 114 us)
+    const uint32_t idle = gridDim.x - busy, mine = blockIdx.x - busy, wave = readfirst((uint32_t)w);
+    for (uint32_t slot = blockIdx.x < busy ? next_slot(a, waves)
+                                           : teams + (W > kWalkWaves ? wave * idle + mine : mine * W + wave);
          slot < ngroups; slot = next_slot(a, waves)) {
         uint32_t g = slot;
         if (sorted) g = readfirst(a.order[slot]);
@@ -1039,6 +1016,7 @@ template <class Active>
 __global__ void __launch_bounds__(256)
 mark_active_groups_kernel(const DevMisc *__restrict__ m, const uint32_t *__restrict__ g_first,
                           const uint32_t *__restrict__ g_count, const uint32_t *__restrict__ pid,
+                          const uint32_t *__restrict__ pcl, const DevCluster *__restrict__ clus,
                           Active active, int64_t n, uint8_t *__restrict__ flags)
 {
     constexpr uint32_t kSeg = 16;
@@ -1049,7 +1027,7 @@ mark_active_groups_kernel(const DevMisc *__restrict__ m, const uint32_t *__restr
         bool any = false;
         for (uint32_t i = l; i < cnt; i += kSeg) any |= active(pid[s + i]);
         const uint32_t seg = (uint32_t)(ballot(any) >> (lane_id() & ~(int)(kSeg - 1))) & 0xffffu;
-        if (l == 0) flags[g] = seg ? group_class(cnt) : (uint8_t)0;
+        if (l == 0) flags[g] = seg ? group_class(cnt, clus[pcl[s]].n) : (uint8_t)0;
     }
     for (int64_t g = (int64_t)ngroups + t; g < n; g += (int64_t)gridDim.x * 256) flags[g] = 0;
 }
@@ -1068,7 +1046,7 @@ static hipError_t active_groups(bh_ctx *c, const Active &active)
     int g = (int)((c->n + 255) / 256);
     if (g > 2048) g = 2048;
     hipLaunchKernelGGL(mark_active_groups_kernel<Active>, dim3(g), dim3(256), 0, c->stream, c->misc,
-                       c->g_first, c->g_count, c->pid[c->cur], active, c->n, c->gflag);
+                       c->g_first, c->g_count, c->pid[c->cur], c->pcl, c->clus, active, c->n, c->gflag);
     BH_LAUNCH_CHECK();
     // the active group list goes to the sort's spare value buffer
     return compact_flags(c, c->gflag, c->n, c->val[1], &c->misc->nactive, walk_order(c, true),

@@ -1,0 +1,62 @@
+// walk_handout.h - the order in which a walk takes the groups, and which of them whole
+// workgroups take.  Rules only, for the device and for tests on the host.
+//
+// A group's time grows with its size, up to several times the mean, so a launch ends with
+// wavefronts idle behind the last large groups: all of a small launch, a tenth of one of
+// 55,000 groups.  Against that groups are taken by descending size class, and in
+// launches of few groups the large ones are walked first, each by a whole workgroup (a
+// team, see walk.hip).  The results do not depend on it bit for bit.
+#pragma once
+
+#include <cstdint>
+
+namespace bh {
+
+// Size classes 1..6 of the groups.
+constexpr int kGroupClasses = 6;
+__host__ __device__ constexpr uint8_t group_class(uint32_t size)
+{
+    return (uint8_t)(1 + (size >= 9) + (size >= 17) + (size >= 33) + (size >= 49) + (size >= 65));
+}
+
+// The class of a group in a cluster of n particles.  A small cluster's groups have short
+// lists whatever their size, so they come last and no team walks them: 500 clusters of
+// 64 particles take 38 us with a wavefront per group, 60 by teams, 100 of 100 42 and 52, 30
+// of 300 50 and 52; 10 of 500 57 and 51.
+constexpr uint32_t kSmallCluster = 320;
+__host__ __device__ constexpr uint8_t group_class(uint32_t size, uint32_t n)
+{
+    return n <= kSmallCluster ? (uint8_t)1 : group_class(size);
+}
+
+// Whether the groups are taken by class (each class in Morton order), of `waves`
+// wavefronts in the grid (V; 4096: all that are resident at once).  2^20 particles
+// (55,388 groups): 1.69 -> 1.56 ms; 240,002: 0.38 -> 0.29 ms.  Above, Morton order alone:
+// the groups at work then span less of the tree, and 470,942 groups of a batch took 7.97 ms
+// so, 8.6 ms by size (the rest of a launch is long enough to hide its end).
+__host__ __device__ constexpr bool by_class(uint64_t ngroups, uint64_t waves)
+{
+    return ngroups <= 24 * waves;
+}
+
+// The least class of the groups that teams walk (0: no teams), by the number of groups:
+//   up to 4 V     those of 65 and more (two or three particles per lane): 7210 groups of
+//                 up to 128: 0.40 -> 0.23 ms;
+//   up to 1.5 V   so are those of 49 and more: 5376 groups 0.60 -> 0.54 ms (with 33
+//                 and more 0.57: each of a team's wavefronts walks the whole tree);
+//   up to 0.625 V so are those of 33 and more: 1891 groups 0.164 -> 0.106 ms;
+//   up to 0.25 V  those of 17 and more: 522 groups of up to 64 411 -> 154 us (with 33 and
+//                 more 233), 485 of up to 32 133 -> 96.  Not the smaller ones, whose lists
+//                 many lanes share already: 4096 particles in groups of up to 16 (1400
+//                 of them at most) 91 us so, 79 by teams from 9 up and 151 by teams
+//                 from 1 up, 1000 groups of one particle 32 and 93.
+__host__ __device__ constexpr int team_class(uint64_t ngroups, uint64_t waves)
+{
+    if (4 * ngroups <= waves) return group_class(17);
+    if (8 * ngroups <= 5 * waves) return group_class(33);
+    if (2 * ngroups <= 3 * waves) return group_class(49);
+    if (ngroups <= 4 * waves) return group_class(65);
+    return 0;
+}
+
+}  // namespace bh
