@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "../../include/bh.h"
+#include "sort_rules.h"
 #include "walk_handout.h"
 
 namespace bh {

@@ -3,7 +3,8 @@
 //
 // Clusters of up to 2^20 particles are sorted through buckets (below): one pass
 // that places the pairs by key range and one workgroup per bucket.  A batch with a
-// larger cluster takes a stable LSD radix sort.  The paper splits one bit per pass;
+// larger cluster, or of thousands of tiny ones (sort_rules.h), takes a stable LSD radix
+// sort.  The paper splits one bit per pass;
 // here each pass places an 8-bit digit, which is the same stable partition done for
 // 256 buckets at once: 8 passes over the 60-bit keys.  For a batch of clusters,
 // further stable passes on the cluster of each element follow, so the keys end up
@@ -378,6 +379,7 @@ compact_down_kernel(const uint8_t *__restrict__ flags, int64_t n,
 // particles 138 -> 39 us of kernels, 4096 125 -> 23 us.
 
 constexpr uint32_t kOver = kSortOver;   // candidate keys per bucket
+static_assert(kRadix == kSortBuckets && kChunk == kSortChunk, "the rule's figures");
 constexpr int kWindow = 40;             // bits a bucket's passes cover
 constexpr uint32_t kShortRun = 16;      // pairs agreeing in them that one thread orders
 constexpr int kPassThreads = 512;       // workgroup of the bucket pass: one chunk
@@ -1020,18 +1022,7 @@ hipError_t radix_sort_pairs(bh_ctx *c)
 
 }  // namespace
 
-// Buckets per chunk of the clusters with several chunks (0: radix sort).  256 buckets
-// per cluster are the limit of the pass, so larger clusters have larger buckets.
-//   up to 2^18 particles in all: 1024 pairs a bucket.  A bucket's sort is a chain of
-//   passes with little work in each, and 256 workgroups fill the device;
-//   clusters of up to 2^19: 2048 pairs, two workgroups to a CU;
-//   clusters of up to 2^20: 4096 pairs.
-int sort_sub(const bh_ctx *c)
-{
-    if (c->max_cluster > (int64_t)kRadix * kChunk) return 0;
-    if (c->n <= (int64_t)kRadix * kChunk / 4) return 4;
-    return c->max_cluster <= (int64_t)kRadix * kChunk / 2 ? 2 : 1;
-}
+int sort_sub(const bh_ctx *c) { return sort_rule(c->n, c->nchunks, c->max_cluster); }
 
 // candidates and splitters, in the cells' centres of mass (written again after the sort)
 uint64_t *sort_candidates(bh_ctx *c)
