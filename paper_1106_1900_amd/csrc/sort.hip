@@ -278,23 +278,71 @@ scan_reduce_kernel(const uint8_t *__restrict__ in, int64_t n, ClassCounts *__res
     if (threadIdx.x == 0) part[blockIdx.x] = sum;
 }
 
+// pre[c nblk + b]: the flags of class c + 1 in the blocks before b; pre[classes nblk + c]: in
+// all blocks.  One workgroup per class.
+constexpr int kClassScanThreads = 1024;
+
+__global__ void __launch_bounds__(kClassScanThreads)
+class_scan_kernel(const ClassCounts *__restrict__ part, uint32_t nblk, uint32_t *__restrict__ pre)
+{
+    constexpr int kWaves = kClassScanThreads / kWave, kItems = 8;
+    __shared__ uint32_t s_tmp[kWaves];
+    const int cls = (int)blockIdx.x, t = threadIdx.x, w = t / kWave;
+    uint32_t *row = pre + (int64_t)cls * nblk;
+    uint32_t run = 0;
+    for (uint32_t b0 = 0; b0 < nblk; b0 += kClassScanThreads * kItems) {
+        const uint32_t b = b0 + (uint32_t)t * kItems;
+        uint32_t v[kItems], mine = 0;
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) v[k] = b + k < nblk ? class_count(part[b + k], cls) : 0u;
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) mine += v[k];
+        const uint32_t inc = wave_incl_scan_add(mine);
+        if (t % kWave == kWave - 1) s_tmp[w] = inc;
+        __syncthreads();
+        uint32_t off = 0, sum = 0;
+#pragma unroll
+        for (int i = 0; i < kWaves; ++i) {
+            const uint32_t x = s_tmp[i];
+            if (i < w) off += x;
+            sum += x;
+        }
+        __syncthreads();
+        uint32_t at = run + off + inc - mine;
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) {
+            if (b + k < nblk) row[b + k] = at;
+            at += v[k];
+        }
+        run += sum;
+    }
+    if (t == 0) pre[(int64_t)kGroupClasses * nblk + cls] = run;
+}
+
 // Writes the positions of set flags, in order, to idx[0..count), and the same items
 // (their positions, or with rank their places in idx) to order: the highest class
-// first, each class in order.  Each block adds up the class counts of the blocks
-// before it and of all blocks (part, from scan_reduce_kernel; null for a few blocks,
-// which count the flags themselves); the last block also writes count and upto[c] = the
-// items of class c + 1 or more.
+// first, each class in order.  The class counts of the blocks before a block and of all
+// blocks come from class_scan_kernel (pre), or, where that is null, each block adds up the
+// blocks' counts (part, from scan_reduce_kernel) or, where that is null too, counts the
+// flags itself.  The last block also writes count and upto[c] = the items of class c + 1
+// or more.
 __global__ void __launch_bounds__(kScanThreads)
 compact_down_kernel(const uint8_t *__restrict__ flags, int64_t n,
-                    const ClassCounts *__restrict__ part, uint32_t *__restrict__ idx,
-                    uint32_t *__restrict__ count, uint32_t *__restrict__ order,
-                    uint32_t *__restrict__ upto, bool rank)
+                    const ClassCounts *__restrict__ part, const uint32_t *__restrict__ pre,
+                    uint32_t *__restrict__ idx, uint32_t *__restrict__ count,
+                    uint32_t *__restrict__ order, uint32_t *__restrict__ upto, bool rank)
 {
     __shared__ uint32_t s_tmp[4];
     __shared__ uint32_t s_sum[2][kGroupClasses];    // before this block, in all blocks
-    if (threadIdx.x < 2 * kGroupClasses) (&s_sum[0][0])[threadIdx.x] = 0;
+    if (threadIdx.x < 2 * kGroupClasses) {
+        const uint32_t k = threadIdx.x % kGroupClasses;
+        const uint32_t at = threadIdx.x < kGroupClasses ? k * gridDim.x + blockIdx.x
+                                                        : kGroupClasses * gridDim.x + k;
+        (&s_sum[0][0])[threadIdx.x] = pre ? pre[at] : 0u;
+    }
     uint32_t before[kGroupClasses] = {}, all[kGroupClasses] = {};
-    if (part) {
+    if (pre) {
+    } else if (part) {
         for (uint32_t b = threadIdx.x; b < gridDim.x; b += kScanThreads) {
             const ClassCounts c = part[b];
 #pragma unroll
@@ -1076,6 +1124,12 @@ hipError_t sort_pairs(bh_ctx *c, bool held)
 // (4.5 us; each block then reads the others' flags, 8 bytes a thread and block).
 constexpr int kCountBlocks = 4;
 
+// Blocks above which their counts are scanned by a launch of their own: otherwise every
+// block reads all the others' (12 bytes each), which is quadratic.  Tree and groups of 10^8
+// particles 5.92 -> 4.53 ms, of 2^24 837 -> 799 us, of 2^23 420 -> 413; 2^22 the same, and
+// below the launch costs 2 us more than it saves.
+constexpr int kScanBlocks = 2048;
+
 hipError_t compact_flags(bh_ctx *c, const uint8_t *flags, int64_t n, uint32_t *idx,
                          uint32_t *count, uint32_t *order, uint32_t *upto, bool rank)
 {
@@ -1083,21 +1137,28 @@ hipError_t compact_flags(bh_ctx *c, const uint8_t *flags, int64_t n, uint32_t *i
     const int nblk = std::max(1, (int)((n + kScanTile - 1) / kScanTile));
     // behind the level rows (which the cells are made from) and before the runs' edges
     ClassCounts *part = nullptr;
+    uint32_t *pre = nullptr;
     if (nblk > kCountBlocks) {
         part = reinterpret_cast<ClassCounts *>(c->blk + level_rows_words(c->n));
         hipLaunchKernelGGL(scan_reduce_kernel, dim3(nblk), dim3(kScanThreads), 0, c->stream, flags, n,
                            part);
         BH_LAUNCH_CHECK();
     }
+    if (nblk > kScanBlocks) {
+        pre = reinterpret_cast<uint32_t *>(part + nblk);
+        hipLaunchKernelGGL(class_scan_kernel, dim3(kGroupClasses), dim3(kClassScanThreads), 0,
+                           c->stream, part, (uint32_t)nblk, pre);
+        BH_LAUNCH_CHECK();
+    }
     hipLaunchKernelGGL(compact_down_kernel, dim3(nblk), dim3(kScanThreads), 0, c->stream, flags, n,
-                       part, idx, count, order, upto, rank);
+                       part, pre, idx, count, order, upto, rank);
     BH_LAUNCH_CHECK();
     return hipSuccess;
 }
 
 int64_t compact_words(int64_t n)
 {
-    return kClassWords * ((n + kScanTile - 1) / kScanTile + 1);
+    return (kClassWords + kGroupClasses) * ((n + kScanTile - 1) / kScanTile + 1);
 }
 
 int64_t sort_blk_words(int64_t n)
