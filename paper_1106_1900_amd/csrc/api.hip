@@ -364,7 +364,7 @@ int load_table(bh_ctx *c, const std::vector<bh_cluster> &cl, int64_t n)
     TRY_ST(staging_ready(c));
     const int64_t K = (int64_t)cl.size();
     int64_t first = 0, nch = 0, nmax = 0;
-    int lmax = 1;
+    int lmax = 1, lmin = 64;
     for (int64_t k = 0; k < K; ++k) {
         const bh_cluster &q = cl[k];
         DevCluster d;
@@ -386,6 +386,7 @@ int load_table(bh_ctx *c, const std::vector<bh_cluster> &cl, int64_t n)
         d.nchunk = (uint32_t)(nch - d.chunk0);
         c->clus_h[k] = d;
         lmax = std::max(lmax, (int)q.nleaf);
+        lmin = std::min(lmin, (int)q.nleaf);
         nmax = std::max(nmax, q.n);
         first += q.n;
     }
@@ -406,6 +407,7 @@ int load_table(bh_ctx *c, const std::vector<bh_cluster> &cl, int64_t n)
         }
     }
     c->max_nleaf = lmax;
+    c->run_leaf = run_leaf(n, K, lmin);
     c->host_clusters = cl;
     c->rec_fresh = false;
     c->any_eps0 = any_zero_eps(cl);

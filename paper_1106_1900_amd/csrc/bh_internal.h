@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "../../include/bh.h"
+#include "moment_rules.h"
 #include "sort_rules.h"
 #include "walk_handout.h"
 
@@ -132,6 +133,7 @@ struct bh_ctx {
     int64_t nbuckets = 0;       // sort buckets of the clusters with several chunks
     int64_t nhist = 0;          // their counts per bucket and chunk
     int max_nleaf = 16;     // largest leaf size over the clusters (LDS halo of the tree build)
+    int run_leaf = 16;      // leaf size by which the moments choose their runs
     int64_t cap_n = 0;      // particle capacity of the buffers
     int64_t cap_c = 0;      // cell capacity
     int64_t cap_k = 0;      // cluster capacity

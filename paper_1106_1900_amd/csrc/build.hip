@@ -535,9 +535,9 @@ __device__ __forceinline__ void level_ranks(bool valid, uint8_t sp, uint8_t lm,
 }
 
 // Where a run of the moments kernels begins: the particle with the lowest split level of
-// every kRunTiles-th tile (the first of them), so that few cells reach across, with
-// that level and the starts of each level before it.
-constexpr int kRunTiles = 4;
+// every first, second or fourth tile (the first of them; see moment_rules.h), so that few
+// cells reach across, with that level and the starts of each level before it.
+static_assert(kTreeTile == kRunTile, "runs are whole tiles");
 struct RunEdge {
     uint32_t x;
     uint32_t split;
@@ -558,7 +558,7 @@ emit_cells_kernel(const uint8_t *__restrict__ split, const uint8_t *__restrict__
                   uint8_t *__restrict__ c_leaf, uint32_t *__restrict__ c_parent,
                   uint32_t *__restrict__ c_child, uint32_t *__restrict__ c_end,
                   uint32_t *__restrict__ c_cend, const uint32_t *__restrict__ pcl,
-                  uint32_t *__restrict__ c_cl, RunEdge *__restrict__ edges)
+                  uint32_t *__restrict__ c_cl, RunEdge *__restrict__ edges, int run_log)
 {
     __shared__ uint32_t s_wc[kTreeTile / kWave][kLevels];
     __shared__ int s_edge[kTreeTile / kWave];
@@ -575,7 +575,7 @@ emit_cells_kernel(const uint8_t *__restrict__ split, const uint8_t *__restrict__
     const bool used = valid && first_lev <= lm;
     const int lo = wave_min_i32(used ? (first_lev > 0 ? first_lev - 1 : 0) : kLevels);
     const int hi = wave_max_i32(used ? (int)lm : -1);
-    const bool edge = blockIdx.x % kRunTiles == 0;      // a run begins in this tile
+    const bool edge = (blockIdx.x & ((1u << run_log) - 1u)) == 0u;      // a run begins in this tile
     if (edge) {
         const int k = wave_min_i32(((int)sp << 8) | (int)threadIdx.x);
         if (threadIdx.x % kWave == 0) s_edge[threadIdx.x / kWave] = k;
@@ -631,7 +631,7 @@ emit_cells_kernel(const uint8_t *__restrict__ split, const uint8_t *__restrict__
         for (int w = 1; w < kTreeTile / kWave; ++w) k = min(k, s_edge[w]);
         const int t0 = k & 255, l = threadIdx.x % kWave;
         if ((int)threadIdx.x / kWave == t0 / kWave) {       // its wavefront: a lane per level
-            RunEdge &e = edges[blockIdx.x / kRunTiles];
+            RunEdge &e = edges[blockIdx.x >> run_log];
             const unsigned long long lt = (1ull << (t0 % kWave)) - 1ull;
             uint32_t c = 0;
             for (int lev = 0; lev < kLevels; ++lev) {
@@ -1135,17 +1135,25 @@ __device__ __forceinline__ void lds_barrier()
 // through LDS (stores to device memory and the loads behind them cost a level 2 us),
 // a run of more than kCap cells through device memory.  The records, which no other
 // cell waits for, come last.  kBox: also the cells' tight boxes (refits).
-template <bool kBox, int kThreads, int kCap, int kRuns>
+// Wavefronts per SIMD that the registers leave room for: as many as the LDS does.
+constexpr int run_waves(bool box, int threads, int cap)
+{
+    if (box) return threads == 512 || cap > 303 ? 2 : (cap > 191 ? 3 : 4);
+    return threads == 256 ? 3 : 4;
+}
+
+template <bool kBox, int kThreads, int kCap, int kRuns, int kTiles>
 __global__ void __launch_bounds__(kThreads)
+__attribute__((amdgpu_waves_per_eu(run_waves(kBox, kThreads, kCap))))
 run_moments_kernel(CellIn in, double4 *__restrict__ c_com, double *__restrict__ c_S,
                    double *__restrict__ box, RecOut ro)
 {
     constexpr uint32_t kTeams = kThreads / kTeam;
     constexpr int kFields = kBox ? 16 : 10;
     static_assert(kCap % 2 == 1, "a cell's fields in different banks");
-    // the staged particles (a run's and as many more as an ordinary leaf can take it
-    // past its end), then the moments of the run's cells (see leaf_moments)
-    constexpr int kStage = (kRuns == 1 ? (kRunTiles + 1) * kTreeTile : kRuns * kRunTiles * kTreeTile) + 64;
+    // the staged particles (a run's, of kTiles tiles, and as many more as an ordinary leaf
+    // can take it past its end), then the moments of the run's cells (see leaf_moments)
+    constexpr int kStage = (kRuns == 1 ? kTiles + 1 : kRuns * kTiles) * kTreeTile + 64;
     constexpr int kStore = kFields * kCap + (kThreads / kWave) * 6 * kTermRow;
     __shared__ double4 s_raw[(kStore / 4 + 1) > kStage ? kStore / 4 + 1 : kStage];
     double(*s_m)[kCap] = reinterpret_cast<double(*)[kCap]>(s_raw);
@@ -1551,7 +1559,7 @@ RunEdge *run_edges(const bh_ctx *c)
 
 int64_t run_edge_words(int64_t n)
 {
-    return (int64_t)(sizeof(RunEdge) / sizeof(uint32_t)) * (n / (kRunTiles * kTreeTile) + 1);
+    return (int64_t)(sizeof(RunEdge) / sizeof(uint32_t)) * most_runs(n);
 }
 
 hipError_t launch_tree(bh_ctx *c)
@@ -1574,7 +1582,8 @@ hipError_t launch_tree(bh_ctx *c)
     hipLaunchKernelGGL(scan ? emit_cells_kernel<true> : emit_cells_kernel<false>, dim3(nblk),
                        dim3(kTreeTile), 0, c->stream, c->split, c->lam, n, blk, nblk, c->misc,
                        c->cap_c, c->c_first, c->c_level, c->c_leaf, c->c_parent, c->c_child,
-                       c->c_end, c->c_nchild, c->pcl, c->c_cl, run_edges(c));
+                       c->c_end, c->c_nchild, c->pcl, c->c_cl, run_edges(c),
+                       run_tiles_log(c->n, c->run_leaf));
     BH_LAUNCH_CHECK();
     int g = grid_for(c->cap_c, kBlock);
     if (g > kFixedGrid) g = kFixedGrid;
@@ -1601,37 +1610,46 @@ hipError_t launch_group_boxes(bh_ctx *c)
     return hipSuccess;
 }
 
-// The leaves and nodes within runs of about 1024 particles, then the nodes across runs:
-// of up to kSpanUnits runs in one workgroup, of more first in units of about 64 runs, a
-// workgroup each, and then across those.  The time is the chain of levels, not the
-// bytes (a level's barrier, its LDS or L2 reads, two divisions): leaves and nodes in one
-// launch per level or group of levels took 28, 89, 110 and 412 us at 1500, 240K and 2^20
-// particles and for 512 clusters of 1024 to 65,536, this 19, 43, 96 and 354.  Units beginning
-// at any multiple of their size, not between large cells: 19, 61, 103, 386.
-// Up to 4096 particles one workgroup's four runs hold the whole system (whole builds:
-// 140 us at 1500 particles and 162 at 4000; four workgroups and one across them 150 and
-// 168), except with boxes, whose moments need more LDS than there is.
+// The leaves and nodes within runs, then the nodes across runs: of up to kSpanUnits runs
+// in one workgroup, of more first in units of about 64 runs, a workgroup each, and then
+// across those.  The time is the chain of levels, not the bytes (a level's barrier, its
+// LDS or L2 reads, two divisions): leaves and nodes in one launch per level or group of
+// levels took 28, 89, 110 and 412 us at 1500, 240K and 2^20 particles and for 512 clusters
+// of 1024 to 65,536, this 19, 43, 96 and 354.  Units beginning at any multiple of their
+// size, not between large cells: 19, 61, 103, 386.  The sizes of the runs and which systems
+// one workgroup holds whole: moment_rules.h.
 // kSpanUnits: as many as the lists of their nodes leave LDS for (builds of 300,000 and
 // 500,000 particles 232 and 261 us, with 256 units, so one launch more, 255 and 286).
 constexpr int kSpanUnits = 512;
+
+template <bool kBox, int kThreads, int kCap, int kTiles>
+void runs_launch(bh_ctx *c, uint32_t runs, const CellIn &in, double *box, const RecOut &ro)
+{
+    hipLaunchKernelGGL((run_moments_kernel<kBox, kThreads, kCap, 1, kTiles>), dim3(runs),
+                       dim3(kThreads), 0, c->stream, in, c->c_com, c->c_S, box, ro);
+}
 
 template <bool kBox>
 hipError_t moments_launches(bh_ctx *c, double *box)
 {
     // every cell's opening radius and walk record are written with its moments
     const RecOut ro{c->clus, c->dom, c->c_level, c->c_cl, c->key[0], c->c_rcrit2, c->c_rec, c->c_geo};
-    const uint32_t runs = (uint32_t)grid_for(c->n, kRunTiles * kTreeTile);
+    const int tiles_log = run_tiles_log(c->n, c->run_leaf);
+    const uint32_t runs = (uint32_t)grid_for(c->n, kTreeTile << tiles_log);
     const CellIn in{c->misc, run_edges(c), runs, c->n, c->lam, c->c_leaf, c->c_first, c->c_count,
                     c->c_child, c->c_nchild, c->p4[c->cur]};
-    if (!kBox && runs <= 4) {
-        hipLaunchKernelGGL((run_moments_kernel<false, 1024, 1279, 4>), dim3(1), dim3(1024), 0,
+    // (with boxes, the moments of a whole system need more LDS than there is)
+    if (!kBox && one_workgroup(c->n, c->K, c->run_leaf)) {
+        hipLaunchKernelGGL((run_moments_kernel<false, 1024, 1279, 16, 1>), dim3(1), dim3(1024), 0,
                            c->stream, in, c->c_com, c->c_S, box, ro);
         BH_LAUNCH_CHECK();
         c->rec_fresh = true;
         return hipSuccess;
     }
-    hipLaunchKernelGGL((run_moments_kernel<kBox, 512, 511, 1>), dim3(runs), dim3(512), 0, c->stream,
-                       in, c->c_com, c->c_S, box, ro);
+    if (tiles_log == 0) runs_launch<kBox, 256, kBox ? 495 : 463, 1>(c, runs, in, box, ro);
+    else if (tiles_log == 1) runs_launch<kBox, 256, kBox ? 191 : 255, 2>(c, runs, in, box, ro);
+    else if (c->n <= (kBox ? kWideRunsBox : kWideRuns)) runs_launch<kBox, 512, 511, 4>(c, runs, in, box, ro);
+    else runs_launch<kBox, 256, kBox ? 303 : 463, 4>(c, runs, in, box, ro);
     BH_LAUNCH_CHECK();
     if (runs > 1) {
         uint32_t depth = 0, units = runs;

@@ -177,6 +177,7 @@ int bh_forces_static(const double *pos, const double *mass, int64_t n, float the
     c.nbuckets = nch > 1 ? nch * sort_sub(&c) : 0;
     c.nhist = c.nbuckets * nch;
     c.max_nleaf = kStaticNleaf;
+    c.run_leaf = run_leaf(n, 1, kStaticNleaf);
     c.any_eps0 = !(eps > 0.0f) || !(eps * eps > 0.0f);
     c.layout += 1;
     if (ctx_enqueue_load(&c, pos, mass) != hipSuccess) {
