@@ -16,7 +16,7 @@ THETA = 0.8
 
 
 @pytest.mark.parametrize("n,nleaf", [
-    (293, 1), (294, 1), (852, 1), (853, 1), (880, 8), (881, 8), (1025, 8), (2556, 8), (2560, 8), (4096, 13),
+    (293, 1), (294, 1), (852, 1), (853, 1), (881, 8), (882, 8), (1025, 8), (2556, 8), (2560, 8), (4096, 13),
     (131_072, 3), (131_073, 2), (131_073, 3), (131_073, 13), (1 << 19, 5), ((1 << 19) + 1, 5),
     ((1 << 19) + 1, 13), ((1 << 21) + 1, 14),
 ])

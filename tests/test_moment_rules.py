@@ -47,7 +47,7 @@ def exe(tmp_path_factory):
 
 @pytest.mark.parametrize("n,k,leaf,tiles,one", [
     (293, 1, 1, 4, True), (294, 1, 1, 1, True), (4096, 1, 16, 4, True), (4097, 1, 16, 4, False),
-    (4096, 1, 8, 1, False), (2500, 1, 8, 1, True), (880, 1, 8, 4, True), (881, 1, 8, 1, True), (4096, 1, 1, 1, False),
+    (4096, 1, 8, 1, False), (2500, 1, 8, 1, True), (881, 1, 8, 4, True), (882, 1, 8, 1, True), (4096, 1, 1, 1, False),
     (131072, 1, 13, 1, False), (131073, 1, 13, 4, False), (1 << 19, 1, 8, 4, False),
     ((1 << 19) + 1, 1, 8, 2, False), (131073, 1, 2, 2, False), (1 << 22, 1, 14, 4, False),
     (2000, 1000, 16, 1, False), (1000000, 500000, 16, 2, False), (1000000, 10000, 16, 4, False),
