@@ -804,14 +804,8 @@ __attribute__((amdgpu_waves_per_eu(BH_WALK_WAVES_PER_EU))) walk_kernel(WalkArgs 
     for (int i = kWave + lane; i < kTileReach; i += kWave) L.tile()[i] = make_float4(kFar, kFar, kFar, 0.0f);
     wave_sync();
 
-    // interaction totals of each wavefront, in LDS: in registers across the walks they cost
-    // seven more spilled scalar and four more spilled vector registers
-    __shared__ unsigned long long s_tot[W][2];
-    __shared__ uint32_t s_over[W];
-    if (lane == 0) {
-        s_tot[w][0] = s_tot[w][1] = 0ull;
-        s_over[w] = 0u;
-    }
+    unsigned long long wave_pp = 0, wave_pc = 0;   // interaction totals of this wavefront
+    bool wave_overflow = false;
     const uint32_t grid_waves = gridDim.x * W;
     const bool sorted = by_class(ngroups, grid_waves);
     // groups at the front of the order that whole workgroups take
@@ -831,11 +825,11 @@ __attribute__((amdgpu_waves_per_eu(BH_WALK_WAVES_PER_EU))) walk_kernel(WalkArgs 
             if (lane == 0) {
                 a.g_npp[g] = npp;
                 a.g_npc[g] = npc;
-                s_tot[w][0] += (unsigned long long)npp * (unsigned long long)gn;
-                s_tot[w][1] += (unsigned long long)npc * (unsigned long long)gn;
             }
+            wave_pp += (unsigned long long)npp * (unsigned long long)gn;
+            wave_pc += (unsigned long long)npc * (unsigned long long)gn;
         }
-        if (lane == 0 && overflow) s_over[w] = 1u;
+        wave_overflow |= overflow;
         __syncthreads();
         slot = readfirst(s_next[turn]);
         turn ^= 1;
@@ -860,14 +854,21 @@ __attribute__((amdgpu_waves_per_eu(BH_WALK_WAVES_PER_EU))) walk_kernel(WalkArgs 
         if (lane == 0) {
             a.g_npp[g] = npp;
             a.g_npc[g] = npc;
-            s_tot[w][0] += (unsigned long long)npp * (unsigned long long)gn;
-            s_tot[w][1] += (unsigned long long)npc * (unsigned long long)gn;
-            if (overflow) s_over[w] = 1u;
         }
+        wave_pp += (unsigned long long)npp * (unsigned long long)gn;
+        wave_pc += (unsigned long long)npc * (unsigned long long)gn;
+        wave_overflow |= overflow;
         wave_sync();
     }
     // the block's totals go to its own slot (summed by walk_sum_kernel): thousands
     // of workgroups adding to one address at the end of the kernel serialise
+    __shared__ unsigned long long s_tot[W][2];
+    __shared__ uint32_t s_over[W];
+    if (lane == 0) {
+        s_tot[w][0] = wave_pp;
+        s_tot[w][1] = wave_pc;
+        s_over[w] = wave_overflow ? 1u : 0u;
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
         unsigned long long pp = 0, pc = 0;
