@@ -235,7 +235,7 @@ int ensure_capacity(bh_ctx *c, int64_t n, int64_t K, int nleaf_min)
         if (bytes_for(c, z) > c->p.hbm_budget_bytes)
             return fail(c, BH_ENOMEM, "particle count exceeds the context's memory budget");
     }
-    // the walk stack packs a cell index into 29 bits
+    // the walk stack packs a cell index into 29 bits where it leaves LDS (CellStack)
     if (z.cells >= (int64_t)1 << 29) {
         z = sizes_for(c, n, K, nleaf_min);
         if (z.cells >= (int64_t)1 << 29)

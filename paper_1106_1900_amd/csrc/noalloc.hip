@@ -24,8 +24,9 @@ namespace {
 constexpr int64_t kStaticMaxN = BH_STATIC_MAX_N;
 constexpr int kStaticNleaf = 16;
 constexpr int kStaticNcrit = 64;
-// Wavefronts of the walk grid: one workgroup of four per CU of a 256-CU device
-// (each wavefront owns a stack spill region of the array).
+// Wavefronts of the walk grid: one workgroup of four per CU of a 256-CU device, or half
+// as many of eight up to 8192 particles (each wavefront owns a stack spill region of 5 KiB
+// of the array, and a context's 4096 would not fit it).
 constexpr int64_t kStaticWaves = 1024;
 // Size of the array: the carved layout for kStaticMaxN particles needs about
 // 35 MB; the first call checks the layout against it.

@@ -31,9 +31,12 @@ __host__ __device__ constexpr uint8_t group_class(uint32_t size, uint32_t n)
 
 // Whether the groups are taken by class (each class in Morton order), of `waves`
 // wavefronts in the grid (V; 4096: all that are resident at once).  2^20 particles
-// (55,388 groups): 1.69 -> 1.56 ms; 240,002: 0.38 -> 0.29 ms.  Above, Morton order alone:
-// the groups at work then span less of the tree, and 470,942 groups of a batch took 7.97 ms
-// so, 8.6 ms by size (the rest of a launch is long enough to hide its end).
+// (55,388 groups): 1.69 -> 1.56 ms; 240,002: 0.38 -> 0.29 ms; 81,660 groups 2.50 -> 2.33,
+// 80,000 of a galaxy at theta = 0.4 6.64 -> 6.26.  Above, Morton order alone: the groups at
+// work then span less of the tree.  Single systems still gain a little by class (119,542
+// groups 3.43 and 3.33 ms, 160,000 4.58 and 4.51, 216,204 the same), but the groups of many
+// clusters lose more (two steps of 200 clusters of 12,000 particles 4.88 ms in Morton order,
+// 5.60 by class, of 400 of 8000 6.32 and 7.35; 470,942 groups 7.97 and 8.6 a walk).
 __host__ __device__ constexpr bool by_class(uint64_t ngroups, uint64_t waves)
 {
     return ngroups <= 24 * waves;
