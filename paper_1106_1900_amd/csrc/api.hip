@@ -145,8 +145,7 @@ Sizes sizes_for(bh_ctx *c, int64_t n, int64_t K, int nleaf_min)
     z.K = K;
     z.chunks = n / kChunk + K + 1;     // every layout with <= n particles, <= K clusters
     z.cells = cell_bound(n, K, nleaf_min);
-    z.blk = std::max(sort_blk_words(n),
-                     level_rows_words(n) + compact_words(n) + run_edge_words(n));
+    z.blk = std::max(sort_blk_words(n), level_rows_words(n) + run_edge_words(n));
     z.spill_waves = walk_grid_waves(c);
     return z;
 }
@@ -189,7 +188,7 @@ hipError_t each_buffer(bh_ctx *c, const Sizes &z, F f)
     B(c->bins, z.n);
     B(c->pbase, z.n);
     B(c->walk_spill, walk_spill_words(z.spill_waves));
-    B(c->walk_part, 2 * z.spill_waves);
+    B(c->walk_part, 2 * (z.spill_waves / kWalkWaves));
     B(c->g_first, z.n);
     B(c->g_count, z.n);
     B(c->g_npp, z.n);

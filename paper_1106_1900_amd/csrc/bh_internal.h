@@ -270,11 +270,10 @@ constexpr int kSortOver = 16;              // candidates per bucket
 hipError_t compact_flags(bh_ctx *c, const uint8_t *flags, int64_t n, uint32_t *idx,
                          uint32_t *count, uint32_t *order, uint32_t *upto, bool rank);
 int64_t sort_blk_words(int64_t n);
-int64_t compact_words(int64_t n);
 int64_t run_edge_words(int64_t n);         // build.hip
 // words at the front of blk that hold the scanned starts per level and tile and the
-// level totals; the compaction's counts and the runs' edges follow (the edges last from
-// a build to the next: the moments of a refit read them too)
+// level totals, then, once the cells are made, the compactions' counts; the runs' edges
+// follow (they last from a build to the next: the moments of a refit read them too)
 constexpr int64_t level_rows_words(int64_t n)
 {
     return (int64_t)(kLevels + 1) * ((n + kTreeTile - 1) / kTreeTile + 1);

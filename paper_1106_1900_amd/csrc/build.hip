@@ -1549,10 +1549,10 @@ hipError_t launch_reorder(bh_ctx *c, const uint32_t *perm)
 
 namespace {
 
-// the runs' edges, behind the level rows and the compaction's counts
+// the runs' edges, behind the level rows
 RunEdge *run_edges(const bh_ctx *c)
 {
-    return reinterpret_cast<RunEdge *>(c->blk + level_rows_words(c->n) + compact_words(c->n));
+    return reinterpret_cast<RunEdge *>(c->blk + level_rows_words(c->n));
 }
 
 }  // namespace

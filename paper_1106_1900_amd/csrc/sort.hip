@@ -1130,16 +1130,20 @@ constexpr int kCountBlocks = 4;
 // below the launch costs 2 us more than it saves.
 constexpr int kScanBlocks = 2048;
 
+// the counts of a block of kScanTile flags fit the level rows of its tiles
+static_assert((kClassWords + kGroupClasses) * kTreeTile <= (kLevels + 1) * kScanTile &&
+              kClassWords + 2 * kGroupClasses <= 2 * (kLevels + 1), "room for the compaction's counts");
+
 hipError_t compact_flags(bh_ctx *c, const uint8_t *flags, int64_t n, uint32_t *idx,
                          uint32_t *count, uint32_t *order, uint32_t *upto, bool rank)
 {
     // one block at least, so that the counts are written for n = 0 too
     const int nblk = std::max(1, (int)((n + kScanTile - 1) / kScanTile));
-    // behind the level rows (which the cells are made from) and before the runs' edges
+    // in the place of the level rows, which the cells have been made from
     ClassCounts *part = nullptr;
     uint32_t *pre = nullptr;
     if (nblk > kCountBlocks) {
-        part = reinterpret_cast<ClassCounts *>(c->blk + level_rows_words(c->n));
+        part = reinterpret_cast<ClassCounts *>(c->blk);
         hipLaunchKernelGGL(scan_reduce_kernel, dim3(nblk), dim3(kScanThreads), 0, c->stream, flags, n,
                            part);
         BH_LAUNCH_CHECK();
@@ -1154,11 +1158,6 @@ hipError_t compact_flags(bh_ctx *c, const uint8_t *flags, int64_t n, uint32_t *i
                        part, pre, idx, count, order, upto, rank);
     BH_LAUNCH_CHECK();
     return hipSuccess;
-}
-
-int64_t compact_words(int64_t n)
-{
-    return (kClassWords + kGroupClasses) * ((n + kScanTile - 1) / kScanTile + 1);
 }
 
 int64_t sort_blk_words(int64_t n)
