@@ -1024,10 +1024,11 @@ mark_active_groups_kernel(const DevMisc *__restrict__ m, const uint32_t *__restr
     const uint32_t t = blockIdx.x * 256 + threadIdx.x, l = t % kSeg, step = gridDim.x * (256 / kSeg);
     for (uint32_t g = t / kSeg; g < ngroups; g += step) {
         const uint32_t s = g_first[g], cnt = g_count[g];
+        const uint32_t cn = clus[pcl[s]].n;     // (in flight with the flags' chain)
         bool any = false;
         for (uint32_t i = l; i < cnt; i += kSeg) any |= active(pid[s + i]);
         const uint32_t seg = (uint32_t)(ballot(any) >> (lane_id() & ~(int)(kSeg - 1))) & 0xffffu;
-        if (l == 0) flags[g] = seg ? group_class(cnt, clus[pcl[s]].n) : (uint8_t)0;
+        if (l == 0) flags[g] = seg ? group_class(cnt, cn) : (uint8_t)0;
     }
     for (int64_t g = (int64_t)ngroups + t; g < n; g += (int64_t)gridDim.x * 256) flags[g] = 0;
 }
