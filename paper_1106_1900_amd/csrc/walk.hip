@@ -809,8 +809,8 @@ __attribute__((amdgpu_waves_per_eu(BH_WALK_WAVES_PER_EU))) walk_kernel(WalkArgs 
     const uint32_t grid_waves = gridDim.x * W;
     const bool sorted = by_class(ngroups, grid_waves);
     // groups at the front of the order that whole workgroups take
-    const int team = team_class(ngroups, grid_waves);
-    const uint32_t teams = team ? readfirst(a.upto[team - 1]) : 0u;
+    const bool few = short_lists(a.misc->depth, a.clus[0].theta, a.clus[0].mac);
+    const uint32_t teams = readfirst(team_groups(a.upto, ngroups, grid_waves, gridDim.x, few));
     __shared__ uint32_t s_next[2];
     int turn = 0;
     for (uint32_t slot = blockIdx.x; slot < teams;) {

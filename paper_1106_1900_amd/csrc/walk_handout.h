@@ -42,7 +42,17 @@ __host__ __device__ constexpr bool by_class(uint64_t ngroups, uint64_t waves)
     return ngroups <= 24 * waves;
 }
 
-// The least class of the groups that teams walk (0: no teams), by the number of groups:
+// Whether groups of 17 to 32 particles have lists too short for a team: by Eq. (1) at a
+// large opening angle, in a system without a dense centre (whose tree is shallow).  8192
+// particles of a uniform cube, theta = 0.75: 32 us by single wavefronts, 43 by teams from 17
+// up; at 0.4, 87 and 68, by the minimum distance 62 and 56.
+__host__ __device__ constexpr bool short_lists(uint32_t depth, float theta, uint32_t mac)
+{
+    return depth < 6 && mac == 0 && theta > 0.55f;
+}
+
+// How many groups at the front of the order teams walk; upto[c]: the groups of class c + 1 or
+// more.  By the number of groups:
 //   up to 4 V     those of 65 and more (two or three particles per lane): 7210 groups of
 //                 up to 128: 0.40 -> 0.23 ms;
 //   up to 1.5 V   so are those of 49 and more: 5376 groups 0.60 -> 0.54 ms (with 33
@@ -53,12 +63,22 @@ __host__ __device__ constexpr bool by_class(uint64_t ngroups, uint64_t waves)
 //                 many lanes share already: 4096 particles in groups of up to 16 (1400
 //                 of them at most) 91 us so, 79 by teams from 9 up and 151 by teams
 //                 from 1 up, 1000 groups of one particle 32 and 93.
-__host__ __device__ constexpr int team_class(uint64_t ngroups, uint64_t waves)
+// Of these the largest classes that hold no more groups than there are workgroups: where most
+// groups are large (a uniform system) they need no help against the tail, and teams walk
+// the tree several times for each of them in several rounds.  200,000 particles of a uniform
+// cube, 2024 groups of 49 and more of 4572: 143 us so, 202 by teams; 412,977 in groups of up
+// to 128, 390 and 465.
+__host__ __device__ inline uint32_t team_groups(const uint32_t *upto, uint64_t ngroups, uint64_t waves,
+                                                uint32_t workgroups, bool short_lists)
 {
-    if (4 * ngroups <= waves) return group_class(17);
-    if (8 * ngroups <= 5 * waves) return group_class(33);
-    if (2 * ngroups <= 3 * waves) return group_class(49);
-    if (ngroups <= 4 * waves) return group_class(65);
+    if (ngroups > 4 * waves) return 0;
+    int c = group_class(65);
+    if (4 * ngroups <= waves) c = group_class(17);
+    else if (8 * ngroups <= 5 * waves) c = group_class(33);
+    else if (2 * ngroups <= 3 * waves) c = group_class(49);
+    if (short_lists && c < group_class(33)) c = group_class(33);
+    for (; c <= kGroupClasses; ++c)
+        if (upto[c - 1] <= workgroups) return upto[c - 1];
     return 0;
 }
 

@@ -1,6 +1,7 @@
 """CPU tests of the walk's hand-out rules (walk_handout.h): which groups whole workgroups
 walk.  Groups of up to 16 particles and those of small clusters have short lists, and a
-workgroup for each of them leaves the others waiting."""
+workgroup for each of them leaves the others waiting; where most groups are large, teams
+would walk the tree for each of them in several rounds."""
 
 import os
 import subprocess
@@ -15,36 +16,82 @@ SRC = r"""
 #include <cstdio>
 #include <cstdlib>
 #include "walk_handout.h"
-int main(int, char **a)
+using namespace bh;
+int main(int argc, char **a)
 {
-    std::printf("%d %d", bh::group_class(std::atoi(a[1]), std::atoi(a[2])),
-                bh::team_class(std::atoi(a[3]), std::atoi(a[4])));
+    // depth theta mac waves per workgroup, then pairs: groups, size (of clusters of 10,000)
+    uint32_t upto[kGroupClasses] = {}, n = 0;
+    for (int i = 6; i + 1 < argc; i += 2) {
+        const uint32_t count = std::atoi(a[i]);
+        for (int c = 0; c < group_class(std::atoi(a[i + 1]), 10000u); ++c) upto[c] += count;
+        n += count;
+    }
+    const int waves = std::atoi(a[4]), per = std::atoi(a[5]);
+    std::printf("%u", team_groups(upto, n, waves, waves / per,
+                                  short_lists(std::atoi(a[1]), std::atof(a[2]), std::atoi(a[3]))));
 }
+"""
+CLASSES = r"""
+#define __host__
+#define __device__
+#include <cstdio>
+#include <cstdlib>
+#include "walk_handout.h"
+int main(int, char **a) { std::printf("%d", bh::group_class(std::atoi(a[1]), std::atoi(a[2]))); }
 """
 
 
-@pytest.fixture(scope="module")
-def by_team(tmp_path_factory):
-    d = tmp_path_factory.mktemp("handout")
-    (d / "rules.cpp").write_text(SRC)
-    exe = str(d / "rules")
-    subprocess.check_call(["g++", "-std=c++17", "-I", CSRC, str(d / "rules.cpp"), "-o", exe])
+def _compile(d, name, text):
+    (d / (name + ".cpp")).write_text(text)
+    subprocess.check_call(["g++", "-std=c++17", "-I", CSRC, str(d / (name + ".cpp")), "-o",
+                           str(d / name)])
 
-    def run(size, cluster, ngroups, waves=4096):
-        out = subprocess.run([exe, *map(str, (size, cluster, ngroups, waves))],
-                             capture_output=True, text=True, check=True).stdout.split()
-        cls, least = map(int, out)
-        return least > 0 and cls >= least
+    def run(*args):
+        out = subprocess.run([str(d / name), *map(str, args)], capture_output=True, text=True,
+                             check=True)
+        return int(out.stdout)
     return run
 
 
-@pytest.mark.parametrize("size,cluster,ngroups,team", [
-    (1, 1000, 1000, False), (8, 1000, 100, False), (16, 3000, 684, False), (17, 3000, 684, True),
-    (64, 4096, 276, True), (2, 2, 1000, False), (64, 64, 500, False), (64, 320, 10, False),
-    (64, 321, 10, True),
-    (32, 9000, 1025, False), (33, 9000, 1025, True), (33, 9000, 2560, True), (33, 9000, 2561, False),
-    (49, 60000, 6144, True), (49, 60000, 6145, False), (65, 60000, 16384, True),
-    (128, 200000, 16385, False),
+@pytest.fixture(scope="module")
+def teams(tmp_path_factory):
+    run = _compile(tmp_path_factory.mktemp("handout"), "teams", SRC)
+
+    def of(groups, depth=10, theta=0.75, mac=0, waves=4096, per=4):
+        return run(depth, theta, mac, waves, per, *[x for g in groups for x in g])
+    return of
+
+
+@pytest.mark.parametrize("size,cluster,same", [
+    (1, 400, 8), (8, 400, 1), (9, 400, 16), (17, 321, 32), (33, 400, 48), (49, 400, 64),
+    (65, 400, 128), (64, 64, 1), (64, 320, 1), (2, 2, 1),
 ])
-def test_which_groups_teams_walk(by_team, size, cluster, ngroups, team):
-    assert by_team(size, cluster, ngroups) == team
+def test_classes(tmp_path, size, cluster, same):
+    cls = _compile(tmp_path, "classes", CLASSES)
+    assert cls(size, cluster) == cls(same, max(cluster, 321) if cluster > 320 else cluster)
+
+
+@pytest.mark.parametrize("groups,want", [
+    ([(1000, 1)], 0), ([(684, 16)], 0), ([(200, 16), (300, 17)], 300),
+    ([(1024, 32)], 1024), ([(1025, 32)], 0), ([(1000, 32), (25, 33)], 25),
+    ([(2500, 32), (60, 33)], 60), ([(2500, 32), (61, 33)], 0), ([(2500, 32), (61, 49)], 61),
+    ([(6000, 32), (144, 49)], 144), ([(6000, 32), (145, 49)], 0), ([(6000, 32), (145, 65)], 145),
+    ([(16000, 32), (384, 65)], 384), ([(16000, 32), (385, 65)], 0),
+    # more of a class than there are workgroups: the next one, or none
+    ([(1025, 49)], 0), ([(1025, 49), (3, 65)], 3), ([(2000, 20), (1024, 49)], 1024),
+    ([(4000, 65)], 0),
+])
+def test_which_groups_teams_walk(teams, groups, want):
+    assert teams(groups) == want
+
+
+def test_wide_workgroups(teams):
+    assert teams([(512, 32)], per=8) == 512
+    assert teams([(513, 32), (2, 33)], per=8) == 2
+
+
+@pytest.mark.parametrize("depth,theta,mac,want", [
+    (4, 0.75, 0, 7), (6, 0.75, 0, 307), (4, 0.55, 0, 307), (4, 0.75, 1, 307),
+])
+def test_short_lists(teams, depth, theta, mac, want):
+    assert teams([(300, 20), (7, 40)], depth, theta, mac) == want
