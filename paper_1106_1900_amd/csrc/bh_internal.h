@@ -265,8 +265,8 @@ int sort_sub(const bh_ctx *c);             // buckets per chunk (0: radix sort)
 uint64_t *sort_candidates(bh_ctx *c);      // where the keys kernel puts the candidates
 constexpr int kSortOver = 16;              // candidates per bucket
 // Positions of the non-zero flags (group classes) to idx, their number to *count;
-// the same items (positions, or with rank places in idx) by descending class to
-// order, and to upto[c] how many are of class c + 1 or more.
+// the same items (positions, or with rank places in idx) to order by descending class,
+// those below first_own_class as one, and to upto[c] how many are of class c + 1 or more.
 hipError_t compact_flags(bh_ctx *c, const uint8_t *flags, int64_t n, uint32_t *idx,
                          uint32_t *count, uint32_t *order, uint32_t *upto, bool rank);
 int64_t sort_blk_words(int64_t n);

@@ -321,16 +321,17 @@ class_scan_kernel(const ClassCounts *__restrict__ part, uint32_t nblk, uint32_t 
 
 // Writes the positions of set flags, in order, to idx[0..count), and the same items
 // (their positions, or with rank their places in idx) to order: the highest class
-// first, each class in order.  The class counts of the blocks before a block and of all
-// blocks come from class_scan_kernel (pre), or, where that is null, each block adds up the
-// blocks' counts (part, from scan_reduce_kernel) or, where that is null too, counts the
-// flags itself.  The last block also writes count and upto[c] = the items of class c + 1
-// or more.
+// first, each class in order, those below first_own_class as one.  The class counts of
+// the blocks before a block and of all blocks come from class_scan_kernel (pre), or, where
+// that is null, each block adds up the blocks' counts (part, from scan_reduce_kernel) or,
+// where that is null too, counts the flags itself.  The last block also writes count and
+// upto[c] = the items of class c + 1 or more.
 __global__ void __launch_bounds__(kScanThreads)
 compact_down_kernel(const uint8_t *__restrict__ flags, int64_t n,
                     const ClassCounts *__restrict__ part, const uint32_t *__restrict__ pre,
                     uint32_t *__restrict__ idx, uint32_t *__restrict__ count,
-                    uint32_t *__restrict__ order, uint32_t *__restrict__ upto, bool rank)
+                    uint32_t *__restrict__ order, uint32_t *__restrict__ upto, uint32_t waves,
+                    uint32_t clusters, bool rank)
 {
     __shared__ uint32_t s_tmp[4];
     __shared__ uint32_t s_sum[2][kGroupClasses];    // before this block, in all blocks
@@ -397,6 +398,11 @@ compact_down_kernel(const uint8_t *__restrict__ flags, int64_t n,
         if (last) upto[k] = first;
     }
     if (last) *count = first;
+    const int own = first_own_class(first, waves, clusters);
+    uint32_t back = 0;      // the place of the next item of the classes below it
+#pragma unroll
+    for (int k = 0; k < kGroupClasses; ++k)
+        back += k + 1 < own ? s_sum[0][k] + class_count(x, k) : s_sum[1][k];
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
         if (!f[k]) continue;
@@ -404,7 +410,7 @@ compact_down_kernel(const uint8_t *__restrict__ flags, int64_t n,
         idx[run++] = (uint32_t)(base + k);
 #pragma unroll
         for (int q = 0; q < kGroupClasses; ++q)
-            if (f[k] == q + 1) order[next[q]++] = item;
+            if (f[k] == q + 1) order[f[k] < own ? back++ : next[q]++] = item;
     }
 }
 
@@ -1155,7 +1161,8 @@ hipError_t compact_flags(bh_ctx *c, const uint8_t *flags, int64_t n, uint32_t *i
         BH_LAUNCH_CHECK();
     }
     hipLaunchKernelGGL(compact_down_kernel, dim3(nblk), dim3(kScanThreads), 0, c->stream, flags, n,
-                       part, pre, idx, count, order, upto, rank);
+                       part, pre, idx, count, order, upto, (uint32_t)c->walk_spill_waves,
+                       (uint32_t)c->K, rank);
     BH_LAUNCH_CHECK();
     return hipSuccess;
 }

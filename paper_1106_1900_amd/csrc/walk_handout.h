@@ -42,6 +42,25 @@ __host__ __device__ constexpr bool by_class(uint64_t ngroups, uint64_t waves)
     return ngroups <= 24 * waves;
 }
 
+// The smallest class that has its own place in the order; the groups of the classes below
+// follow in Morton order together.  With many groups per wavefront the small classes no
+// longer shorten the end of a launch, and what neighbours have in common in the tree
+// counts, the more the shorter their lists are:
+//   up to 8 V    each class by itself: 300,000 particles of a Plummer sphere (4 V, theta =
+//                0.4) 2.0 ms in Morton order, 1.57 so, 1.70 with those of up to 32 together;
+//                20 clusters of 1000 to 65,536 (6 V) 1.75, 1.47 and 1.57;
+//   above        those of up to 32 particles together: 600,000 in clumps of 200 by the
+//                minimum distance 0.50, 0.54 and 0.52; 1.1M of a Plummer sphere (14 V)
+//                6.05, 5.53 and 5.65;
+//   and in clusters of less than 500 groups on average those of up to 48: 300 clusters of
+//                1000 to 10,000 (18 V, theta = 0.75) 1.01 in Morton order, 1.15 by all
+//                classes, 1.08 with up to 32 and 1.02 with up to 48 together; 60 of 1000
+//                to 50,000 (725 groups each, theta = 0.4) 2.35, 2.05, 2.09 and 2.21.
+__host__ __device__ constexpr int first_own_class(uint64_t ngroups, uint64_t waves, uint64_t clusters)
+{
+    return ngroups <= 8 * waves ? 1 : ngroups < 500 * clusters ? group_class(49) : group_class(33);
+}
+
 // Whether groups of 17 to 32 particles have lists too short for a team: by Eq. (1) at a
 // large opening angle, in a system without a dense centre (whose tree is shallow).  8192
 // particles of a uniform cube, theta = 0.75: 32 us by single wavefronts, 43 by teams from 17

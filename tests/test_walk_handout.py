@@ -95,3 +95,27 @@ def test_wide_workgroups(teams):
 ])
 def test_short_lists(teams, depth, theta, mac, want):
     assert teams([(300, 20), (7, 40)], depth, theta, mac) == want
+
+
+OWN = r"""
+#define __host__
+#define __device__
+#include <cstdio>
+#include <cstdlib>
+#include "walk_handout.h"
+int main(int, char **a)
+{
+    std::printf("%d", bh::first_own_class(std::atoll(a[1]), 4096, std::atoll(a[2])));
+}
+"""
+
+
+@pytest.mark.parametrize("ngroups,clusters,size", [
+    (1, 1, 1), (16385, 1, 1), (32768, 1, 1), (32769, 1, 33), (98304, 1, 33), (75400, 300, 49),
+    (32768, 300, 1), (50000, 100, 33), (49999, 100, 49),
+])
+def test_small_groups_stay_in_tree_order(tmp_path, ngroups, clusters, size):
+    """With several groups per wavefront only the large ones are taken out of Morton order."""
+    own = _compile(tmp_path, "own", OWN)
+    cls = _compile(tmp_path, "classes", CLASSES)
+    assert own(ngroups, clusters) == cls(size, 400)
