@@ -49,16 +49,20 @@ __host__ __device__ constexpr bool by_class(uint64_t ngroups, uint64_t waves)
 //   up to 8 V    each class by itself: 300,000 particles of a Plummer sphere (4 V, theta =
 //                0.4) 2.0 ms in Morton order, 1.57 so, 1.70 with those of up to 32 together;
 //                20 clusters of 1000 to 65,536 (6 V) 1.75, 1.47 and 1.57;
-//   above        those of up to 32 particles together: 600,000 in clumps of 200 by the
-//                minimum distance 0.50, 0.54 and 0.52; 1.1M of a Plummer sphere (14 V)
-//                6.05, 5.53 and 5.65;
+//   above        those of up to 16 particles together: 600,000 of a disc galaxy in groups
+//                of up to 32 (16 V, theta = 0.75) 0.96, 1.01 and 0.96; 2^20 of a Plummer
+//                sphere (13 V) 1.76, 1.64 and 1.65, with up to 32 together 1.68 (at theta =
+//                0.4 5.89, 5.30, 5.34 and 5.45);
 //   and in clusters of less than 500 groups on average those of up to 48: 300 clusters of
 //                1000 to 10,000 (18 V, theta = 0.75) 1.01 in Morton order, 1.15 by all
 //                classes, 1.08 with up to 32 and 1.02 with up to 48 together; 60 of 1000
 //                to 50,000 (725 groups each, theta = 0.4) 2.35, 2.05, 2.09 and 2.21.
+// A single system of many small clumps still loses by it: 1.1M particles in clumps of 200 (17 V)
+// 0.87 in Morton order, 0.89 so, by the minimum distance 1.09 and 1.18; 300,000 (4.7 V)
+// 0.25 and 0.27.
 __host__ __device__ constexpr int first_own_class(uint64_t ngroups, uint64_t waves, uint64_t clusters)
 {
-    return ngroups <= 8 * waves ? 1 : ngroups < 500 * clusters ? group_class(49) : group_class(33);
+    return ngroups <= 8 * waves ? 1 : ngroups < 500 * clusters ? group_class(49) : group_class(17);
 }
 
 // Whether groups of 17 to 32 particles have lists too short for a team: by Eq. (1) at a

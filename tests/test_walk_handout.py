@@ -111,8 +111,8 @@ int main(int, char **a)
 
 
 @pytest.mark.parametrize("ngroups,clusters,size", [
-    (1, 1, 1), (16385, 1, 1), (32768, 1, 1), (32769, 1, 33), (98304, 1, 33), (75400, 300, 49),
-    (32768, 300, 1), (50000, 100, 33), (49999, 100, 49),
+    (1, 1, 1), (16385, 1, 1), (32768, 1, 1), (32769, 1, 17), (98304, 1, 17), (75400, 300, 49),
+    (32768, 300, 1), (50000, 100, 17), (49999, 100, 49),
 ])
 def test_small_groups_stay_in_tree_order(tmp_path, ngroups, clusters, size):
     """With several groups per wavefront only the large ones are taken out of Morton order."""
