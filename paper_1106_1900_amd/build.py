@@ -32,7 +32,7 @@ HIPFLAGS = [
 # single-wavefront loop alone it took 126 VGPRs (four wavefronts per SIMD, no scratch)
 # and walked the 2^20 Plummer sphere 0.4-1.3% faster than with the default strategy
 # (mean walk time of three sets of interleaved A/B runs, 11 pairs).  The kernel that
-# also holds the loop of whole workgroups takes all 128, with 9 of them and 49 scalar
+# also holds the loop of whole workgroups takes all 128, with 8 of them and 47 scalar
 # ones spilled (28 bytes of scratch a lane).  For the other sources the strategy gained
 # nothing.
 SOURCE_FLAGS = {
